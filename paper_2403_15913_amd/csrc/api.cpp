@@ -489,8 +489,8 @@ kkt_status Engine::place(const std::vector<const Symbolic*>& s, const std::vecto
         F.y = I.y + F.col0;
         F.dinv = I.dinv + F.col0;
         F.rw = PD.rows + S.sn_rowofs[k] + F.c;
-        F.done = (const int*)((const char*)I.rs + offsetof(RefineState, done));
-        F.cgdone = (const int*)((const char*)I.cg + offsetof(CgState, done));
+        F.done = (const int*)((const char*)I.rs.p + offsetof(RefineState, done));
+        F.cgdone = (const int*)((const char*)I.cg.p + offsetof(CgState, done));
         F.ch0 = S.ch_ptr[k];
         F.nch = S.ch_ptr[k + 1] - S.ch_ptr[k];
         for (int j = 0; j < 2 && j < F.nch; j++) {

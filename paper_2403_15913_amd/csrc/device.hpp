@@ -9,6 +9,30 @@
 
 namespace kkt {
 
+// A pointer into device memory held in a descriptor, in the global address
+// space on the device. A plain pointer loaded from memory could point
+// anywhere, so its accesses would compile to flat instructions, which also
+// count on the LDS counter: every LDS read behind a flat store then waits for
+// the store's round trip to HBM.
+#if defined(__HIP_DEVICE_COMPILE__)
+#define KKT_GLOBAL __attribute__((address_space(1)))
+#else
+#define KKT_GLOBAL
+#endif
+#if defined(__HIP__)
+#define KKT_HD __host__ __device__
+#else
+#define KKT_HD
+#endif
+template <class T>
+struct dptr {
+    KKT_GLOBAL T* p;
+    dptr() = default;
+    KKT_HD dptr(T* q) : p((KKT_GLOBAL T*)q) {}
+    KKT_HD operator T*() const { return (T*)p; }
+    KKT_HD T* operator->() const { return (T*)p; }
+};
+
 // Entries of K with more than this many products of J entries are assembled
 // by a 16-lane group each instead of one thread (the symbolic analysis lists
 // them once per pattern).
@@ -17,44 +41,44 @@ constexpr int kHeavyPairs = 8;
 struct PatDev {
     int n, m, ns;
     int nlevels;
-    const int* sn_col0;     // ns+1
-    const int* sn_ncol;
-    const int* sn_nrow;
-    const int64_t* sn_rowofs;
-    const int64_t* sn_lofs;
-    const int64_t* sn_uofs;
-    const int64_t* sn_vofs;
-    const int* rows;
-    const int* rel;
-    const int* rel_np;
-    const int* ch_ptr;
-    const int* ch_list;
-    const int64_t* pinv_ofs;  // per ch_list entry
-    const int* pinv;          // parent update row -> child update row, or -1
-    const int64_t* k_snptr;
-    const int* k_loc;
-    const int* k_w;
-    const int* k_diag;
-    const int64_t* k_pptr;
-    const int* pair_a;
-    const int* pair_b;
-    const int* jrow;
-    const int* perm;
-    const int* iperm;
-    const int64_t* sp_ptr;
-    const int* k_csr;
-    const int* sp_col;
-    const int* j_ptr;
-    const int* j_col;
-    const int* jt_ptr;
-    const int* jt_e;
-    const int* jt_row;
+    dptr<const int> sn_col0;     // ns+1
+    dptr<const int> sn_ncol;
+    dptr<const int> sn_nrow;
+    dptr<const int64_t> sn_rowofs;
+    dptr<const int64_t> sn_lofs;
+    dptr<const int64_t> sn_uofs;
+    dptr<const int64_t> sn_vofs;
+    dptr<const int> rows;
+    dptr<const int> rel;
+    dptr<const int> rel_np;
+    dptr<const int> ch_ptr;
+    dptr<const int> ch_list;
+    dptr<const int64_t> pinv_ofs;  // per ch_list entry
+    dptr<const int> pinv;          // parent update row -> child update row, or -1
+    dptr<const int64_t> k_snptr;
+    dptr<const int> k_loc;
+    dptr<const int> k_w;
+    dptr<const int> k_diag;
+    dptr<const int64_t> k_pptr;
+    dptr<const int> pair_a;
+    dptr<const int> pair_b;
+    dptr<const int> jrow;
+    dptr<const int> perm;
+    dptr<const int> iperm;
+    dptr<const int64_t> sp_ptr;
+    dptr<const int> k_csr;
+    dptr<const int> sp_col;
+    dptr<const int> j_ptr;
+    dptr<const int> j_col;
+    dptr<const int> jt_ptr;
+    dptr<const int> jt_e;
+    dptr<const int> jt_row;
     // J by columns in pivot order: the entries of column perm[k] are
     // jtp_ptr[k] .. jtp_ptr[k+1], with their rows and CSR entry indices
-    const int* jtp_ptr;
-    const int* jtp_row;
-    const int* jtp_e;
-    const int* j_colp;      // pivot position of the column of every CSR entry of J
+    dptr<const int> jtp_ptr;
+    dptr<const int> jtp_row;
+    dptr<const int> jtp_e;
+    dptr<const int> j_colp;      // pivot position of the column of every CSR entry of J
 };
 
 struct RefineState {
@@ -98,37 +122,37 @@ struct InstDev {
     // offsets of this instance inside the caller's concatenated arrays
     int64_t w_off, j_off, n_off, m_off;
     // numeric storage owned by the factor
-    double* L;          // supernode panels, column-major, leading dimension = front rows
-    double* U;          // update matrices, column-major u x u
-    double* V;          // solve update vectors
-    double* kval;       // assembled lower-triangle entries of K (grouped by supernode)
-    double* kcsr;       // the same values in the symmetric row lists (both triangles, original rows)
-    double* rpart;      // residual block maxima: 5 per residual block
-    double* js;         // Lifted-KKT: J values scaled by their row's Sigma_s (HyKKT: copy of J)
-    double* dinv;       // reciprocals of the pivots of L (pivot order)
-    double* y;          // permuted work vector (n)
-    double* r;          // residual (n)
-    double* xprev;      // previous refinement iterate (n)
-    double* tn;         // scratch (n)
-    double* fg;         // HyKKT f_gamma in pivot order (n)
-    double* cvec;       // HyKKT Schur right-hand side c (m)
-    double* rvec;       // CG residual (m)
-    double* pvec;       // CG direction (m)
-    double* qvec;       // S_gamma p (m)
-    double* pvec2;      // CG direction, second buffer (m): iterations alternate
-    double* jtv;        // HyKKT: J values by columns in pivot order (jtp_ptr layout)
-    double* k0csr;      // single factors: W + Sigma_x + delta I in the symmetric row lists (kcsr layout)
-    double* jraw;       // Lifted-KKT, single factors: J values by rows (js holds them scaled)
-    double* ssv;        // Lifted-KKT, single factors: Sigma_s (m)
-    double* aug_b;      // augmented solve: condensed right-hand side (n, original numbering)
-    double* aug_t;      // augmented solve: correction K^{-1} b (n)
-    double* aug_e;      // augmented solve: residual (e1 n, e2 m, e4 m)
-    double* aug_prev;   // augmented solve: previous iterate (dx n, ds m, dz m)
-    AugState* aug;
-    double* red;        // per-block partial sums (deterministic reductions)
-    int* status;        // [0] latched status, [1] first failing pivot (permuted index)
-    RefineState* rs;
-    CgState* cg;
+    dptr<double> L;          // supernode panels, column-major, leading dimension = front rows
+    dptr<double> U;          // update matrices, column-major u x u
+    dptr<double> V;          // solve update vectors
+    dptr<double> kval;       // assembled lower-triangle entries of K (grouped by supernode)
+    dptr<double> kcsr;       // the same values in the symmetric row lists (both triangles, original rows)
+    dptr<double> rpart;      // residual block maxima: 5 per residual block
+    dptr<double> js;         // Lifted-KKT: J values scaled by their row's Sigma_s (HyKKT: copy of J)
+    dptr<double> dinv;       // reciprocals of the pivots of L (pivot order)
+    dptr<double> y;          // permuted work vector (n)
+    dptr<double> r;          // residual (n)
+    dptr<double> xprev;      // previous refinement iterate (n)
+    dptr<double> tn;         // scratch (n)
+    dptr<double> fg;         // HyKKT f_gamma in pivot order (n)
+    dptr<double> cvec;       // HyKKT Schur right-hand side c (m)
+    dptr<double> rvec;       // CG residual (m)
+    dptr<double> pvec;       // CG direction (m)
+    dptr<double> qvec;       // S_gamma p (m)
+    dptr<double> pvec2;      // CG direction, second buffer (m): iterations alternate
+    dptr<double> jtv;        // HyKKT: J values by columns in pivot order (jtp_ptr layout)
+    dptr<double> k0csr;      // single factors: W + Sigma_x + delta I in the symmetric row lists (kcsr layout)
+    dptr<double> jraw;       // Lifted-KKT, single factors: J values by rows (js holds them scaled)
+    dptr<double> ssv;        // Lifted-KKT, single factors: Sigma_s (m)
+    dptr<double> aug_b;      // augmented solve: condensed right-hand side (n, original numbering)
+    dptr<double> aug_t;      // augmented solve: correction K^{-1} b (n)
+    dptr<double> aug_e;      // augmented solve: residual (e1 n, e2 m, e4 m)
+    dptr<double> aug_prev;   // augmented solve: previous iterate (dx n, ds m, dz m)
+    dptr<AugState> aug;
+    dptr<double> red;        // per-block partial sums (deterministic reductions)
+    dptr<int> status;        // [0] latched status, [1] first failing pivot (permuted index)
+    dptr<RefineState> rs;
+    dptr<CgState> cg;
 };
 
 // One per front work item, in launch order: what a front's kernels read
@@ -136,20 +160,20 @@ struct InstDev {
 // alone instead of a chain of descriptor lookups. The first two children are
 // inline; later children are read from the pattern arrays.
 struct FrontDesc {
-    const double* kv;       // original entries of K in the front
-    const int* kl;          // their panel places (column << 16 | row)
-    double* L;              // stored panel
-    double* U;              // update matrix (u x u)
-    double* V;              // update vector (u)
-    double* y;              // work vector at the front's first column
-    double* dinv;           // pivot reciprocals at the front's first column
-    const int* rw;          // rows of the update part (instance numbering)
-    const int* done;        // the instance's refinement stop flag
-    const int* cgdone;      // the instance's CG stop flag
-    const double* cU[2];    // first two children: update matrices,
-    const double* cV[2];    //   update vectors,
-    const int* crl[2];      //   relative rows of their update parts,
-    const int* cinv[2];     //   inverse maps (this front's update row -> theirs, or -1),
+    dptr<const double> kv;       // original entries of K in the front
+    dptr<const int> kl;          // their panel places (column << 16 | row)
+    dptr<double> L;              // stored panel
+    dptr<double> U;              // update matrix (u x u)
+    dptr<double> V;              // update vector (u)
+    dptr<double> y;              // work vector at the front's first column
+    dptr<double> dinv;           // pivot reciprocals at the front's first column
+    dptr<const int> rw;          // rows of the update part (instance numbering)
+    dptr<const int> done;        // the instance's refinement stop flag
+    dptr<const int> cgdone;      // the instance's CG stop flag
+    dptr<const double> cU[2];    // first two children: update matrices,
+    dptr<const double> cV[2];    //   update vectors,
+    dptr<const int> crl[2];      //   relative rows of their update parts,
+    dptr<const int> cinv[2];     //   inverse maps (this front's update row -> theirs, or -1),
     int cuc[2], cnb[2];     //   update sizes, and rows mapping into this front's columns
     int r, c, col0, nk;     // rows, columns, first column, entries of K
     int nch, ch0, inst, id; // children, first child in ch_list, instance, supernode

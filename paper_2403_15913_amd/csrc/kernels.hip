@@ -1422,7 +1422,7 @@ __device__ __forceinline__ void fwd_front(const InstDev& I, const FrontDesc& F, 
     // (c <= 128 < threads), and the first entries of the first two
     // children's update vectors with their relative indices.
     constexpr int BU = 8;  // double2 per thread and block in registers (ld < 256)
-    const double2* __restrict__ s2 = (const double2*)F.L;
+    const double2* __restrict__ s2 = (const double2*)(const double*)F.L;
     double2* d2 = (double2*)P;
     const int n2 = even_up(ld * c) >> 1;
     const int bw2 = 8 * ld;
@@ -1595,7 +1595,7 @@ __device__ __forceinline__ void bwd_front(const FrontDesc& F, double* __restrict
     // The update rows' indices are loaded first, so the gather of their
     // values waits only for them while the panel loads stay in flight.
     int ri = u > 0 ? rw[min(tid, u - 1)] : 0;
-    const double2* __restrict__ s2 = (const double2*)F.L;
+    const double2* __restrict__ s2 = (const double2*)(const double*)F.L;
     double2* d2 = (double2*)P;
     const int n2 = even_up(ld * c) >> 1;
     double2 pv[PU];

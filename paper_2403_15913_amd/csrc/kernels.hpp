@@ -11,21 +11,21 @@ namespace kkt {
 // solve), passed by value. Instance q uses base + its offsets (InstDev
 // w_off / j_off / n_off / m_off), so a batch reads concatenated arrays.
 struct Calls {
-    const double* w;
-    const double* jv;
-    const double* sx;
-    const double* ss;   // NULL -> K_gamma with row weight gamma
+    dptr<const double> w;
+    dptr<const double> jv;
+    dptr<const double> sx;
+    dptr<const double> ss;   // NULL -> K_gamma with row weight gamma
     double gamma;
     double delta;       // primal regularisation added to the diagonal of K (inertia correction)
-    const int* eqm;     // general HyKKT: 1 for the equality rows of J (weight gamma), 0 for the
+    dptr<const int> eqm;     // general HyKKT: 1 for the equality rows of J (weight gamma), 0 for the
                         // inequality rows (weight sigma_s); NULL otherwise
     int keep_k0;        // assembly also writes K0 (or K_k) into k0csr (single factors that need it)
-    const double* b;    // Lifted-KKT solve
-    double* x;
-    const double* f;    // HyKKT solve
-    const double* g;
-    double* dx;
-    double* dy;
+    dptr<const double> b;    // Lifted-KKT solve
+    dptr<double> x;
+    dptr<const double> f;    // HyKKT solve
+    dptr<const double> g;
+    dptr<double> dx;
+    dptr<double> dy;
 };
 
 constexpr int kBlock = 256;
@@ -38,13 +38,13 @@ static_assert(16 % kResidualSplit == 0, "a 256-row item splits into whole rows p
 // in topological order: parent item (-1 for roots), number of children, and
 // per-item counters reset before every launch.
 struct DepLists {
-    const int* parent;
-    const int* nchild;
-    int* cnt;     // children done (factor / forward sweep)
-    int* fdone;   // root forward step done
-    int* bdone;   // backward step done
-    int* ticket;
-    int* err;     // set when a bounded wait expired
+    dptr<const int> parent;
+    dptr<const int> nchild;
+    dptr<int> cnt;     // children done (factor / forward sweep)
+    dptr<int> fdone;   // root forward step done
+    dptr<int> bdone;   // backward step done
+    dptr<int> ticket;
+    dptr<int> err;     // set when a bounded wait expired
     int nitems;
 };
 
@@ -64,14 +64,14 @@ hipError_t set_kernel_attributes();
 // allocation-free solve): redirected copies of the instance and front
 // descriptors and the vectors a refined solve writes.
 struct SolveWs {
-    InstDev* inst;       // 1
-    FrontDesc* fd;       // one per front, in the factor's launch order
-    double* y;           // n: permuted work vector
-    double* V;           // forward-sweep update vectors (the factor's V layout)
-    double* r;           // n: residual
-    double* xprev;       // n: previous iterate
-    double* rpart;       // residual block maxima
-    RefineState* rs;     // 1
+    dptr<InstDev> inst;       // 1
+    dptr<FrontDesc> fd;       // one per front, in the factor's launch order
+    dptr<double> y;           // n: permuted work vector
+    dptr<double> V;           // forward-sweep update vectors (the factor's V layout)
+    dptr<double> r;           // n: residual
+    dptr<double> xprev;       // n: previous iterate
+    dptr<double> rpart;       // residual block maxima
+    dptr<RefineState> rs;     // 1
 };
 // Writes ws.inst and ws.fd from the factor's descriptors (src_inst[0],
 // src_fd[0 .. nf)) with every per-solve pointer moved into ws.
@@ -79,8 +79,8 @@ void launch_ws_redirect(const InstDev* src_inst, const FrontDesc* src_fd, int nf
 
 // A device-to-device copy of `len` doubles (gathering a served wave's inputs).
 struct CopySeg {
-    const double* src;
-    double* dst;
+    dptr<const double> src;
+    dptr<double> dst;
     int64_t len;
 };
 void launch_copy_segments(const CopySeg* segs, int nseg, hipStream_t st);
@@ -153,12 +153,12 @@ void launch_cg_residual(const InstDev* insts, const Calls& C, const WorkItem* nc
 // Augmented system of eq. (kkt:augmented) without equality rows (see the
 // kernels): the caller's right-hand sides r1, r2, r4 and unknowns dx, ds, dz
 struct AugCall {
-    const double* r1;   // n
-    const double* r2;   // m
-    const double* r4;   // m
-    double* dx;         // n
-    double* ds;         // m
-    double* dz;         // m
+    dptr<const double> r1;   // n
+    dptr<const double> r2;   // m
+    dptr<const double> r4;   // m
+    dptr<double> dx;         // n
+    dptr<double> ds;         // m
+    dptr<double> dz;         // m
 };
 // mode 0: b = -(r1 + J^T (Sigma_s r4 - r2)); mode 1: the same with -r = e,
 // the current residual (correction right-hand side)
@@ -179,22 +179,22 @@ void launch_aug_revert(const InstDev* insts, const AugCall& A, const WorkItem* n
 // Interior-point loop on a convex QP (min 1/2 x^T W x + c^T x, J x <= u) over
 // one factor's pattern; vectors in original numbering (see the kernels)
 struct IpmCall {
-    const double* w;    // W values (lower CSR entry order)
-    const double* jv;   // J values
-    const double* c;    // n
-    const double* u;    // m
-    double* x;          // n
-    double* s;          // m
-    double* z;          // m
-    double* dsw;        // m: D_s = z / s (the refactor's sigma_s)
-    double* r1;         // n
-    double* r2;         // m
-    double* r4;         // m
-    double* dx;         // n
-    double* ds;         // m
-    double* dz;         // m
-    double* red;        // reduction slots (4 per 256-row block of n, then of m)
-    IpmState* st;
+    dptr<const double> w;    // W values (lower CSR entry order)
+    dptr<const double> jv;   // J values
+    dptr<const double> c;    // n
+    dptr<const double> u;    // m
+    dptr<double> x;          // n
+    dptr<double> s;          // m
+    dptr<double> z;          // m
+    dptr<double> dsw;        // m: D_s = z / s (the refactor's sigma_s)
+    dptr<double> r1;         // n
+    dptr<double> r2;         // m
+    dptr<double> r4;         // m
+    dptr<double> dx;         // n
+    dptr<double> ds;         // m
+    dptr<double> dz;         // m
+    dptr<double> red;        // reduction slots (4 per 256-row block of n, then of m)
+    dptr<IpmState> st;
 };
 void launch_ipm_start(const InstDev* insts, const IpmCall& P, const WorkItem* ncols, int nn, const WorkItem* mrows,
                       int nm, double tol, int maxit, double sigma, double tau_min, hipStream_t st);
@@ -230,14 +230,14 @@ struct CrPull {
     int vi, si;          // y_i: first variable (concatenated), width
 };
 struct CrArrays {
-    double* D;           // assembled diagonal blocks (column-major); only the scatter writes them
-    double* L;           // same layout: the updated blocks of stages that stay, then L_k
-    double* C;           // couplings: the assembled E_k first, then the fill blocks
-    double* P;           // off-diagonal factor blocks
-    double* U;           // symmetric updates
-    double* t;           // solve work vector (concatenated numbering)
-    const CrTask* tasks;
-    const CrPull* pulls;
+    dptr<double> D;           // assembled diagonal blocks (column-major); only the scatter writes them
+    dptr<double> L;           // same layout: the updated blocks of stages that stay, then L_k
+    dptr<double> C;           // couplings: the assembled E_k first, then the fill blocks
+    dptr<double> P;           // off-diagonal factor blocks
+    dptr<double> U;           // symmetric updates
+    dptr<double> t;           // solve work vector (concatenated numbering)
+    dptr<const CrTask> tasks;
+    dptr<const CrPull> pulls;
 };
 // an entry of the assembled K (kcsr, lower positions) and its place in D or C
 struct CrScatter {
