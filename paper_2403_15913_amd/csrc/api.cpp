@@ -251,7 +251,7 @@ kkt_status Engine::place(const std::vector<const Symbolic*>& s, const std::vecto
                 if (S.sn_ncol[k] > kLargeFrontCols) return fail(KKT_ERR_PATTERN, "large front wider than 64 columns");
                 n_large++;
             } else {
-                lds_factor = std::max(lds_factor, (size_t)factor_lds_bytes(S.sn_nrow[k], S.sn_ncol[k]));
+                lds_factor = std::max(lds_factor, (size_t)factor_launch_lds_bytes(S.sn_nrow[k], S.sn_ncol[k]));
                 lds_solve = std::max(lds_solve, (size_t)solve_lds_bytes(S.sn_nrow[k], S.sn_ncol[k]));
             }
             const size_t nbu = (size_t)(S.sn_nrow[k] - S.sn_ncol[k] + 15) / 16;
@@ -443,7 +443,7 @@ kkt_status Engine::place(const std::vector<const Symbolic*>& s, const std::vecto
                 lvl_lmaxr[l] = std::max(lvl_lmaxr[l], S.sn_nrow[sn[t].id]);
             } else {
                 lvl_maxu[l] = std::max(lvl_maxu[l], u);
-                lvl_flds[l] = std::max(lvl_flds[l], (size_t)factor_lds_bytes(S.sn_nrow[sn[t].id], S.sn_ncol[sn[t].id]));
+                lvl_flds[l] = std::max(lvl_flds[l], (size_t)factor_launch_lds_bytes(S.sn_nrow[sn[t].id], S.sn_ncol[sn[t].id]));
                 lvl_maxc[l] = std::max(lvl_maxc[l], S.sn_ncol[sn[t].id]);
             }
             const int nbu = (u + 15) / 16;

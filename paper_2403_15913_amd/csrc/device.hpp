@@ -7,6 +7,8 @@
 #pragma once
 #include <cstdint>
 
+#include "lds_layout.hpp"
+
 namespace kkt {
 
 // A pointer into device memory held in a descriptor, in the global address
@@ -18,11 +20,6 @@ namespace kkt {
 #define KKT_GLOBAL __attribute__((address_space(1)))
 #else
 #define KKT_GLOBAL
-#endif
-#if defined(__HIP__)
-#define KKT_HD __host__ __device__
-#else
-#define KKT_HD
 #endif
 template <class T>
 struct dptr {

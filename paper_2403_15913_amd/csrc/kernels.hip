@@ -30,10 +30,7 @@ namespace kkt {
 #define KKT_BWD_SMALL_PU 16
 #endif
 #ifndef KKT_SMALL_WAVES_PER_EU
-#define KKT_SMALL_WAVES_PER_EU 2
-#endif
-#ifndef KKT_SMALL_EU
-#define KKT_SMALL_EU 12
+#define KKT_SMALL_WAVES_PER_EU 3
 #endif
 #define KKT_ST_NOT_SPD 4
 #define KKT_ST_NONFINITE 5
@@ -322,34 +319,29 @@ __device__ __forceinline__ void static_for(F&& f) {
     static_for_impl(std::make_integer_sequence<int, N>{}, f);
 }
 
-// 16x16 tile of A B^T from a column-major LDS panel P (leading dimension ld):
-// A = rows i0..i0+15, B = rows j0..j0+15, both over columns k0..k0+K-1
-// (K a multiple of 4). Rows >= rlim read as zero.
-__device__ inline d4 tile_abt(const double* P, int ld, int i0, int j0, int k0, int K, int rlim, int lane) {
+// 16x16 tile of A B^T from a column-major panel P (leading dimension ld): A =
+// rows i0..i0+15, B = rows j0..j0+15, both over columns k0..k0+15. Rows >= rlim are read clamped (their results
+// are not used).
+__device__ inline d4 tile_abt(const double* P, int ld, int i0, int j0, int k0, int rlim, int lane) {
     const int lr = lane & 15, lk = lane >> 4;
-    const int ia = i0 + lr, jb = j0 + lr;
-    const bool va = ia < rlim, vb = jb < rlim;
-    // rows clamped into the panel so every load is valid and unpredicated
-    const int iac = min(ia, rlim - 1), jbc = min(jb, rlim - 1);
+    const int iac = min(i0 + lr, rlim - 1), jbc = min(j0 + lr, rlim - 1);
+    const double* const Lk = P + (int64_t)(k0 + lk) * ld;
+    double a[4], b[4];
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        a[q] = Lk[4 * q * ld + iac];
+        b[q] = Lk[4 * q * ld + jbc];
+    }
     d4 acc = {0.0, 0.0, 0.0, 0.0};
-    int kk = 0;
-    for (; kk + 16 <= K; kk += 16) {
-        double a[4], b[4];
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
-            const int col = (k0 + kk + 4 * q + lk) * ld;
-            a[q] = P[col + iac];
-            b[q] = P[col + jbc];
-        }
-#pragma unroll
-        for (int q = 0; q < 4; q++) acc = mfma_f64_16x16x4(va ? a[q] : 0.0, vb ? b[q] : 0.0, acc);
-    }
-    for (; kk < K; kk += 4) {
-        const int col = (k0 + kk + lk) * ld;
-        const double a = P[col + iac], b = P[col + jbc];
-        acc = mfma_f64_16x16x4(va ? a : 0.0, vb ? b : 0.0, acc);
-    }
+    for (int q = 0; q < 4; q++) acc = mfma_f64_16x16x4(a[q], b[q], acc);
     return acc;
+}
+
+// LDS accumulation without a read-back (destinations distinct where order
+// matters); cheaper than a read, an add and a write that wait for each other
+__device__ __forceinline__ void lds_add(double* p, double v) {
+    __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 // Empty asm that takes a value in a vector register: emits nothing, but
@@ -415,233 +407,182 @@ __device__ inline void tri_tile(int t, int tj0, int nb, int& ti, int& tj) {
 // ---------------------------------------------------------------------------
 // multifrontal factorisation of one front per workgroup
 // ---------------------------------------------------------------------------
-// The front panel (r rows x c columns) lives in LDS, column-major with an odd
-// leading dimension. It is assembled from the original entries of K and the
-// children's update matrices, factored in 16-column blocks (diagonal block by
-// one wave in registers, TRSM by all threads, trailing update on the matrix
-// cores), then the update matrix U = -L21 L21^T is formed on the matrix cores
-// and the children's pass-through entries are added to it.
-constexpr int kFactorThreads = 512;
-// small fronts: four waves per workgroup, so several fronts share a
-// compute unit (registers for two workgroups per compute unit at least)
+// The front panel (r rows x c columns) lives in LDS. It is assembled from the
+// original entries of K and the children's update matrices and factored in
+// 16-column blocks; the update matrix U = -L21 L21^T is formed on the matrix
+// cores and the children's pass-through entries are added to it.
+//
+// Bound: neither flops nor bytes but the dependent steps of one front (one per
+// compute unit on most levels) and the instructions each wave issues in them.
+// Clocks of a 66 x 198 front (about 2.4 GHz): children added 20k, a column
+// block 7k (its pivot chain 3.5k), the look-ahead update of the next column
+// block 2.7k. Twelve waves rather than eight, since a wave issues at most
+// every fourth cycle and the updates have that many independent tiles;
+// sixteen spill (128 registers). Measured, factor launches of the paper-scale
+// tree (2,001 fronts, 13 levels): eight waves with a column-major panel 702
+// us, eight waves with the blocked panel 614 us, twelve 570 us, sixteen 671 us.
+constexpr int kFactorThreads = 768;
+constexpr int kFactorQueueThreads = 512;
+// small fronts: four waves per workgroup, so several fronts share a compute
+// unit. 168 registers let three do so where the LDS allows (measured on 256
+// NMPC instances: factor launches 2.53 -> 2.22 ms with the blocked panel,
+// 2.41 ms with two workgroups per compute unit)
 constexpr int kFactorThreadsSmall = 256;
-static_assert(kFactorThreads == 512 && kFactorThreadsSmall == 256,
-              "the panel schedule is written for eight or four waves");
+static_assert(kFactorThreads <= 1024 && kFactorThreadsSmall >= 128, "one panel wave and one update wave at least");
 
-// EU: extend-add entries per thread and batch (register budget of the caller)
-template <int EU>
-__device__ __forceinline__ void factor_front(const InstDev& I, const FrontDesc& F, double* __restrict__ P,
-                                             double* invd, const bool fused_update, const bool fused_panel) {
-    const PatDev& T = I.P;
-    const int c = F.c, r = F.r;
-    const int u = r - c, col0 = F.col0;
-    // descriptor fields used inside the loops below, read once
-    int* const status = I.status;
-    double* const dinv = F.dinv;
-    const double* const Ubase = I.U;
-    const int* const chl = T.ch_list;
-    const int* const sn_ncol = T.sn_ncol;
-    const int* const sn_nrow = T.sn_nrow;
-    const int* const rel_np = T.rel_np;
-    const int64_t* const sn_uofs = T.sn_uofs;
-    const int* const rel = T.rel;
-    const int64_t* const sn_rowofs = T.sn_rowofs;
-    const int ch0 = F.ch0, ch1 = F.ch0 + F.nch;
-    const int rp = rup16(r), cp = rup16(c);
-    const int ld = r | 1;
+// A front's panel in LDS, in column blocks of 16: block kb holds the rows from
+// its diagonal block down, row by row, 16 doubles each, so a lane reaches its
+// row's entries, or its part of a matrix-core operand, with 16-byte accesses
+// at offsets that depend on the lane alone (a wave issues one instruction
+// every four cycles at best, so on a compute unit that holds one front the
+// instruction count of each step is what its time goes by). Rows: the front's
+// own, padded to cp, then the update rows, padded to 16; padding stays zero.
+// Within a row, entry k sits at slot(k), which puts the four columns a lane
+// supplies to four matrix instructions (4q + l / 16 to the q-th) side by
+// side, and the row's eight 16-byte pieces are permuted by the row number, so
+// that consecutive rows spread over the banks.
+constexpr int kRow = kFrontRowStride;
+__device__ __forceinline__ int block_base(const int kb, const int rt) { return kRow * (kb * rt - 8 * kb * (kb + 1)); }
+__device__ __forceinline__ constexpr int slot(const int k) { return ((k & 3) << 2) | (k >> 2); }
+__device__ __forceinline__ int in_row(const int row, const int k) { return slot(k) ^ ((row & 7) << 1); }
+
+// Operand of one 16-row block and 16 columns: lane l holds row l % 16, columns
+// 4q + l / 16 for instruction q. p: the lane's row; o: in_row of column l / 16.
+struct Frag {
+    double2 lo, hi;
+    __device__ __forceinline__ double operator[](const int q) const {
+        return q == 0 ? lo.x : q == 1 ? lo.y : q == 2 ? hi.x : hi.y;
+    }
+};
+__device__ __forceinline__ Frag frag_load(const double* __restrict__ p, const int o) {
+    Frag f;
+    f.lo = *(const double2*)(p + o);
+    f.hi = *(const double2*)(p + (o ^ 2));
+    return f;
+}
+
+// Dense part of a front whose panel is column-major in LDS (leading dimension
+// ld = r | 1): fronts taller than the panel waves can cover. The pivot chain
+// by wave 0 beside the updates, then the rows below the diagonal block by all
+// threads (the blocked path's arithmetic). With eight waves or more, those
+// that share wave 0's SIMD (waves 4, 8) stay out of the updates beside the
+// chain, so the pivot chain has its SIMD to itself.
+template <class UnitF, class StoreF>
+__device__ __forceinline__ void factor_tall(const InstDev& I, const FrontDesc& F, double* __restrict__ P, double* invd,
+                                            const int nuu, UnitF u_unit, StoreF u_store) {
+    const int c = F.c, r = F.r, ld = r | 1;
+    const int cp = rup16(c), nbc = cp >> 4, nbr = rup16(r) >> 4;
     const int tid = threadIdx.x, nt = blockDim.x;
-    const int lane = tid & 63, wave = tid >> 6, nwave = nt >> 6;
-
-    // Assembly of the front: the original entries of K, then the children's
-    // update matrices (entries (a, b), a >= b, whose column b maps into the
-    // panel), child by child in a fixed order (two children can add into the
-    // same entry). The loads of the K entries and of the first batch of the
-    // first two children are all issued before the first wait, so their
-    // memory round trips overlap; later batches are loaded and added in turn.
-    // Loads use clamped indices, nothing is predicated.
-    struct Child {
-        const double* Uc;
-        const int* rl;
-        int uc, nb, tot;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nwave = nt >> 6;
+    const int lr = lane & 15, lk = lane >> 4;
+    struct TFrag {
+        double b[4], a0[4], a1[4];
     };
-    struct ExtBatch {
-        double v[EU];
-        int ra[EU], rb[EU];  // relative row / column
-        unsigned keep;       // bit k: entry k is in range and in the lower part
-    };
-    // child k (0-based): the first two from the front descriptor
-    auto child_at = [&](const int k) {
-        Child C;
-        if (k < 2) {
-            C.uc = k ? F.cuc[1] : F.cuc[0];
-            C.nb = k ? F.cnb[1] : F.cnb[0];
-            C.Uc = k ? F.cU[1] : F.cU[0];
-            C.rl = k ? F.crl[1] : F.crl[0];
-        } else {
-            const int ch = __builtin_amdgcn_readfirstlane(chl[ch0 + k]);
-            const int cc = __builtin_amdgcn_readfirstlane(sn_ncol[ch]);
-            C.uc = __builtin_amdgcn_readfirstlane(sn_nrow[ch]) - cc;
-            C.nb = __builtin_amdgcn_readfirstlane(rel_np[ch]);
-            C.Uc = Ubase + sn_uofs[ch];
-            C.rl = rel + sn_rowofs[ch] + cc;
-        }
-        C.tot = C.nb * C.uc;
-        return C;
-    };
-    // (column, row) of the flat index q0 + k*nt by stepping, not dividing
-    auto ext_load = [&](ExtBatch& B, const Child& C, const int q0) {
-        const int uc = C.uc, tot = C.tot;
-        const int db = nt / uc, da = nt - db * uc;
-        int bq = q0 / uc, aq = q0 - bq * uc;
-        // the keep flags come from the indices alone, so no load waits for
-        // another before all of them are issued
-        B.keep = 0;
+    // columns k0 .. k0 + 15, rows from rb (column operand) and ra (two row
+    // blocks); rows past r are read clamped
+    auto frag = [&](TFrag& G, const int k0, const int rb, const int ra) {
+        const double* const Lk = P + (k0 + lk) * ld;
+        const int ib = min(rb + lr, r - 1), i0 = min(ra + lr, r - 1), i1 = min(ra + 16 + lr, r - 1);
 #pragma unroll
-        for (int k = 0; k < EU; k++) {
-            const int qa = q0 + k * nt;
-            B.keep |= (qa < tot && aq >= bq) ? 1u << k : 0u;
-            B.v[k] = C.Uc[min(qa, tot - 1)];
-            B.ra[k] = C.rl[qa < tot ? aq : uc - 1];
-            B.rb[k] = C.rl[min(bq, C.nb - 1)];
-            aq += da;
-            bq += db;
-            if (aq >= uc) {
-                aq -= uc;
-                bq++;
+        for (int q = 0; q < 4; q++) {
+            G.b[q] = Lk[4 * q * ld + ib];
+            G.a0[q] = Lk[4 * q * ld + i0];
+            G.a1[q] = Lk[4 * q * ld + i1];
+        }
+    };
+    auto mult = [&](const TFrag& G, d4& s0, d4& s1) {
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            s0 = mfma_f64_16x16x4(G.b[q], G.a0[q], s0);
+            s1 = mfma_f64_16x16x4(G.b[q], G.a1[q], s1);
+        }
+    };
+    // block kb's update of the column blocks [tj0, tj1) in two-tile units t0,
+    // t0 + ts, ...; columns past c are not written (they stay zero)
+    auto update_units = [&](const int kb, const int tj0, const int tj1, const int t0, const int ts) {
+        int tj = tj0, t = t0;
+        while (tj < tj1) {
+            const int nu = (nbr - tj + 1) >> 1;
+            if (t >= nu) {
+                t -= nu;
+                tj++;
+                continue;
             }
-        }
-    };
-    auto ext_pin = [&](ExtBatch& B) {
+            const int ti = tj + 2 * t;
+            const int row0 = (ti << 4) + lr, row1 = row0 + 16, cu0 = (tj << 4) + lk;
+            const int ra0 = min(row0, r - 1), ra1 = min(row1, r - 1);
+            TFrag G;
+            frag(G, kb << 4, tj << 4, ti << 4);
+            double p0[4], p1[4];
 #pragma unroll
-        for (int k = 0; k < EU; k++) {
-            pin(B.v[k]);
-            pin(B.ra[k]);
-            pin(B.rb[k]);
-        }
-    };
-    // the destinations of one child are distinct: read all, then write
-    auto ext_add = [&](const ExtBatch& B) {
-        double cur[EU];
-        int dst[EU];
-#pragma unroll
-        for (int k = 0; k < EU; k++) {
-            dst[k] = B.rb[k] * ld + B.ra[k];
-            cur[k] = P[dst[k]];
-        }
-#pragma unroll
-        for (int k = 0; k < EU; k++)
-            if ((B.keep >> k) & 1u) P[dst[k]] = cur[k] + B.v[k];
-    };
-    // all batches of child C; the first one is already loaded when pre
-    auto ext_child = [&](const Child& C, ExtBatch& B, const bool pre) {
-        for (int q0 = tid; q0 < C.tot; q0 += nt * EU) {
-            if (!(pre && q0 == tid)) {
-                ext_load(B, C, q0);
-                ext_pin(B);
+            for (int e = 0; e < 4; e++) {
+                p0[e] = P[(cu0 + 4 * e) * ld + ra0];
+                p1[e] = P[(cu0 + 4 * e) * ld + ra1];
             }
-            ext_add(B);
+            d4 s0 = {0.0, 0.0, 0.0, 0.0}, s1 = s0;
+            mult(G, s0, s1);
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                if (row0 < r && cu0 + 4 * e < c) P[(cu0 + 4 * e) * ld + row0] = p0[e] - s0[e];
+                if (row1 < r && cu0 + 4 * e < c) P[(cu0 + 4 * e) * ld + row1] = p1[e] - s1[e];
+            }
+            t += ts;
+        }
+    };
+    const bool many = nwave >= 8;
+    const int upd_w = wave - 1 - (many ? wave >> 2 : 0), upd_n = many ? nwave - nwave / 4 : nwave - 1;
+    for (int ph = 0;; ph++) {
+        const bool la = ph & 1;
+        const int kb = ph >> 1;
+        const int j0 = kb << 4, w = min(16, c - j0);
+        if (!la && wave == 0) {
+            // Each 16-lane row of the wave holds the block, lane i of a row
+            // holding row j0+i (entries right of the diagonal are never read
+            // back; rows past r are zero).
+            const bool live = j0 + lr < r;
+            const int row = min(j0 + lr, r - 1);
+            double a[16];
+#pragma unroll
+            for (int k = 0; k < 16; k++) a[k] = P[(j0 + k) * ld + row];
+            if (!live) {
+#pragma unroll
+                for (int k = 0; k < 16; k++) a[k] = 0.0;
+            }
+            static_for<16>([&](auto J) {
+                constexpr int j = J;
+                if (j < w) {
+                    double d = readfirstlane_d(row_bcast<j>(a[j]));
+                    if (!(d > 0.0) || !isfinite(d)) {
+                        if (lane == 0) {
+                            int* const status = I.status;
+                            atomicMin(&status[1], F.col0 + j0 + j);
+                            atomicMax(&status[0], KKT_ST_NOT_SPD);
+                        }
+                        d = 1.0;
+                    }
+                    double inv, ljj;
+                    pivot_roots(d, inv, ljj);
+                    a[j] = lr == j ? ljj : a[j] * inv;
+                    if (lane == 0) invd[j] = inv;
+                    static_for<16>([&](auto K) {
+                        constexpr int k = K;
+                        if constexpr (k > j) a[k] = fma(-a[j], row_bcast<k>(a[j]), a[k]);
+                    });
+                }
+            });
+            if (lane < 16 && live) {
+#pragma unroll
+                for (int k = 0; k < 16; k++)
+                    if (k < w && k <= lr) P[(j0 + k) * ld + j0 + lr] = a[k];
+            }
+        } else if (la || (kb > 0 && !(many && (wave & 3) == 0))) {
+            update_units(la ? kb : kb - 1, kb + 1, la ? kb + 2 : nbc, la ? wave : upd_w, la ? nwave : upd_n);
         }
         __syncthreads();
-    };
-    const int nch = ch1 - ch0;
-    Child C0 = {}, C1 = {};
-    ExtBatch B0, B1;
-    if (nch > 0) C0 = child_at(0);
-    if (nch > 1) C1 = child_at(1);
-    const bool pre0 = nch > 0 && C0.tot > 0, pre1 = nch > 1 && C1.tot > 0;
-    const int nk = F.nk;
-    const int* __restrict__ kl = F.kl;
-    const double* __restrict__ kv = F.kv;
-    constexpr int KU = 8;
-    double kvv[KU];
-    int klv[KU];
-#pragma unroll
-    for (int k = 0; k < KU; k++) {
-        const int q = min(tid + k * nt, nk - 1);
-        kvv[k] = kv[max(q, 0)];
-        klv[k] = kl[max(q, 0)];
-    }
-    if (pre0) ext_load(B0, C0, tid);
-    if (pre1) ext_load(B1, C1, tid);
-#pragma unroll
-    for (int k = 0; k < KU; k++) {
-        pin(kvv[k]);
-        pin(klv[k]);
-    }
-    if (pre0) ext_pin(B0);
-    if (pre1) ext_pin(B1);
-    for (int q = tid; q < ld * cp; q += nt) P[q] = 0.0;
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < KU; k++)
-        if (tid + k * nt < nk) P[(klv[k] >> 16) * ld + (klv[k] & 0xffff)] = kvv[k];
-    for (int q = tid + KU * nt; q < nk; q += nt) {
-        const int loc = kl[q];
-        P[(loc >> 16) * ld + (loc & 0xffff)] = kv[q];
-    }
-    __syncthreads();
-    if (nch > 0) ext_child(C0, B0, pre0);
-    if (nch > 1) ext_child(C1, B1, pre1);
-    for (int q = 2; q < nch; q++) {
-        const Child C = child_at(q);
-        ext_child(C, B0, false);
-    }
-
-    const int nbc = cp >> 4, nbr = rp >> 4;
-    // diagonal block kb by one wave (the pivot chain)
-    auto diag_block = [&](const int kb) {
-        const int j0 = kb << 4, w = min(16, c - j0);
-        // Diagonal block: each 16-lane row of the wave holds the block, lane
-        // i of a row holding row j0+i (entries right of the diagonal are
-        // never read back; rows past r are zero). Step j: the pivot comes
-        // from lane j, column j is scaled, and every lane takes column j's
-        // entries of the later rows by row broadcasts for its rank-one
-        // update.
-        const int i = lane & 15;
-        const bool live = j0 + i < r;
-        const int row = min(j0 + i, r - 1);
-        double a[16];
-#pragma unroll
-        for (int k = 0; k < 16; k++) a[k] = P[(j0 + k) * ld + row];
-        if (!live) {
-#pragma unroll
-            for (int k = 0; k < 16; k++) a[k] = 0.0;
-        }
-        static_for<16>([&](auto J) {
-            constexpr int j = J;
-            if (j < w) {
-                double d = readfirstlane_d(row_bcast<j>(a[j]));
-                if (!(d > 0.0) || !isfinite(d)) {
-                    if (lane == 0) {
-                        atomicMin(&status[1], col0 + j0 + j);
-                        atomicMax(&status[0], KKT_ST_NOT_SPD);
-                    }
-                    d = 1.0;
-                }
-                double inv, ljj;
-                pivot_roots(d, inv, ljj);
-                a[j] = i == j ? ljj : a[j] * inv;
-                if (lane == 0) invd[j] = inv;
-                // the next pivot's column first
-                static_for<16>([&](auto K) {
-                    constexpr int k = K;
-                    if constexpr (k > j) a[k] = fma(-a[j], row_bcast<k>(a[j]), a[k]);
-                });
-            }
-        });
-        if (lane < 16 && live) {
-#pragma unroll
-            for (int k = 0; k < 16; k++)
-                if (k < w && k <= i) P[(j0 + k) * ld + j0 + i] = a[k];
-        }
-    };
-    // rows below diagonal block kb, by all threads (after diag_block(kb))
-    auto trsm_block = [&](const int kb) {
-        const int j0 = kb << 4, w = min(16, c - j0);
-        if (tid < w) dinv[j0 + tid] = invd[tid];
-        // rows below the diagonal block: x = p L_kk^{-T}; column j of L_kk
-        // is fetched (contiguous, broadcast to all lanes) while step j-1
-        // computes
+        if (la) continue;
+        if (tid < w) F.dinv[j0 + tid] = invd[tid];
+        // rows below the diagonal block: x = p L_kk^{-T}; column j of L_kk is
+        // fetched (contiguous, broadcast to all lanes) while step j-1 computes
         for (int i = j0 + 16 + tid; i < r; i += nt) {
             double x[16], lc[16], ln[16];
 #pragma unroll
@@ -666,252 +607,557 @@ __device__ __forceinline__ void factor_front(const InstDev& I, const FrontDesc& 
             for (int k = 0; k < 16; k++)
                 if (k < w) P[(j0 + k) * ld + i] = x[k];
         }
-    };
-    // update by block kb of the column blocks [tj0, tj1) (matrix cores);
-    // tiles t0, t0 + ts, ... of that range
-    auto update_tiles = [&](const int kb, const int tj0, const int tj1, const int t0, const int ts) {
-        const int j0 = kb << 4;
-        int ntile = 0;
-        for (int jt = tj0; jt < tj1; jt++) ntile += nbr - jt;
-        for (int t = t0; t < ntile; t += ts) {
-            int ti, tj;
-            tri_tile(t, tj0, nbr, ti, tj);
-            const d4 acc = tile_abt(P, ld, ti << 4, tj << 4, j0, 16, r, lane);
-            const int col = (tj << 4) + (lane & 15);
-#pragma unroll
-            for (int e = 0; e < 4; e++) {
-                const int row = (ti << 4) + 4 * e + (lane >> 4);
-                if (col < c && row >= col && row < r) P[col * ld + row] -= acc[e];
-            }
-        }
-    };
-    // Column block kb of the panel in one pass by each panel wave (0-3): every
-    // 16-lane row of a wave holds the diagonal block (lane i: row j0+i) and
-    // runs the pivot chain on it, and each lane also carries one row below
-    // the block (wave w, lane l: row j0+16+64w+l). Step j scales column j
-    // and broadcasts its entries of the diagonal rows across the 16-lane
-    // rows; the same broadcast values serve the rank-one update of the
-    // diagonal rows and the substitution step of the rows below. Each entry
-    // sees the same operations in the same order as a pivot chain followed
-    // by a row-by-row triangular solve.
-    double dsave[16];  // wave 0: the last factored diagonal block (see flush_diag)
-    auto panel_block = [&](const int kb) {
-        const int j0 = kb << 4, w = min(16, c - j0);
-        const int i = lane & 15;
-        const bool live = j0 + i < r;
-        const int row = min(j0 + i, r - 1);
-        const int prow = j0 + 16 + (wave << 6) + lane;
-        const bool plive = prow < r;
-        const int prc = min(prow, r - 1);
-        double a[16], x[16];
-#pragma unroll
-        for (int k = 0; k < 16; k++) {
-            a[k] = P[(j0 + k) * ld + row];
-            x[k] = P[(j0 + k) * ld + prc];
-        }
-        if (!live) {
-#pragma unroll
-            for (int k = 0; k < 16; k++) a[k] = 0.0;
-        }
-        // Without branches inside the steps (a failing pivot is recorded and
-        // replaced by one, every step of a full block is unconditional), so
-        // the updates of step j can be scheduled alongside the pivot of step
-        // j+1.
-        double myinv = 0.0;
-        unsigned badv = 0;  // the same in every lane
-        auto steps = [&](auto full) {
-            static_for<16>([&](auto J) {
-                constexpr int j = J;
-                if (decltype(full)::value || j < w) {
-                    const double dp = row_bcast<j>(a[j]);
-                    const bool ok = dp > 0.0 && isfinite(dp);
-                    badv |= ok ? 0u : 1u << j;
-                    double inv, ljj;
-                    pivot_roots(ok ? dp : 1.0, inv, ljj);
-                    a[j] = i == j ? ljj : a[j] * inv;
-                    myinv = i == j ? inv : myinv;
-                    x[j] *= inv;
-                    double lk[16];
-                    static_for<16>([&](auto K) {
-                        constexpr int k = K;
-                        if constexpr (k > j) lk[k] = row_bcast<k>(a[j]);
-                    });
-                    static_for<16>([&](auto K) {
-                        constexpr int k = K;
-                        if constexpr (k > j) {
-                            a[k] = fma(-a[j], lk[k], a[k]);
-                            x[k] = fma(-x[j], lk[k], x[k]);
-                        }
-                    });
-                }
-            });
-        };
-        if (w == 16)
-            steps(std::true_type{});
-        else
-            steps(std::false_type{});
-        const unsigned bad = __builtin_amdgcn_readfirstlane(badv);
-        if (bad && tid == 0) {
-            atomicMin(&status[1], col0 + j0 + __builtin_ctz(bad));
-            atomicMax(&status[0], KKT_ST_NOT_SPD);
-        }
-        // The other panel waves load this diagonal block at their start, in
-        // the same phase: wave 0 keeps the factored block in registers and
-        // writes it back after the phase's barrier (flush_diag).
-        if (wave == 0) {
-#pragma unroll
-            for (int k = 0; k < 16; k++) dsave[k] = a[k];
-            if (lane < w) dinv[j0 + lane] = myinv;
-        }
-        if (plive) {
-#pragma unroll
-            for (int k = 0; k < 16; k++)
-                if (k < w) P[(j0 + k) * ld + prow] = x[k];
-        }
-    };
-    // Right-looking blocked Cholesky with one block of look-ahead: column
-    // block kb+1 takes block kb's update first; then the first waves (up to
-    // four) factor column block kb+1 while the others apply block kb's
-    // update to the columns beyond it. Every entry still receives the block updates in
-    // block order. Fronts taller than waves 0-3 can cover, and the
-    // persistent queue kernel, take the pivot chain by wave 0 and a
-    // separate triangular solve of the rows below (same arithmetic).
-    // panel waves: at most four, and at least one wave is left for the
-    // look-ahead update
-    const int maxp = min(4, nwave - 1);
-    if (fused_panel && r <= 16 + maxp * 64) {
-        // panel waves: one per 64 rows below the diagonal block (at least
-        // one), the rest take the look-ahead update
-        auto npanel = [&](const int kb) { return min(maxp, max(1, (r - (kb << 4) - 16 + 63) >> 6)); };
-        // wave 0, after the barrier that ends panel_block(kb): the factored
-        // diagonal block kb into the panel. Nothing reads or writes that block
-        // until the panel is copied out (the updates touch the rows below it
-        // and later column blocks).
-        auto flush_diag = [&](const int kb) {
-            const int j0 = kb << 4, w = min(16, c - j0);
-            const int i = lane & 15;
-            if (lane < 16 && j0 + i < r) {
-#pragma unroll
-                for (int k = 0; k < 16; k++)
-                    if (k < w && k <= i) P[(j0 + k) * ld + j0 + i] = dsave[k];
-            }
-        };
-        if (wave < npanel(0)) panel_block(0);
         __syncthreads();
-        for (int kb = 0; kb + 1 < nbc; kb++) {
-            if (wave == 0) flush_diag(kb);
-            update_tiles(kb, kb + 1, kb + 2, wave, nwave);
-            __syncthreads();
-            const int np = npanel(kb + 1);
-            if (wave < np) panel_block(kb + 1);
-            else update_tiles(kb, kb + 2, nbc, wave - np, nwave - np);
-            __syncthreads();
-        }
-        if (wave == 0) flush_diag(nbc - 1);
-        __syncthreads();
-    } else {
-        // with eight waves, the wave that shares wave 0's SIMD (wave 4) stays
-        // out of the look-ahead update, so the pivot chain has its SIMD to
-        // itself; with four waves, waves 1-3 take it
-        const bool eight = nwave == 8;
-        const int upd_w = wave - 1 - (eight && wave > 4 ? 1 : 0), upd_n = eight ? nwave - 2 : nwave - 1;
-        if (wave == 0) diag_block(0);
-        __syncthreads();
-        trsm_block(0);
-        __syncthreads();
-        for (int kb = 0; kb + 1 < nbc; kb++) {
-            update_tiles(kb, kb + 1, kb + 2, wave, nwave);
-            __syncthreads();
-            if (wave == 0) diag_block(kb + 1);
-            else if (!eight || wave != 4) update_tiles(kb, kb + 2, nbc, upd_w, upd_n);
-            __syncthreads();
-            trsm_block(kb + 1);
-            __syncthreads();
-        }
+        if (kb + 1 == nbc) break;
     }
-
     // panel -> HBM: same layout, contiguous 16-byte stores
     copy_vec(F.L, P, even_up(ld * c), tid, nt);
-    if (u == 0 || !fused_update) return;
-    // Update matrix U = -L21 L21^T (lower part) on the matrix cores, with
-    // the children's entries that pass through to it: each lane's places
-    // (a, b) of a tile find a child's entry through the child's inverse row
-    // map (this front's update row -> the child's, or -1), and the entries are
-    // added child by child in child order, the same additions in the same
-    // order as the strip kernel's read-modify-write, with one store per
-    // place. The first two children's values are read before the tile's
-    // matrix-core steps (indices clamped into range, so no load is
-    // predicated); further children are gathered after them.
-    double* __restrict__ Us = F.U;
-    const int nbu = (u + 15) >> 4;
-    const int ntu = nbu * (nbu + 1) / 2;
-    const int K4 = (c + 3) & ~3;
-    struct PassChild {
-        const double* Uc;
-        const int* inv;
-        int uc;
+    for (int t = wave; t < nuu; t += nwave) {
+        int ti, tj;
+        u_unit(t, ti, tj);
+        d4 s0 = {0.0, 0.0, 0.0, 0.0}, s1 = s0;
+        TFrag G;
+        for (int k0 = 0; k0 < cp; k0 += 16) {
+            frag(G, k0, c + (tj << 4), c + (ti << 4));
+            mult(G, s0, s1);
+        }
+        u_store(ti, tj, s0, s1);
+    }
+}
+
+// EK, EC: the first extend-add batch of a child holds EC columns per wave in
+// each of EK chunks of 64 rows; US: units of the update matrix one wave
+// accumulates in registers beside the panel (register budget of the caller)
+template <int EK, int EC, int US>
+__device__ __forceinline__ void factor_front(const InstDev& I, const FrontDesc& F, double* __restrict__ P,
+                                             double* invd, const bool fused_update) {
+    const int c = F.c, r = F.r;
+    const int u = r - c, nch = F.nch;
+    const int cp = rup16(c);
+    const int ld = r | 1;  // of the stored panel
+    double* __restrict__ const Lst = F.L;
+    double* __restrict__ const dinv = F.dinv;
+    const int tid = threadIdx.x, nt = blockDim.x;
+    // the wave index as a scalar: everything derived from it is uniform
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nwave = nt >> 6;
+    const int lr = lane & 15, lk = lane >> 4;
+    const int nbc = cp >> 4, nbu = (u + 15) >> 4, nbr = nbc + nbu, rt = nbr << 4;
+    // At most four waves factor a panel block (one per 64 rows below its
+    // diagonal block), and at least one is left for the updates. Taller
+    // fronts, and the few whose blocked panel does not fit, use a plain
+    // column-major panel (leading dimension ld).
+    const int maxp = min(4, nwave - 1);
+    const bool blocked = front_blocked(r, c, maxp);
+    const int shift = blocked ? cp - c : 0;  // panel row of an update row: row + shift
+    // place of (row, column) of the front in the LDS panel
+    auto place = [&](const int row, const int col) {
+        const int prow = row < c ? row : row + shift;
+        return blocked ? block_base(col >> 4, rt) + prow * kRow + in_row(prow, col & 15) : col * ld + row;
     };
-    auto pass_child = [&](const int k) {
-        PassChild C;
+
+    // Assembly of the front: the original entries of K, then the children's
+    // update matrices (entries (a, b), a >= b, whose column b maps into the
+    // panel), child by child in a fixed order (two children can add into the
+    // same entry). One wave takes columns wave, wave + nwave, ... of a child,
+    // its lanes the rows in chunks of 64: the relative rows of a chunk are
+    // loaded once and serve all of its columns (a column's own relative index
+    // is a lane of the same registers), so an entry costs one load. The
+    // panel is cleared and K's entries are placed while the first child's
+    // loads are in flight, and a child's loads are issued before the previous
+    // child is added; one copy of the code serves every child.
+    struct Child {
+        const double* Uc;
+        const int* rl;
+        int uc, nb;
+    };
+    // child k (0-based): the first two from the front descriptor
+    auto child_at = [&](const int k) {
+        Child C;
         if (k < 2) {
-            C.Uc = k ? F.cU[1] : F.cU[0];
-            C.inv = k ? F.cinv[1] : F.cinv[0];
             C.uc = k ? F.cuc[1] : F.cuc[0];
+            C.nb = k ? F.cnb[1] : F.cnb[0];
+            C.Uc = k ? F.cU[1] : F.cU[0];
+            C.rl = k ? F.crl[1] : F.crl[0];
         } else {
-            const int ch = __builtin_amdgcn_readfirstlane(chl[ch0 + k]);
-            C.Uc = Ubase + sn_uofs[ch];
-            C.inv = T.pinv + T.pinv_ofs[ch0 + k];
-            C.uc = __builtin_amdgcn_readfirstlane(sn_nrow[ch]) - __builtin_amdgcn_readfirstlane(sn_ncol[ch]);
+            const PatDev& T = I.P;
+            const int ch = __builtin_amdgcn_readfirstlane(T.ch_list[F.ch0 + k]);
+            const int cc = __builtin_amdgcn_readfirstlane(T.sn_ncol[ch]);
+            C.uc = __builtin_amdgcn_readfirstlane(T.sn_nrow[ch]) - cc;
+            C.nb = __builtin_amdgcn_readfirstlane(T.rel_np[ch]);
+            C.Uc = I.U + T.sn_uofs[ch];
+            C.rl = T.rel + T.sn_rowofs[ch] + cc;
         }
         return C;
     };
-    // this lane's four values of child C at rows a0 + 4e, column b (lower
-    // places of this front's update matrix only)
-    auto pass_gather = [&](const PassChild& C, const int a0, const int b, double* v, bool* in) {
-        const int ib = C.inv[min(b, u - 1)];
-        int ia[4];
+    struct ExtBatch {
+        int ra[EK];        // relative rows of the first EK chunks
+        double v[EK][EC];  // the wave's first EC columns there
+    };
+    // chunk q holds entries of column b: some row at or below the diagonal
+    auto ext_has = [&](const Child& C, const int q, const int b) {
+        return (q << 6) < C.uc && b < C.nb && b < (q << 6) + 64;
+    };
+    auto ext_load = [&](ExtBatch& B, const Child& C) {
+        const double* Ub = C.Uc + (int64_t)wave * C.uc;
+        const int64_t step = (int64_t)nwave * C.uc;
 #pragma unroll
-        for (int e = 0; e < 4; e++) ia[e] = C.inv[min(a0 + 4 * e, u - 1)];
+        for (int q = 0; q < EK; q++) B.ra[q] = C.rl[min((q << 6) + lane, C.uc - 1)];
 #pragma unroll
-        for (int e = 0; e < 4; e++) {
-            const int a = a0 + 4 * e;
-            in[e] = a < u && b <= a && ia[e] >= 0 && ib >= 0;
-            v[e] = C.Uc[(int64_t)max(ib, 0) * C.uc + max(ia[e], 0)];
+        for (int j = 0; j < EC; j++, Ub += step) {
+#pragma unroll
+            for (int q = 0; q < EK; q++)
+                if (ext_has(C, q, wave + j * nwave)) B.v[q][j] = Ub[min((q << 6) + lane, C.uc - 1)];
         }
     };
-    PassChild P0 = {}, P1 = {};
-    if (nch > 0) P0 = pass_child(0);
-    if (nch > 1) P1 = pass_child(1);
-    for (int t = wave; t < ntu; t += nwave) {
-        int ti, tj;
-        tri_tile(t, 0, nbu, ti, tj);
-        const int b = (tj << 4) + (lane & 15);
-        const int a0 = (ti << 4) + (lane >> 4);
-        double v0[4] = {0.0, 0.0, 0.0, 0.0}, v1[4] = {0.0, 0.0, 0.0, 0.0};
-        bool in0[4] = {false, false, false, false}, in1[4] = {false, false, false, false};
-        if (nch > 0) pass_gather(P0, a0, b, v0, in0);
-        if (nch > 1) pass_gather(P1, a0, b, v1, in1);
-        const d4 acc = tile_abt(P, ld, c + (ti << 4), c + (tj << 4), 0, K4, r, lane);
-        double w[4];
+    // place of (relative row, relative column): a lane's row part and a
+    // column part (bits 0-3 of both are combined by exclusive or)
+    auto row_at = [&](const int ra) {
+        const int prow = ra < c ? ra : ra + shift;
+        return blocked ? prow * kRow | (prow & 7) << 1 : ra;
+    };
+    auto col_at = [&](const int rb) { return blocked ? block_base(rb >> 4, rt) | slot(rb & 15) : rb * ld; };
+    auto place_at = [&](const int pa, const int pb) {
+        return blocked ? (pa & ~15) + (pb & ~15) + ((pa ^ pb) & 15) : pa + pb;
+    };
+    // one entry per lane of column b, chunk q (the destinations of one child
+    // are distinct, so the adds need no order among themselves)
+    auto ext_one = [&](const Child& C, const int q, const int b, const int pa, const int pb, const double v) {
+        const int a = (q << 6) + lane;
+        if (a >= b && a < C.uc) lds_add(&P[place_at(pa, pb)], v);
+    };
+    auto ext_add = [&](const Child& C, const ExtBatch& B) {
+        int pa[EK];
+#pragma unroll
+        for (int q = 0; q < EK; q++) pa[q] = row_at(B.ra[q]);
+#pragma unroll
+        for (int j = 0; j < EC; j++) {
+            const int b = wave + j * nwave;
+            // (columns of a child number at most 128)
+            const int pb = col_at(__builtin_amdgcn_readlane(b < 64 ? B.ra[0] : B.ra[1], b & 63));
+#pragma unroll
+            for (int q = 0; q < EK; q++)
+                if (ext_has(C, q, b)) ext_one(C, q, b, pa[q], pb, B.v[q][j]);
+        }
+        // the rest: columns past the batch, and chunks past it
+        for (int q = 0; (q << 6) < C.uc; q++) {
+            const int b0 = q < EK ? wave + EC * nwave : wave;
+            if (!ext_has(C, q, b0)) continue;
+            const int ac = min((q << 6) + lane, C.uc - 1);
+            const int pq = row_at(C.rl[ac]);
+            for (int b = b0; ext_has(C, q, b); b += 4 * nwave) {
+                double v[4];
+                int rb[4];
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    const int bj = min(b + j * nwave, C.nb - 1);
+                    v[j] = C.Uc[(int64_t)bj * C.uc + ac];
+                    rb[j] = C.rl[bj];
+                }
+#pragma unroll
+                for (int j = 0; j < 4; j++)
+                    if (ext_has(C, q, b + j * nwave)) ext_one(C, q, b + j * nwave, pq, col_at(rb[j]), v[j]);
+            }
+        }
+    };
+    // tall fronts: the waves take the chunks of a child instead (there are more
+    // chunks than a batch holds), sixteen columns in flight
+    auto ext_tall = [&](const Child& C) {
+        for (int q = wave; (q << 6) < C.uc; q += nwave) {
+            const int ac = min((q << 6) + lane, C.uc - 1);
+            const int pq = row_at(C.rl[ac]);
+            for (int b = 0; ext_has(C, q, b); b += 16) {
+                double v[16];
+                int rb[16];
+#pragma unroll
+                for (int j = 0; j < 16; j++) {
+                    const int bj = min(b + j, C.nb - 1);
+                    v[j] = C.Uc[(int64_t)bj * C.uc + ac];
+                    rb[j] = C.rl[bj];
+                }
+#pragma unroll
+                for (int j = 0; j < 16; j++)
+                    if (ext_has(C, q, b + j)) ext_one(C, q, b + j, pq, col_at(rb[j]), v[j]);
+            }
+        }
+    };
+    {
+        const int nk = F.nk;
+        const int* __restrict__ kl = F.kl;
+        const double* __restrict__ kv = F.kv;
+        constexpr int KU = 8;
+        double kvv[KU];
+        int klv[KU];
+#pragma unroll
+        for (int k = 0; k < KU; k++) {
+            const int q = max(min(tid + k * nt, nk - 1), 0);
+            kvv[k] = kv[q];
+            klv[k] = kl[q];
+        }
+        Child Cn = {}, Cc = {};
+        ExtBatch Bn, Bc;
+        for (int k = -1; k < nch; k++) {
+            const bool next = k + 1 < nch;
+            if (next) {
+                Cn = child_at(k + 1);
+                if (blocked && Cn.nb > 0) ext_load(Bn, Cn);
+            }
+            if (k < 0) {
+                double2* const P2 = (double2*)P;
+                const double2 z = {0.0, 0.0};
+                const int n2 = (blocked ? block_base(nbc, rt) + nbc * 16 * kRow : ld * cp) >> 1;
+                for (int q = tid; q < n2; q += nt) P2[q] = z;
+                __syncthreads();
+#pragma unroll
+                for (int q = 0; q < KU; q++)
+                    if (tid + q * nt < nk) P[place(klv[q] & 0xffff, klv[q] >> 16)] = kvv[q];
+                for (int q = tid + KU * nt; q < nk; q += nt) {
+                    const int loc = kl[q];
+                    P[place(loc & 0xffff, loc >> 16)] = kv[q];
+                }
+            } else if (Cc.nb > 0) {
+                if (blocked) ext_add(Cc, Bc);
+                else ext_tall(Cc);
+            }
+            __syncthreads();
+            Cc = Cn;
+            Bc = Bn;
+        }
+    }
+
+    // Update matrix U = -L21 L21^T (lower part) on the matrix cores, in units
+    // of two tiles above each other; unit t is tiles (ti, tj), (ti + 1, tj) of
+    // U's tile grid, column by column. Accumulators start at zero and take
+    // the panel's columns in order; the children's entries that pass through
+    // to U are added at the end, child by child in child order, before the
+    // one store: each lane's places find a child's entry through the child's
+    // inverse row map (this front's update row -> the child's, or -1).
+    // Element e of a tile's result in lane l is row l % 16, column 4e + l /
+    // 16: a column's rows are consecutive lanes.
+    const int nuu = fused_update ? ((nbu + 1) >> 1) * ((nbu >> 1) + 1) : 0;  // sum over tj of ceil((nbu - tj) / 2)
+    auto u_unit = [&](int t, int& ti, int& tj) {
+        tj = 0;
+        while (t >= (nbu - tj + 1) >> 1) {
+            t -= (nbu - tj + 1) >> 1;
+            tj++;
+        }
+        ti = tj + 2 * t;
+    };
+    auto u_store = [&](const int ti, const int tj, const d4& s0, const d4& s1) {
+        const int a0 = (ti << 4) + lr, a1 = a0 + 16, b0 = (tj << 4) + lk;
+        double w0[4], w1[4];
 #pragma unroll
         for (int e = 0; e < 4; e++) {
-            w[e] = -acc[e];
-            if (in0[e]) w[e] += v0[e];
-            if (in1[e]) w[e] += v1[e];
+            w0[e] = -s0[e];
+            w1[e] = -s1[e];
         }
-        for (int k = 2; k < nch; k++) {
-            double vk[4];
-            bool ink[4];
-            pass_gather(pass_child(k), a0, b, vk, ink);
+        for (int k = 0; k < nch; k++) {
+            const double* Uc;
+            const int* inv;
+            int uc;
+            if (k < 2) {
+                Uc = k ? F.cU[1] : F.cU[0];
+                inv = k ? F.cinv[1] : F.cinv[0];
+                uc = k ? F.cuc[1] : F.cuc[0];
+            } else {
+                const PatDev& T = I.P;
+                const int ch = __builtin_amdgcn_readfirstlane(T.ch_list[F.ch0 + k]);
+                Uc = I.U + T.sn_uofs[ch];
+                inv = T.pinv + T.pinv_ofs[F.ch0 + k];
+                uc = __builtin_amdgcn_readfirstlane(T.sn_nrow[ch]) - __builtin_amdgcn_readfirstlane(T.sn_ncol[ch]);
+            }
+            const int i0 = inv[min(a0, u - 1)], i1 = inv[min(a1, u - 1)];
+            int ib[4];
+            double v0[4], v1[4];
 #pragma unroll
-            for (int e = 0; e < 4; e++)
-                if (ink[e]) w[e] += vk[e];
+            for (int e = 0; e < 4; e++) ib[e] = inv[min(b0 + 4 * e, u - 1)];
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                const int64_t col = (int64_t)max(ib[e], 0) * uc;
+                v0[e] = Uc[col + max(i0, 0)];
+                v1[e] = Uc[col + max(i1, 0)];
+            }
+            // (places outside U's lower part are not stored, so whatever
+            // they take does not matter)
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                if (i0 >= 0 && ib[e] >= 0) w0[e] += v0[e];
+                if (i1 >= 0 && ib[e] >= 0) w1[e] += v1[e];
+            }
         }
+        double* __restrict__ Us = F.U;
 #pragma unroll
         for (int e = 0; e < 4; e++) {
-            const int a = a0 + 4 * e;
-            if (a < u && b <= a) Us[(int64_t)b * u + a] = w[e];
+            const int b = b0 + 4 * e;
+            if (b <= a0 && a0 < u) Us[(int64_t)b * u + a0] = w0[e];
+            if (b <= a1 && a1 < u) Us[(int64_t)b * u + a1] = w1[e];
         }
+    };
+
+    // Right-looking blocked Cholesky with one block of look-ahead: column
+    // block kb+1 takes block kb's update first; then the panel waves factor
+    // column block kb+1 while the others apply block kb's update to the
+    // columns beyond it and to the update matrix. Every entry receives the
+    // block updates in block order.
+    if (blocked) {
+        // what a lane adds to its row's address: rows here are lr, or lk + 4e,
+        // modulo 16, and each panel row is lr modulo 16 as well
+        const int rx = (lr & 7) << 1, fo = in_row(lr, lk);
+        const int dof[2] = {in_row(lk, lr), in_row(lk + 4, lr)};
+        auto npanel = [&](const int kb) { return min(maxp, max(1, (rt - (kb << 4) - 16 + 63) >> 6)); };
+        // units of U below nreg live in registers of the waves that never
+        // factor a panel block: unit s * ntw + (wave - np0) is slot s of a wave
+        const int np0 = npanel(0), ntw = nwave - np0;
+        const int nreg = min(nuu, US * ntw);
+        const int ns = wave >= np0 ? (nreg - (wave - np0) + ntw - 1) / ntw : 0;  // this wave's slots
+        d4 s0[US], s1[US];
+        int uij[US];                  // (ti << 16) | tj
+        int pa[US], pb[US];           // the operands' places in a column block
+#pragma unroll
+        for (int s = 0; s < US; s++) {
+            s0[s] = s1[s] = d4{0.0, 0.0, 0.0, 0.0};
+            uij[s] = pa[s] = pb[s] = 0;
+        }
+        if (ns > 0) {
+#pragma unroll
+            for (int s = 0; s < US; s++) {
+                int ti = 0, tj = 0;
+                if (s < ns) u_unit(s * ntw + wave - np0, ti, tj);
+                uij[s] = (ti << 16) | tj;
+                pa[s] = (cp + (ti << 4) + lr) * kRow;
+                pb[s] = (cp + (tj << 4) + lr) * kRow;
+            }
+        }
+        // Block kb's update of tiles (ti, tj), (ti + 1, tj) of the panel: the
+        // result's element e in lane l is row 4e + l / 16, column l % 16. The
+        // strict upper part of a diagonal tile takes values nothing reads.
+        struct Unit {
+            Frag b, a0, a1;
+            double p0[4], p1[4];
+            double* D;
+            int o1;
+        };
+        auto unit_load = [&](Unit& X, const int kb, const int ti, const int tj) {
+            const double* const Lk = P + block_base(kb, rt) + lr * kRow;
+            X.o1 = ti + 1 < nbr ? 16 * kRow : 0;
+            X.b = frag_load(Lk + (tj << 4) * kRow, fo);
+            X.a0 = frag_load(Lk + (ti << 4) * kRow, fo);
+            X.a1 = frag_load(Lk + (ti << 4) * kRow + X.o1, fo);
+            X.D = P + block_base(tj, rt) + ((ti << 4) + lk) * kRow;
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                X.p0[e] = X.D[4 * e * kRow + dof[e & 1]];
+                X.p1[e] = X.D[4 * e * kRow + dof[e & 1] + X.o1];
+            }
+        };
+        auto unit_store = [&](const Unit& X, const d4& t0, const d4& t1) {
+            if (X.o1) {
+#pragma unroll
+                for (int e = 0; e < 4; e++) X.D[(4 * e + 16) * kRow + dof[e & 1]] = X.p1[e] - t1[e];
+            }
+#pragma unroll
+            for (int e = 0; e < 4; e++) X.D[4 * e * kRow + dof[e & 1]] = X.p0[e] - t0[e];
+        };
+        for (int ph = 0;; ph++) {
+            // even phases 2 kb: panel block kb beside the rest of block
+            // kb-1's update; odd phases: block kb's update of column block kb+1
+            const bool la = ph & 1;
+            const int kb = ph >> 1, np = la || kb == nbc ? 0 : npanel(kb);
+            if (wave < np) {
+                // Column block kb of the panel in one pass: every 16-lane row
+                // of a panel wave holds the diagonal block (lane i: row j0+i)
+                // and runs the pivot chain on it, and each lane also carries
+                // one row below the block (wave w, lane l: row
+                // j0+16+64w+l). Step j scales column j and broadcasts its
+                // entries of the diagonal rows across the 16-lane rows; the
+                // same broadcast values serve the rank-one update of the
+                // diagonal rows and the substitution step of the rows below.
+                // Each entry sees the same operations in the same order as a
+                // pivot chain followed by a row-by-row triangular solve.
+                const int j0 = kb << 4, w = min(16, c - j0);
+                const int prow = j0 + 16 + (wave << 6) + lane;
+                double* const Pa = P + block_base(kb, rt) + (j0 + lr) * kRow;
+                double* const Px = P + block_base(kb, rt) + (min(prow, rt - 16 + lr)) * kRow;
+                double a[16], x[16];
+#pragma unroll
+                for (int k = 0; k < 16; k += 2) {
+                    const double2 va = *(const double2*)(Pa + (k ^ rx)), vx = *(const double2*)(Px + (k ^ rx));
+                    a[slot(k)] = va.x;
+                    a[slot(k + 1)] = va.y;
+                    x[slot(k)] = vx.x;
+                    x[slot(k + 1)] = vx.y;
+                }
+                double myinv = 0.0;
+                unsigned badv = 0;  // the same in every lane
+                // No branches inside a group of four steps (a failing pivot
+                // is recorded and replaced by one), so the updates of step j
+                // can be scheduled alongside the pivot of step j+1; steps
+                // past the last column meet zero rows and columns.
+                static_for<4>([&](auto G) {
+                    constexpr int g = G;
+                    if (4 * g < w) {
+                        static_for<4>([&](auto Q) {
+                            constexpr int j = 4 * g + decltype(Q)::value;
+                            const double dp = row_bcast<j>(a[j]);
+                            const bool ok = dp > 0.0 && isfinite(dp);
+                            badv |= ok ? 0u : 1u << j;
+                            double inv, ljj;
+                            pivot_roots(ok ? dp : 1.0, inv, ljj);
+                            a[j] = lr == j ? ljj : a[j] * inv;
+                            myinv = lr == j ? inv : myinv;
+                            x[j] *= inv;
+                            double lj[16];
+                            static_for<16>([&](auto K) {
+                                constexpr int k = K;
+                                if constexpr (k > j) lj[k] = row_bcast<k>(a[j]);
+                            });
+                            static_for<16>([&](auto K) {
+                                constexpr int k = K;
+                                if constexpr (k > j) {
+                                    a[k] = fma(-a[j], lj[k], a[k]);
+                                    x[k] = fma(-x[j], lj[k], x[k]);
+                                }
+                            });
+                        });
+                    }
+                });
+                // The rows below go to LDS for the updates and to HBM; the
+                // factored diagonal block to HBM only (nothing reads it here
+                // again, and the other panel waves load it in this phase).
+                if (prow < rt) {
+#pragma unroll
+                    for (int k = 0; k < 16; k += 2) {
+                        double2 vx;
+                        vx.x = x[slot(k)];
+                        vx.y = x[slot(k + 1)];
+                        *(double2*)(Px + (k ^ rx)) = vx;
+                    }
+                }
+                double* __restrict__ const Lp = Lst + (int64_t)j0 * ld;
+                const int row = prow < c ? prow : prow - shift;
+                if ((prow < c || prow >= cp) && row < r) {
+                    unsigned o = row;  // 32-bit offsets from a scalar base
+                    if (w == 16) {
+#pragma unroll
+                        for (int k = 0; k < 16; k++, o += ld) Lp[o] = x[k];
+                    } else {
+#pragma unroll
+                        for (int k = 0; k < 15; k++, o += ld)
+                            if (k < w) Lp[o] = x[k];
+                    }
+                }
+                // the diagonal block's columns, dealt to the panel waves (the
+                // places above the diagonal take whatever the lane holds
+                // there; nothing reads them)
+                if (lane < w) {
+                    const unsigned mine = ((np == 1 ? 0xffffu : np == 2 ? 0x5555u : np == 3 ? 0x9249u : 0x1111u) << wave) &
+                                          ((1u << w) - 1);
+                    unsigned o = j0 + lane;
+#pragma unroll
+                    for (int k = 0; k < 16; k++, o += ld)
+                        if ((mine >> k) & 1u) Lp[o] = a[k];
+                    if (wave == 0) dinv[j0 + lane] = myinv;
+                }
+                if (wave == 0) {
+                    const unsigned bad = __builtin_amdgcn_readfirstlane(badv) & ((1u << w) - 1);
+                    if (bad && lane == 0) {
+                        int* const status = I.status;
+                        atomicMin(&status[1], F.col0 + j0 + __builtin_ctz(bad));
+                        atomicMax(&status[0], KKT_ST_NOT_SPD);
+                    }
+                }
+            } else if (la || kb > 0) {
+                // units t, t + ts, ... of the columns [kb + 1, tj1), two at a
+                // time: a chain of four dependent f64 matrix instructions
+                // takes about 500 cycles whatever else the SIMD does
+                const int ku = la ? kb : kb - 1, tj1 = la ? kb + 2 : nbc, ts = nwave - np;
+                int tj = kb + 1, t = wave - np;
+                while (tj < tj1) {
+                    const int nu = (nbr - tj + 1) >> 1;
+                    if (t >= nu) {
+                        t -= nu;
+                        tj++;
+                        continue;
+                    }
+                    Unit X, Y;
+                    d4 x0 = {0.0, 0.0, 0.0, 0.0}, x1 = x0;
+                    unit_load(X, ku, tj + 2 * t, tj);
+                    t += ts;
+                    if (t < nu) {
+                        d4 y0 = {0.0, 0.0, 0.0, 0.0}, y1 = y0;
+                        unit_load(Y, ku, tj + 2 * t, tj);
+                        t += ts;
+#pragma unroll
+                        for (int q = 0; q < 4; q++) {
+                            x0 = mfma_f64_16x16x4(X.a0[q], X.b[q], x0);
+                            x1 = mfma_f64_16x16x4(X.a1[q], X.b[q], x1);
+                            y0 = mfma_f64_16x16x4(Y.a0[q], X.b[q], y0);
+                            y1 = mfma_f64_16x16x4(Y.a1[q], X.b[q], y1);
+                        }
+                        unit_store(X, x0, x1);
+                        unit_store(Y, y0, y1);
+                    } else {
+#pragma unroll
+                        for (int q = 0; q < 4; q++) {
+                            x0 = mfma_f64_16x16x4(X.a0[q], X.b[q], x0);
+                            x1 = mfma_f64_16x16x4(X.a1[q], X.b[q], x1);
+                        }
+                        unit_store(X, x0, x1);
+                    }
+                }
+            }
+            if (!la && kb > 0 && ns > 0) {
+                // this wave's slots of U, two at a time
+                const double* const Lk = P + block_base(kb - 1, rt);
+#pragma unroll
+                for (int s = 0; s < US; s += 2) {
+                    if (s < ns) {
+                        constexpr int last = US - 1;
+                        const int s2 = s < last ? s + 1 : s;
+                        const int xo = (uij[s] >> 16) + 1 < nbu ? 16 * kRow : 0, yo = (uij[s2] >> 16) + 1 < nbu ? 16 * kRow : 0;
+                        const Frag xb = frag_load(Lk + pb[s], fo), xa0 = frag_load(Lk + pa[s], fo),
+                                   xa1 = frag_load(Lk + pa[s] + xo, fo);
+                        const Frag yb = frag_load(Lk + pb[s2], fo), ya0 = frag_load(Lk + pa[s2], fo),
+                                   ya1 = frag_load(Lk + pa[s2] + yo, fo);
+#pragma unroll
+                        for (int q = 0; q < 4; q++) {
+                            s0[s] = mfma_f64_16x16x4(xb[q], xa0[q], s0[s]);
+                            s1[s] = mfma_f64_16x16x4(xb[q], xa1[q], s1[s]);
+                            if (s < last) {
+                                s0[s2] = mfma_f64_16x16x4(yb[q], ya0[q], s0[s2]);
+                                s1[s2] = mfma_f64_16x16x4(yb[q], ya1[q], s1[s2]);
+                            }
+                        }
+                    }
+                }
+            }
+            if (!la && kb == nbc) break;
+            __syncthreads();
+            if (ph == 2 * nbc - 2) ph++;  // no column block follows the last
+        }
+#pragma unroll
+        for (int s = 0; s < US; s++)
+            if (s < ns) u_store(uij[s] >> 16, uij[s] & 0xffff, s0[s], s1[s]);
+        // the units of U that no wave held in registers
+        for (int t = nreg + wave; t < nuu; t += nwave) {
+            int ti, tj;
+            u_unit(t, ti, tj);
+            d4 t0 = {0.0, 0.0, 0.0, 0.0}, t1 = t0;
+            const int qa0 = (cp + (ti << 4) + lr) * kRow;
+            const int qa1 = ti + 1 < nbu ? qa0 + 16 * kRow : qa0;
+            const int qb = (cp + (tj << 4) + lr) * kRow;
+            for (int kb = 0; kb < nbc; kb++) {
+                const double* const Lk = P + block_base(kb, rt);
+                const Frag xb = frag_load(Lk + qb, fo), xa0 = frag_load(Lk + qa0, fo), xa1 = frag_load(Lk + qa1, fo);
+#pragma unroll
+                for (int q = 0; q < 4; q++) {
+                    t0 = mfma_f64_16x16x4(xb[q], xa0[q], t0);
+                    t1 = mfma_f64_16x16x4(xb[q], xa1[q], t1);
+                }
+            }
+            u_store(ti, tj, t0, t1);
+        }
+    } else {
+        factor_tall(I, F, P, invd, nuu, u_unit, u_store);
     }
     // every wave is done with the panel in LDS and with its stores before
     // the caller reuses the LDS or publishes the front
@@ -923,7 +1169,7 @@ __global__ __launch_bounds__(kFactorThreads) void k_factor(const InstDev* __rest
     extern __shared__ __align__(16) double P[];
     __shared__ double invd[16];
     const FrontDesc& F = fds[blockIdx.x];
-    factor_front<18>(insts[F.inst], F, P, invd, fused_update != 0, true);
+    factor_front<2, 6, 1>(insts[F.inst], F, P, invd, fused_update != 0);
 }
 
 // the same front factorization by four waves (every entry takes the same
@@ -933,21 +1179,20 @@ void k_factor_small(const InstDev* __restrict__ insts, const FrontDesc* __restri
     extern __shared__ __align__(16) double P[];
     __shared__ double invd[16];
     const FrontDesc& F = fds[blockIdx.x];
-    factor_front<KKT_SMALL_EU>(insts[F.inst], F, P, invd, fused_update != 0, true);
+    factor_front<2, 8, 2>(insts[F.inst], F, P, invd, fused_update != 0);
 }
 
 // ---------------------------------------------------------------------------
 // update matrix of a front by 16-column strips (level schedule)
 // ---------------------------------------------------------------------------
 // 16x16 tile of L21 L21^T read from a stored panel (column-major, leading
-// dimension ld, kmax columns): the same k steps as tile_abt over the
-// zero-padded LDS panel, with columns >= kmax contributing zeros.
+// dimension ld, kmax columns): the same steps as over the zero-padded LDS
+// panel, with columns >= kmax contributing zeros. Rows past rlim are read
+// clamped (their results are not stored).
 __device__ inline d4 tile_abt_g(const double* __restrict__ Lp, int ld, int i0, int j0, int kmax, int rlim,
                                 int lane) {
     const int lr = lane & 15, lk = lane >> 4;
-    const int ia = i0 + lr, jb = j0 + lr;
-    const bool va = ia < rlim, vb = jb < rlim;
-    const int iac = min(ia, rlim - 1), jbc = min(jb, rlim - 1);
+    const int iac = min(i0 + lr, rlim - 1), jbc = min(j0 + lr, rlim - 1);
     // every column's loads are issued before the first step (kmax <= 128:
     // at most 32 steps of 4); indices past the last step repeat it, so no
     // load is predicated, and only the steps below nq run
@@ -964,7 +1209,7 @@ __device__ inline d4 tile_abt_g(const double* __restrict__ Lp, int ld, int i0, i
     for (int q = 0; q < 32; q++) {
         if (q < nq) {
             const bool vk = 4 * q + lk < kmax;
-            acc = mfma_f64_16x16x4(va && vk ? a[q] : 0.0, vb && vk ? b[q] : 0.0, acc);
+            acc = mfma_f64_16x16x4(vk ? a[q] : 0.0, vk ? b[q] : 0.0, acc);
         }
     }
     return acc;
@@ -1239,7 +1484,7 @@ __global__ __launch_bounds__(kBigThreads) void k_big_tiles(const InstDev* __rest
     if (t >= ntile) return;
     int ti, tj;
     tri_tile(t, kb + 1, nbr, ti, tj);
-    const d4 acc = tile_abt(P, ld, ti << 4, tj << 4, j0, 16, r, lane);
+    const d4 acc = tile_abt(P, ld, ti << 4, tj << 4, j0, r, lane);
     const int col = (tj << 4) + (lane & 15);
 #pragma unroll
     for (int e = 0; e < 4; e++) {
@@ -1303,11 +1548,7 @@ __device__ inline int take_ticket(int* ticket, int* slot) {
     return t;
 }
 
-// the persistent loop keeps its scheduling state live across the front, so
-// its extend-add batches are smaller (no register spills)
-constexpr int kQueueExtBatch = 12;
-
-__global__ __launch_bounds__(kFactorThreads) void k_factor_queue(const InstDev* __restrict__ insts,
+__global__ __launch_bounds__(kFactorQueueThreads) void k_factor_queue(const InstDev* __restrict__ insts,
                                                                 const FrontDesc* __restrict__ fds, DepLists D) {
     extern __shared__ __align__(16) double P[];
     __shared__ double invd[16];
@@ -1321,7 +1562,7 @@ __global__ __launch_bounds__(kFactorThreads) void k_factor_queue(const InstDev* 
         __syncthreads();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         const FrontDesc& F = fds[t];
-        factor_front<kQueueExtBatch>(insts[F.inst], F, P, invd, true, true);
+        factor_front<2, 6, 4>(insts[F.inst], F, P, invd, true);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         __syncthreads();
         if (sched_wave() && par >= 0) publish_add(D.cnt + par);
@@ -3582,7 +3823,7 @@ void launch_update(const InstDev* insts, const FrontDesc* fds, const StripItem* 
 }
 void launch_factor_queue(const InstDev* insts, const FrontDesc* fds, const DepLists& D, int grid, size_t lds,
                          hipStream_t st) {
-    if (D.nitems > 0) k_factor_queue<<<grid, kFactorThreads, lds, st>>>(insts, fds, D);
+    if (D.nitems > 0) k_factor_queue<<<grid, kFactorQueueThreads, lds, st>>>(insts, fds, D);
 }
 void launch_sweeps_queue(const InstDev* insts, const FrontDesc* fds, const DepLists& D, int grid, size_t lds,
                          int skip_done, hipStream_t st) {

@@ -5,6 +5,12 @@
 #include <algorithm>
 #include <cstdint>
 
+#if defined(__HIP__)
+#define KKT_HD __host__ __device__
+#else
+#define KKT_HD
+#endif
+
 namespace kkt {
 
 // Panels use an odd leading dimension r|1 in LDS and in HBM (conflict-free
@@ -14,6 +20,27 @@ namespace kkt {
 inline int64_t factor_lds_bytes(int r, int c) {
     const int64_t cp = (c + 15) & ~15;
     return (int64_t)(r | 1) * cp * 8 + (int64_t)r * 4 + 16;
+}
+
+// The front kernel's blocked panel: column blocks of 16, each with the rows
+// from its diagonal block down (own columns padded to 16, update rows padded
+// to 16), 16 doubles per row.
+constexpr int kFrontRowStride = 16;
+KKT_HD constexpr int64_t blocked_lds_bytes(int r, int c) {
+    const int64_t nbc = (c + 15) >> 4, rt = 16 * (nbc + ((r - c + 15) >> 4));
+    return 8 * kFrontRowStride * (nbc * rt - 8 * nbc * (nbc - 1));
+}
+constexpr int64_t kBlockedLdsMax = 158 * 1024;
+// Fronts that take the blocked panel with maxp panel waves: one wave covers 64
+// rows below the diagonal block. The few whose blocked panel is over the
+// budget although the column-major one fits stay column-major.
+KKT_HD constexpr bool front_blocked(int r, int c, int maxp) {
+    const int rt = 16 * (((c + 15) >> 4) + ((r - c + 15) >> 4));
+    return rt <= 16 + 64 * maxp && blocked_lds_bytes(r, c) <= kBlockedLdsMax;
+}
+// what a front of the factor launches reserves (eight or four waves)
+inline int64_t factor_launch_lds_bytes(int r, int c) {
+    return front_blocked(r, c, 4) ? std::max(factor_lds_bytes(r, c), blocked_lds_bytes(r, c)) : factor_lds_bytes(r, c);
 }
 
 // sweeps: (r|1) x c panel (padded to an even count) + r vector entries + c pivot reciprocals
