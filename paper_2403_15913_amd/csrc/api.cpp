@@ -150,10 +150,12 @@ hipError_t DevPattern::build(const Symbolic& S) {
 #undef UP
     // J by columns in pivot order, and the pivot position of every J entry's
     // column (the CG reads and writes the sweep vector directly)
+    std::vector<int> tl;
     std::vector<int> tp(S.n + 1, 0), trow(S.jt_row.size()), te(S.jt_e.size()), colp(S.j_col.size());
     for (int k = 0; k < S.n; k++) {
         const int j = S.perm[k];
         tp[k + 1] = tp[k] + (S.jt_ptr[j + 1] - S.jt_ptr[j]);
+        if (tp[k + 1] - tp[k] > kLongColumn) tl.push_back(k);
         for (int q = S.jt_ptr[j], o = tp[k]; q < S.jt_ptr[j + 1]; q++, o++) {
             trow[o] = S.jt_row[q];
             te[o] = S.jt_e[q];
@@ -161,11 +163,14 @@ hipError_t DevPattern::build(const Symbolic& S) {
     }
     for (size_t p = 0; p < S.j_col.size(); p++) colp[p] = S.iperm[S.j_col[p]];
     if ((e = upload(b_jtpptr, tp)) != hipSuccess || (e = upload(b_jtprow, trow)) != hipSuccess ||
-        (e = upload(b_jtpe, te)) != hipSuccess || (e = upload(b_jcolp, colp)) != hipSuccess)
+        (e = upload(b_jtpe, te)) != hipSuccess || (e = upload(b_jtplong, tl)) != hipSuccess ||
+        (e = upload(b_jcolp, colp)) != hipSuccess)
         return e;
     desc.jtp_ptr = (const int*)b_jtpptr.p;
     desc.jtp_row = (const int*)b_jtprow.p;
     desc.jtp_e = (const int*)b_jtpe.p;
+    desc.jtp_long = (const int*)b_jtplong.p;
+    desc.nlong = (int)tl.size();
     desc.j_colp = (const int*)b_jcolp.p;
     return hipSuccess;
 }
@@ -242,9 +247,10 @@ kkt_status Engine::place(const std::vector<const Symbolic*>& s, const std::vecto
         ko[q + 1] = ko[q] + S.nnzk;
         co[q + 1] = co[q] + S.sp_ptr[S.n];
         po[q + 1] = po[q] + 5 * (int64_t)((S.n + kBlock - 1) / kBlock) * kResidualSplit;
-        // reduction slots of the CG and the augmented solve: up to 8 per
-        // 256-row block of n and of m
-        ro[q + 1] = ro[q] + 8 * (int64_t)((S.n + kBlock - 1) / kBlock + (S.m + kBlock - 1) / kBlock) + 4;
+        // reduction slots of the CG and the augmented solve: up to 8 per part
+        // of a 256-row block of n and per block of m
+        ro[q + 1] = ro[q] + 8 * (int64_t)(kRowSplit * ((S.n + kBlock - 1) / kBlock) + (S.m + kBlock - 1) / kBlock) +
+                    (S.n + 15) / 16 + 4;  // (and one per 16 long columns)
         for (int k = 0; k < S.ns; k++) {
             // large fronts are factored and solved in HBM (no panel in LDS)
             if (is_large(S, k)) {
@@ -906,7 +912,7 @@ kkt_status Engine::replay(kkt_solve_info* infos, hipStream_t st) {
 // eta test when asked for, then S_gamma p_k and the update; iteration maxit
 // is the last test only.
 void Engine::cg_iteration(int k, int maxit, bool eta_test, hipStream_t st) {
-    TL(KKT_PHASE_CG, launch_cg_dir(di(), nitems, n_nitems, k, ndone, st));
+    TL(KKT_PHASE_CG, launch_cg_dir(di(), nitems, n_nitems, pat_of[0]->desc.nlong, k, ndone, st));
     if (k >= maxit) return;
     if (eta_test) TL(KKT_PHASE_CONTROL, launch_cg_eta_test(di(), cg_calls, ninst, k, ndone, st));
     sweeps(st, SKIP_CG);
@@ -922,7 +928,7 @@ kkt_status Engine::cg_schur(const Calls& C, double tol, int maxit, double eta_to
     const bool eta_test = eta_tol > 0.0;
     TL(KKT_PHASE_CONTROL, launch_fill_i32(nd, 0, 1, st));
     // f_gamma = f + gamma J^T g (pivot order), c = J K_gamma^{-1} f_gamma - g
-    TL(KKT_PHASE_CG, launch_cg_fg(di(), C, nitems, n_nitems, tol, maxit, eta_tol, st));
+    TL(KKT_PHASE_CG, launch_cg_fg(di(), C, nitems, n_nitems, pat_of[0]->desc.nlong, tol, maxit, eta_tol, st));
     sweeps(st, SKIP_NONE);
     TL(KKT_PHASE_CG, launch_cg_c(di(), C, mitems, n_mitems, ninst, st));
     hipError_t e = hipSuccess;
@@ -955,7 +961,7 @@ kkt_status Engine::cg_schur(const Calls& C, double tol, int maxit, double eta_to
         }
     }
     // dx = K_gamma^{-1}(f_gamma - J^T dy), then the saddle-system residual and eta
-    TL(KKT_PHASE_CG, launch_cg_dxrhs(di(), C, nitems, n_nitems, st));
+    TL(KKT_PHASE_CG, launch_cg_dxrhs(di(), C, nitems, n_nitems, pat_of[0]->desc.nlong, st));
     sweeps(st, SKIP_NONE);
     TL(KKT_PHASE_PERMUTE, launch_perm_out(di(), C, nitems, n_nitems, POUT_DX, st));
     TL(KKT_PHASE_RESIDUAL, launch_cg_residual(di(), C, nitems, n_nitems, mitems, n_mitems, ninst, st));
@@ -985,7 +991,7 @@ kkt_status Engine::solve_augmented(const AugCall& A, int maxit, double tol, kkt_
     last_stream = st;
     const int ni = 10;  // refinement of the first condensed solve: kkt_solve's defaults
     const double itol = 1e-14;
-    TL(KKT_PHASE_RESIDUAL, launch_aug_rhs(di(), A, nitems, n_nitems, 0, st));
+    TL(KKT_PHASE_RESIDUAL, launch_aug_rhs(di(), A, nitems, n_nitems, pat_of[0]->desc.nlong, 0, st));
     Calls C;
     std::memset(&C, 0, sizeof(C));
     C.b = aug_b;
@@ -1010,7 +1016,7 @@ kkt_status Engine::solve_augmented(const AugCall& A, int maxit, double tol, kkt_
         if (S.done) break;
         // correction: condensed right-hand side of e, one solve with the
         // factor, recovery of the slack and multiplier parts, update
-        TL(KKT_PHASE_RESIDUAL, launch_aug_rhs(di(), A, nitems, n_nitems, 1, st));
+        TL(KKT_PHASE_RESIDUAL, launch_aug_rhs(di(), A, nitems, n_nitems, pat_of[0]->desc.nlong, 1, st));
         solve_start(Ct, 0, 0.0, st);
         TL(KKT_PHASE_RESIDUAL, launch_aug_recover(di(), A, nitems, n_nitems, mitems, n_mitems, 1, st));
     }

@@ -34,6 +34,9 @@ struct dptr {
 // by a 16-lane group each instead of one thread (the symbolic analysis lists
 // them once per pattern).
 constexpr int kHeavyPairs = 8;
+// Columns of J with more than this many entries are summed by a 16-lane group
+// each in the J^T v kernels (listed once per pattern).
+constexpr int kLongColumn = 8;
 
 struct PatDev {
     int n, m, ns;
@@ -75,6 +78,8 @@ struct PatDev {
     dptr<const int> jtp_ptr;
     dptr<const int> jtp_row;
     dptr<const int> jtp_e;
+    dptr<const int> jtp_long;    // pivot positions of the columns with more than kLongColumn entries
+    int nlong;                   // ... and their number
     dptr<const int> j_colp;      // pivot position of the column of every CSR entry of J
 };
 

@@ -36,7 +36,7 @@ size_t carve(char* base, int n, int m, IpmBuffers* B) {
     B->dx = (double*)take(nn);
     B->ds = (double*)take(mm);
     B->dz = (double*)take(mm);
-    B->red = (double*)take(8 * (size_t)(4 * ((n + 255) / 256) + 4 * ((m + 255) / 256) + 8));
+    B->red = (double*)take(8 * (size_t)(4 * kRowSplit * ((n + 255) / 256) + 4 * ((m + 255) / 256) + 8));
     B->st = (IpmState*)take(sizeof(IpmState));
     return off;
 }

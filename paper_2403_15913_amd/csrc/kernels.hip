@@ -2307,10 +2307,12 @@ __global__ __launch_bounds__(256) void k_matvec(const InstDev* __restrict__ inst
 // iterations can be queued without reading decisions back.
 //
 // Reduction slots of one instance (4 per 256-row block):
-//   N-region red[4 b + k], n-side blocks:  0 max row sum of |A|, 1 max |f|
-//                                          (k_cg_fg); 2 max |r|, 3 max
-//                                          |J^T r| (k_cg_dir, eta test);
-//                                          0, 1 again for the final residual
+//   N-region red[4 (kRowSplit b + part) + k], n-side blocks: 0 max row sum of
+//                                          |A| (k_cg_rows, every part), 1 max
+//                                          |f| (k_cg_fg, part 0); 2 max |r|,
+//                                          3 max |J^T r| (k_cg_dir, eta test,
+//                                          part 0); 0, 1 of every part again
+//                                          for the final residual
 //   M-region red[mslot0 + 4 b + k]:        0 r.r, 1 max |dy| (k_cg_c with
 //                                          dy = 0, then k_cg_upd); 2 max |g|,
 //                                          3 max row sum of |J| (k_cg_c)
@@ -2347,18 +2349,32 @@ __device__ inline double block_max(double v) {
 }
 
 __device__ __forceinline__ int cg_nb(int len) { return (len + 255) >> 8; }
-__device__ __forceinline__ int cg_mslot0(const InstDev& I) { return 4 * cg_nb(I.P.n); }
-__device__ __forceinline__ int cg_qslot0(const InstDev& I) { return 4 * (cg_nb(I.P.n) + cg_nb(I.P.m)); }
+// (the n-side region holds kRowSplit records per 256-row block)
+__device__ __forceinline__ int cg_mslot0(const InstDev& I) { return 4 * kRowSplit * cg_nb(I.P.n); }
+__device__ __forceinline__ int cg_qslot0(const InstDev& I) { return cg_mslot0(I) + 4 * cg_nb(I.P.m); }
 
-// fixed-order sum / maximum over slot k of nb blocks (stride `stride`)
+// fixed-order sum / maximum over slot k of nb blocks (stride `stride`), eight
+// loads in flight (indices past the end repeat the last slot: a maximum does
+// not change, and a sum leaves them out)
+template <class Use>
+__device__ __forceinline__ void slots_each(const double* red, int nb, int stride, int k, Use&& use) {
+    for (int b0 = threadIdx.x; b0 < nb; b0 += 8 * (int)blockDim.x) {
+        double t[8];
+#pragma unroll
+        for (int u = 0; u < 8; u++) t[u] = red[stride * min(b0 + u * (int)blockDim.x, nb - 1) + k];
+#pragma unroll
+        for (int u = 0; u < 8; u++)
+            if (b0 + u * (int)blockDim.x < nb) use(t[u]);
+    }
+}
 __device__ inline double slots_sum(const double* red, int nb, int stride, int k) {
     double v = 0.0;
-    for (int b = threadIdx.x; b < nb; b += blockDim.x) v += red[stride * b + k];
+    slots_each(red, nb, stride, k, [&](double t) { v += t; });
     return block_sum(v);
 }
 __device__ inline double slots_max(const double* red, int nb, int stride, int k) {
     double v = 0.0;
-    for (int b = threadIdx.x; b < nb; b += blockDim.x) v = fmax(v, red[stride * b + k]);
+    slots_each(red, nb, stride, k, [&](double t) { v = fmax(v, t); });
     return block_max(v);
 }
 // maximum of the negated slots (a minimum, for slots that may all be positive)
@@ -2392,12 +2408,117 @@ __device__ __forceinline__ double gather_dot(int q0, int q1, const double* __res
     return s;
 }
 
+// Columns of J with more than kLongColumn entries (a stage's coupling
+// variables hold about 70 where most columns hold three or four) are summed by
+// 16-lane groups in workgroups of their own behind a kernel's row blocks; one
+// lane alone takes two dependent memory round trips per four entries while
+// its wave waits. Lane l loads terms l, l + 16, ...; every lane then adds all
+// terms in column order, taking them from the lanes by row broadcasts, so the
+// sum has the bits of the one-lane loop. (Distillation pattern, n = 142,000,
+// 10,000 columns of 70 entries: k_cg_dir 35.8 -> 16.3 us; n = 21,371:
+// k_aug_rhs 30.6 -> 6.2 us.)
+__device__ __forceinline__ bool long_column(int q0, int q1) { return q1 - q0 > kLongColumn; }
+
+// the column of this thread's group in workgroup b of the long columns (pivot
+// position), or -1
+__device__ __forceinline__ int group_column(const PatDev& P, int b) {
+    const int h = b * 16 + (int)(threadIdx.x >> 4);
+    return h < P.nlong ? P.jtp_long[h] : -1;
+}
+
+// term(q, a, x, y): entry q's coefficient and values; add(a, x, y) in column
+// order (by every lane; terms past the end are zero)
+template <class Term, class Add>
+__device__ __forceinline__ void column_terms(int q0, int q1, Term&& term, Add&& add) {
+    const int l = threadIdx.x & 15;
+    for (int q = q0; q < q1; q += 64) {
+        double a[4], x[4], y[4];
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            const int qu = q + 16 * u + l;
+            term(min(qu, q1 - 1), a[u], x[u], y[u]);
+            a[u] = qu < q1 ? a[u] : 0.0;
+            x[u] = qu < q1 ? x[u] : 0.0;
+            y[u] = qu < q1 ? y[u] : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; u++)
+            if (q + 16 * u < q1)
+                static_for<16>([&](auto K) {
+                    constexpr int k = K;
+                    add(row_bcast<k>(a[u]), row_bcast<k>(x[u]), row_bcast<k>(y[u]));
+                });
+    }
+}
+
+// Sums over the entries p0 .. p1 - 1 of a row of a symmetric row list (or of a
+// column of J) by a 16-lane group: lane l takes entries l, l + 16, ..., four
+// of its entries in flight; term(p) gives an entry's coefficient and gathered
+// value, add(a, t) takes it and their product. The lanes' sums are then
+// combined by the caller.
+template <class Term, class Add>
+__device__ __forceinline__ void lane_terms(int64_t p0, int64_t p1, int l, Term&& term, Add&& add) {
+    for (int64_t p = p0 + l; p < p1; p += 64) {
+        double a[4], x[4];
+#pragma unroll
+        for (int u = 0; u < 4; u++) term(min(p + 16 * u, p1 - 1), a[u], x[u]);
+#pragma unroll
+        for (int u = 0; u < 4; u++)
+            if (p + 16 * u < p1) add(a[u], a[u] * x[u]);
+    }
+}
+__device__ __forceinline__ double sum16(double v) {
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o, 16);
+    return v;
+}
+// Row kernels by 16-lane groups: kRowSplit workgroups of 256 threads share a
+// 256-row item, each group takes kRowsPerGroup of their rows (one thread per
+// row reads a wave's 64 rows, 20 to 140 entries each, uncoalesced and one
+// round trip after another: measured on n = 142,000 k_cg_res_n 200 -> 46 us,
+// on n = 21,371 k_aug_res_n 73 -> 16 us).
+constexpr int kRowsPerGroup = 16 / kRowSplit;
+// row t (0 .. kRowsPerGroup - 1) of this thread's group
+__device__ __forceinline__ int group_row(const WorkItem& it, int t) {
+    return it.id + (int)(blockIdx.x % kRowSplit) * 16 * kRowsPerGroup + 16 * t + (int)(threadIdx.x >> 4);
+}
+__device__ __forceinline__ int row_slot(const WorkItem& it) {
+    return (it.id >> 8) * kRowSplit + (int)(blockIdx.x % kRowSplit);
+}
+
+// L-region red[lslot0 + b]: max |J^T r| over the 16 columns of long-column
+// workgroup b (k_cg_dir, eta test)
+__device__ __forceinline__ int cg_lslot0(const InstDev& I) { return cg_qslot0(I) + 2 * cg_nb(I.P.m); }
+
 // f_gamma = f + gamma J^T g in pivot order (sweep vector and a copy for dx),
-// the n-side norms (per row i of the saddle matrix, sum_j |K0_ij| +
-// sum_r |J_ri|; |f_i|), and the CG record's set-up (workgroup 0).
+// the maximum of |f_i|, and the CG record's set-up (workgroup 0).
 __global__ __launch_bounds__(256) void k_cg_fg(const InstDev* __restrict__ insts, Calls C,
-                                               const WorkItem* __restrict__ items, double tol, int maxit,
+                                               const WorkItem* __restrict__ items, int nitems, double tol, int maxit,
                                                double eta_tol) {
+    const double* __restrict__ g = C.g;
+    auto out = [&](const InstDev& I, int k, double sum) {
+        const double v = C.f[I.n_off + I.P.perm[k]] + C.gamma * sum;
+        I.fg[k] = v;
+        I.y[k] = v;
+    };
+    if ((int)blockIdx.x >= nitems) {  // long columns
+        const InstDev& I = insts[0];
+        const int k = group_column(I.P, blockIdx.x - nitems);
+        if (k < 0) return;
+        double s = 0.0;
+        column_terms(
+            I.P.jtp_ptr[k], I.P.jtp_ptr[k + 1],
+            [&](int q, double& a, double& x, double& y) {
+                const int row = I.P.jtp_row[q];
+                const bool eq = !C.eqm || C.eqm[row];
+                a = eq ? I.jtv[q] : 0.0;
+                x = eq ? g[row] : 0.0;
+                y = 0.0;
+            },
+            [&](double a, double x, double) { s += a * x; });
+        if ((threadIdx.x & 15) == 0) out(I, k, s);
+        return;
+    }
     const WorkItem it = items[blockIdx.x];
     const InstDev& I = insts[it.inst];
     if (it.id == 0 && threadIdx.x == 0) {
@@ -2412,34 +2533,56 @@ __global__ __launch_bounds__(256) void k_cg_fg(const InstDev* __restrict__ insts
         G->eta = 0.0;
     }
     const int k = it.id + threadIdx.x;
-    double arow = 0.0, fa = 0.0;
+    double fa = 0.0;
     if (k < I.P.n) {
-        const int j = I.P.perm[k];
-        const double* __restrict__ g = C.g + I.m_off;
-        double s = 0.0, csum = 0.0;
-        for (int q = I.P.jtp_ptr[k]; q < I.P.jtp_ptr[k + 1]; q++) {
-            const int row = I.P.jtp_row[q];
-            if (C.eqm && !C.eqm[row]) continue;  // general HyKKT: equality rows only
-            const double a = I.jtv[q];
-            s += a * g[row];
-            csum += fabs(a);
+        const int q0 = I.P.jtp_ptr[k], q1 = I.P.jtp_ptr[k + 1];
+        if (!long_column(q0, q1)) {
+            double s = 0.0;
+            for (int q = q0; q < q1; q++) {
+                const int row = I.P.jtp_row[q];
+                if (C.eqm && !C.eqm[row]) continue;  // general HyKKT: equality rows only
+                s += I.jtv[q] * g[row];
+            }
+            out(I, k, s);
         }
-        const double fj = C.f[I.n_off + j];
-        const double v = fj + C.gamma * s;
-        I.fg[k] = v;
-        I.y[k] = v;
-        double ka = 0.0;
-        for (int64_t p = I.P.sp_ptr[j]; p < I.P.sp_ptr[j + 1]; p++) ka += fabs(I.k0csr[p]);
-        arow = ka + csum;
-        fa = fabs(fj);
+        fa = fabs(C.f[I.n_off + I.P.perm[k]]);
+    }
+    fa = block_max(fa);
+    if (threadIdx.x == 0) I.red[4 * kRowSplit * (it.id >> 8) + 1] = fa;
+}
+
+// the maximum over the primal rows of the saddle matrix of sum_j |K0_ij| +
+// sum_r |J_ri| (general HyKKT: equality rows of J only), original numbering
+__global__ __launch_bounds__(256) void k_cg_rows(const InstDev* __restrict__ insts, Calls C,
+                                                 const WorkItem* __restrict__ items) {
+    const WorkItem it = items[blockIdx.x / kRowSplit];
+    const InstDev& I = insts[it.inst];
+    const int l = threadIdx.x & 15;
+    double arow = 0.0;
+#pragma unroll
+    for (int t = 0; t < kRowsPerGroup; t++) {
+        const int j = group_row(it, t);
+        double s = 0.0;
+        if (j < I.P.n) {
+            lane_terms(
+                I.P.sp_ptr[j], I.P.sp_ptr[j + 1], l,
+                [&](int64_t p, double& a, double& x) {
+                    a = I.k0csr[p];
+                    x = 0.0;
+                },
+                [&](double a, double) { s += fabs(a); });
+            lane_terms(
+                I.P.jt_ptr[j], I.P.jt_ptr[j + 1], l,
+                [&](int64_t q, double& a, double& x) {
+                    a = !C.eqm || C.eqm[I.P.jt_row[q]] ? I.jraw[I.P.jt_e[q]] : 0.0;
+                    x = 0.0;
+                },
+                [&](double a, double) { s += fabs(a); });
+        }
+        arow = fmax(arow, sum16(s));
     }
     arow = block_max(arow);
-    fa = block_max(fa);
-    if (threadIdx.x == 0) {
-        double* s = I.red + 4 * (it.id >> 8);
-        s[0] = arow;
-        s[1] = fa;
-    }
+    if (threadIdx.x == 0) I.red[4 * row_slot(it)] = arow;
 }
 
 // After the sweeps: c = J K_gamma^{-1} f_gamma - g; r = c; p_old = 0; dy = 0;
@@ -2487,8 +2630,9 @@ __global__ __launch_bounds__(256) void k_cg_c(const InstDev* __restrict__ insts,
 // With eta_tol > 0 the maxima of |r_k| and |J^T r_k| go to the N-region for
 // k_cg_eta_test.
 __global__ __launch_bounds__(256) void k_cg_dir(const InstDev* __restrict__ insts,
-                                                const WorkItem* __restrict__ items, int k, int* ndone) {
-    const WorkItem it = items[blockIdx.x];
+                                                const WorkItem* __restrict__ items, int nitems, int k, int* ndone) {
+    const bool longs = (int)blockIdx.x >= nitems;  // long columns (behind the row blocks)
+    const WorkItem it = longs ? WorkItem{0, -1} : items[blockIdx.x];
     const InstDev& I = insts[it.inst];
     CgState* G = I.cg;
     if (G->done) return;  // uniform per block
@@ -2519,45 +2663,70 @@ __global__ __launch_bounds__(256) void k_cg_dir(const InstDev* __restrict__ inst
     double* __restrict__ pn = parity ? I.pvec2 : I.pvec;
     const double* __restrict__ po = parity ? I.pvec : I.pvec2;
     const double* __restrict__ r = I.rvec;
-    const int kk = it.id + threadIdx.x;
-    double ra = 0.0, ja = 0.0;
-    if (kk < I.P.m) {
-        pn[kk] = fma(beta, po[kk], r[kk]);
-        ra = fabs(r[kk]);
-    }
     const bool eta_test = G->eta_tol > 0.0;
-    if (kk < I.P.n) {
-        const int q0 = I.P.jtp_ptr[kk], q1 = I.P.jtp_ptr[kk + 1];
-        double s = 0.0, t = 0.0;
-        for (int q = q0; q < q1; q += 4) {
-            int row[4];
-            double a[4], rv[4], pv[4];
-#pragma unroll
-            for (int u = 0; u < 4; u++) {
-                const int qc = min(q + u, q1 - 1);
-                row[u] = I.P.jtp_row[qc];
-                a[u] = I.jtv[qc];
-            }
-#pragma unroll
-            for (int u = 0; u < 4; u++) {
-                rv[u] = r[row[u]];
-                pv[u] = po[row[u]];
-            }
-#pragma unroll
-            for (int u = 0; u < 4; u++)
-                if (q + u < q1) {
-                    s += a[u] * fma(beta, pv[u], rv[u]);
-                    t += a[u] * rv[u];
-                }
+    double ra = 0.0, ja = 0.0;
+    if (longs) {
+        const int kk = group_column(I.P, blockIdx.x - nitems);
+        if (kk >= 0) {
+            double s = 0.0, t = 0.0;
+            column_terms(
+                I.P.jtp_ptr[kk], I.P.jtp_ptr[kk + 1],
+                [&](int q, double& a, double& x, double& y) {
+                    const int row = I.P.jtp_row[q];
+                    a = I.jtv[q];
+                    y = r[row];
+                    x = fma(beta, po[row], y);
+                },
+                [&](double a, double x, double y) {
+                    s += a * x;
+                    t += a * y;
+                });
+            if ((threadIdx.x & 15) == 0) I.y[kk] = s;
+            ja = fabs(t);
         }
-        I.y[kk] = s;
-        ja = fabs(t);
+    } else {
+        const int kk = it.id + threadIdx.x;
+        if (kk < I.P.m) {
+            pn[kk] = fma(beta, po[kk], r[kk]);
+            ra = fabs(r[kk]);
+        }
+        const int q0 = kk < I.P.n ? I.P.jtp_ptr[kk] : 0, q1 = kk < I.P.n ? I.P.jtp_ptr[kk + 1] : 0;
+        if (kk < I.P.n && !long_column(q0, q1)) {
+            double s = 0.0, t = 0.0;
+            for (int q = q0; q < q1; q += 4) {
+                int row[4];
+                double a[4], rv[4], pv[4];
+#pragma unroll
+                for (int u = 0; u < 4; u++) {
+                    const int qc = min(q + u, q1 - 1);
+                    row[u] = I.P.jtp_row[qc];
+                    a[u] = I.jtv[qc];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; u++) {
+                    rv[u] = r[row[u]];
+                    pv[u] = po[row[u]];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; u++)
+                    if (q + u < q1) {
+                        s += a[u] * fma(beta, pv[u], rv[u]);
+                        t += a[u] * rv[u];
+                    }
+            }
+            I.y[kk] = s;
+            ja = fabs(t);
+        }
     }
     if (!eta_test) return;  // uniform per launch
     ra = block_max(ra);
     ja = block_max(ja);
     if (threadIdx.x == 0) {
-        double* sl = I.red + 4 * (it.id >> 8);
+        if (longs) {
+            I.red[cg_lslot0(I) + blockIdx.x - nitems] = ja;
+            return;
+        }
+        double* sl = I.red + 4 * kRowSplit * (it.id >> 8);
         sl[2] = ra;
         sl[3] = ja;
     }
@@ -2577,10 +2746,10 @@ __global__ __launch_bounds__(256) void k_cg_eta_test(const InstDev* __restrict__
     const int nbn = cg_nb(I.P.n), nbm = cg_nb(I.P.m);
     const double* Nr = I.red;
     const double* Mr = I.red + cg_mslot0(I);
-    const double norm_a = fmax(slots_max(Nr, nbn, 4, 0), slots_max(Mr, nbm, 4, 3));
-    const double norm_rhs = fmax(slots_max(Nr, nbn, 4, 1), slots_max(Mr, nbm, 4, 2));
-    const double rmax = slots_max(Nr, nbn, 4, 2);
-    const double jrmax = slots_max(Nr, nbn, 4, 3);
+    const double norm_a = fmax(slots_max(Nr, kRowSplit * nbn, 4, 0), slots_max(Mr, nbm, 4, 3));
+    const double norm_rhs = fmax(slots_max(Nr, nbn, 4 * kRowSplit, 1), slots_max(Mr, nbm, 4, 2));
+    const double rmax = slots_max(Nr, nbn, 4 * kRowSplit, 2);
+    const double jrmax = fmax(slots_max(Nr, nbn, 4 * kRowSplit, 3), slots_max(I.red + cg_lslot0(I), (I.P.nlong + 15) >> 4, 1, 0));
     const double dymax = slots_max(Mr, nbm, 4, 1);
     if (threadIdx.x == 0) {
         G->norm_a = norm_a;
@@ -2661,39 +2830,72 @@ __global__ __launch_bounds__(256) void k_cg_upd(const InstDev* __restrict__ inst
 
 // right-hand side of the last solve: y[k] = f_gamma[k] - (J^T dy)_{perm[k]}
 __global__ __launch_bounds__(256) void k_cg_dxrhs(const InstDev* __restrict__ insts, Calls C,
-                                                  const WorkItem* __restrict__ items) {
-    const WorkItem it = items[blockIdx.x];
+                                                  const WorkItem* __restrict__ items, int nitems) {
+    const bool longs = (int)blockIdx.x >= nitems;
+    const WorkItem it = longs ? WorkItem{0, -1} : items[blockIdx.x];
     const InstDev& I = insts[it.inst];
-    const int k = it.id + threadIdx.x;
-    if (k >= I.P.n) return;
     const double* __restrict__ dy = C.dy + I.m_off;
-    const double s = gather_dot(I.P.jtp_ptr[k], I.P.jtp_ptr[k + 1], I.jtv, I.P.jtp_row, [&](int r) { return dy[r]; });
-    I.y[k] = I.fg[k] - s;
+    const int k = longs ? group_column(I.P, blockIdx.x - nitems) : it.id + (int)threadIdx.x;
+    if (k < 0 || k >= I.P.n) return;
+    const int q0 = I.P.jtp_ptr[k], q1 = I.P.jtp_ptr[k + 1];
+    if (longs) {
+        double s = 0.0;
+        column_terms(
+            q0, q1,
+            [&](int q, double& a, double& x, double& y) {
+                a = I.jtv[q];
+                x = dy[I.P.jtp_row[q]];
+                y = 0.0;
+            },
+            [&](double a, double x, double) { s += a * x; });
+        if ((threadIdx.x & 15) == 0) I.y[k] = I.fg[k] - s;
+    } else if (!long_column(q0, q1)) {
+        I.y[k] = I.fg[k] - gather_dot(q0, q1, I.jtv, I.P.jtp_row, [&](int r) { return dy[r]; });
+    }
 }
 
 // Saddle-system residual of (dx, dy): rows of the primal block,
 // f - K0 dx - J^T dy (original numbering), with the maxima of |res| and |dx|.
 __global__ __launch_bounds__(256) void k_cg_res_n(const InstDev* __restrict__ insts, Calls C,
                                                   const WorkItem* __restrict__ items) {
-    const WorkItem it = items[blockIdx.x];
+    const WorkItem it = items[blockIdx.x / kRowSplit];
     const InstDev& I = insts[it.inst];
-    const int j = it.id + threadIdx.x;
+    const int l = threadIdx.x & 15;
+    const double* __restrict__ dx = C.dx + I.n_off;
+    const double* __restrict__ dy = C.dy + I.m_off;
     double ra = 0.0, xa = 0.0;
-    if (j < I.P.n) {
-        const double* __restrict__ dx = C.dx + I.n_off;
-        const double* __restrict__ dy = C.dy + I.m_off;
+#pragma unroll
+    for (int t = 0; t < kRowsPerGroup; t++) {
+        const int j = group_row(it, t);
         double s = 0.0;
-        for (int64_t p = I.P.sp_ptr[j]; p < I.P.sp_ptr[j + 1]; p++) s += I.k0csr[p] * dx[I.P.sp_col[p]];
-        for (int q = I.P.jt_ptr[j]; q < I.P.jt_ptr[j + 1]; q++) s += I.jraw[I.P.jt_e[q]] * dy[I.P.jt_row[q]];
-        ra = fabs(C.f[I.n_off + j] - s);
-        xa = fabs(dx[j]);
+        if (j < I.P.n) {
+            lane_terms(
+                I.P.sp_ptr[j], I.P.sp_ptr[j + 1], l,
+                [&](int64_t p, double& a, double& x) {
+                    a = I.k0csr[p];
+                    x = dx[I.P.sp_col[p]];
+                },
+                [&](double, double ax) { s += ax; });
+            lane_terms(
+                I.P.jt_ptr[j], I.P.jt_ptr[j + 1], l,
+                [&](int64_t q, double& a, double& x) {
+                    a = I.jraw[I.P.jt_e[q]];
+                    x = dy[I.P.jt_row[q]];
+                },
+                [&](double, double ax) { s += ax; });
+        }
+        s = sum16(s);
+        if (l == 0 && j < I.P.n) {
+            ra = fmax(ra, fabs(C.f[I.n_off + j] - s));
+            xa = fmax(xa, fabs(dx[j]));
+        }
     }
     ra = block_max(ra);
     xa = block_max(xa);
     if (threadIdx.x == 0) {
-        double* s = I.red + 4 * (it.id >> 8);
-        s[0] = ra;
-        s[1] = xa;
+        double* sl = I.red + 4 * row_slot(it);
+        sl[0] = ra;
+        sl[1] = xa;
     }
 }
 
@@ -2729,7 +2931,7 @@ __global__ __launch_bounds__(256) void k_cg_eta(const InstDev* __restrict__ inst
     const int nbn = cg_nb(I.P.n), nbm = cg_nb(I.P.m);
     const double* Nr = I.red;
     const double* Qr = I.red + cg_qslot0(I);
-    const double r1 = slots_max(Nr, nbn, 4, 0), x1 = slots_max(Nr, nbn, 4, 1);
+    const double r1 = slots_max(Nr, kRowSplit * nbn, 4, 0), x1 = slots_max(Nr, kRowSplit * nbn, 4, 1);
     const double r2 = slots_max(Qr, nbm, 2, 0), y2 = slots_max(Qr, nbm, 2, 1);
     if (threadIdx.x == 0) {
         const double den = G->norm_a * fmax(x1, y2) + G->norm_rhs;
@@ -2746,8 +2948,8 @@ __global__ __launch_bounds__(256) void k_cg_norms(const InstDev* __restrict__ in
     CgState* G = I.cg;
     const int nbn = cg_nb(I.P.n), nbm = cg_nb(I.P.m);
     const double* Mr = I.red + cg_mslot0(I);
-    const double an = fmax(slots_max(I.red, nbn, 4, 0), slots_max(Mr, nbm, 4, 3));
-    const double fm = fmax(slots_max(I.red, nbn, 4, 1), slots_max(Mr, nbm, 4, 2));
+    const double an = fmax(slots_max(I.red, kRowSplit * nbn, 4, 0), slots_max(Mr, nbm, 4, 3));
+    const double fm = fmax(slots_max(I.red, nbn, 4 * kRowSplit, 1), slots_max(Mr, nbm, 4, 2));
     if (threadIdx.x == 0) {
         G->norm_a = an;
         G->norm_rhs = fm;
@@ -2766,26 +2968,40 @@ __global__ __launch_bounds__(256) void k_cg_norms(const InstDev* __restrict__ in
 // augmented system and solves for the correction the same way.
 // Slots: N-region 8 per block (k_aug_res_n), M-region 8 per block after it.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ int aug_mslot0(const InstDev& I) { return 8 * cg_nb(I.P.n); }
+__device__ __forceinline__ int aug_mslot0(const InstDev& I) { return 8 * kRowSplit * cg_nb(I.P.n); }
 
 // b_j = p1_j - sum_q J_qj (p2_q - Sigma_s,q p4_q) with p = -r (mode 0) or
 // p = e (mode 1); pivot-ordered threads, b in original numbering
 __global__ __launch_bounds__(256) void k_aug_rhs(const InstDev* __restrict__ insts, AugCall A,
-                                                 const WorkItem* __restrict__ items, int mode) {
-    const WorkItem it = items[blockIdx.x];
+                                                 const WorkItem* __restrict__ items, int nitems, int mode) {
+    const bool longs = (int)blockIdx.x >= nitems;
+    const WorkItem it = longs ? WorkItem{0, -1} : items[blockIdx.x];
     const InstDev& I = insts[it.inst];
     if (mode == 1 && I.aug->done) return;  // uniform per block
-    const int k = it.id + threadIdx.x;
-    if (k >= I.P.n) return;
+    const int k = longs ? group_column(I.P, blockIdx.x - nitems) : it.id + (int)threadIdx.x;
+    if (k < 0 || k >= I.P.n) return;
     const int n = I.P.n, m = I.P.m;
     const int j = I.P.perm[k];
     const double* __restrict__ p2 = mode ? I.aug_e + n : A.r2;
     const double* __restrict__ p4 = mode ? I.aug_e + n + m : A.r4;
     const double sgn = mode ? 1.0 : -1.0;
+    const int q0 = I.P.jtp_ptr[k], q1 = I.P.jtp_ptr[k + 1];
     double s = 0.0;
-    for (int q = I.P.jtp_ptr[k]; q < I.P.jtp_ptr[k + 1]; q++) {
-        const int row = I.P.jtp_row[q];
-        s += I.jtv[q] * (sgn * p2[row] - I.ssv[row] * (sgn * p4[row]));
+    if (longs) {
+        column_terms(
+            q0, q1,
+            [&](int q, double& a, double& x, double& y) {
+                const int row = I.P.jtp_row[q];
+                a = I.jtv[q];
+                x = sgn * p2[row] - I.ssv[row] * (sgn * p4[row]);
+                y = 0.0;
+            },
+            [&](double a, double x, double) { s += a * x; });
+        if ((threadIdx.x & 15) != 0) return;
+    } else {
+        if (long_column(q0, q1)) return;
+        s = gather_dot(q0, q1, I.jtv, I.P.jtp_row,
+                       [&](int row) { return sgn * p2[row] - I.ssv[row] * (sgn * p4[row]); });
     }
     const double p1 = mode ? I.aug_e[j] : -A.r1[j];
     I.aug_b[j] = p1 - s;
@@ -2854,33 +3070,49 @@ __device__ __forceinline__ double aug_ratio(double r, double den) {
 // the row sums of |A| and the maxima of |dx| and |r1|
 __global__ __launch_bounds__(256) void k_aug_res_n(const InstDev* __restrict__ insts, AugCall A,
                                                    const WorkItem* __restrict__ items) {
-    const WorkItem it = items[blockIdx.x];
+    const WorkItem it = items[blockIdx.x / kRowSplit];
     const InstDev& I = insts[it.inst];
     if (I.aug->done) return;
-    const int j = it.id + threadIdx.x;
+    const int l = threadIdx.x & 15;
     double ea = 0.0, om = 0.0, ar = 0.0, xa = 0.0, ba = 0.0;
-    if (j < I.P.n) {
+#pragma unroll
+    for (int t = 0; t < kRowsPerGroup; t++) {
+        const int j = group_row(it, t);
         double s = 0.0, den = 0.0, rs = 0.0;
-        for (int64_t p = I.P.sp_ptr[j]; p < I.P.sp_ptr[j + 1]; p++) {
-            const double a = I.k0csr[p], t = a * A.dx[I.P.sp_col[p]];
-            s += t;
-            den += fabs(t);
+        auto add = [&](double a, double ax) {
+            s += ax;
+            den += fabs(ax);
             rs += fabs(a);
+        };
+        if (j < I.P.n) {
+            lane_terms(
+                I.P.sp_ptr[j], I.P.sp_ptr[j + 1], l,
+                [&](int64_t p, double& a, double& x) {
+                    a = I.k0csr[p];
+                    x = A.dx[I.P.sp_col[p]];
+                },
+                add);
+            lane_terms(
+                I.P.jt_ptr[j], I.P.jt_ptr[j + 1], l,
+                [&](int64_t q, double& a, double& x) {
+                    a = I.jraw[I.P.jt_e[q]];
+                    x = A.dz[I.P.jt_row[q]];
+                },
+                add);
         }
-        for (int q = I.P.jt_ptr[j]; q < I.P.jt_ptr[j + 1]; q++) {
-            const double a = I.jraw[I.P.jt_e[q]], t = a * A.dz[I.P.jt_row[q]];
-            s += t;
-            den += fabs(t);
-            rs += fabs(a);
+        s = sum16(s);
+        den = sum16(den);
+        rs = sum16(rs);
+        if (l == 0 && j < I.P.n) {
+            const double p1 = -A.r1[j];
+            const double e1 = p1 - s;
+            I.aug_e[j] = e1;
+            ea = fmax(ea, fabs(e1));
+            om = fmax(om, aug_ratio(fabs(e1), den + fabs(p1)));
+            ar = fmax(ar, rs);
+            xa = fmax(xa, fabs(A.dx[j]));
+            ba = fmax(ba, fabs(p1));
         }
-        const double p1 = -A.r1[j];
-        const double e1 = p1 - s;
-        I.aug_e[j] = e1;
-        ea = fabs(e1);
-        om = aug_ratio(ea, den + fabs(p1));
-        ar = rs;
-        xa = fabs(A.dx[j]);
-        ba = fabs(p1);
     }
     ea = block_max(ea);
     om = block_max(om);
@@ -2888,7 +3120,7 @@ __global__ __launch_bounds__(256) void k_aug_res_n(const InstDev* __restrict__ i
     xa = block_max(xa);
     ba = block_max(ba);
     if (threadIdx.x == 0) {
-        double* sl = I.red + 8 * (it.id >> 8);
+        double* sl = I.red + 8 * row_slot(it);
         sl[0] = ea;
         sl[1] = om;
         sl[2] = ar;
@@ -2953,9 +3185,17 @@ __global__ __launch_bounds__(256) void k_aug_decide(const InstDev* __restrict__ 
     const int nbn = cg_nb(I.P.n), nbm = cg_nb(I.P.m);
     const double* Nr = I.red;
     const double* Mr = I.red + aug_mslot0(I);
-    double v[5];
-    for (int k = 0; k < 5; k++) v[k] = fmax(slots_max(Nr, nbn, 8, k), slots_max(Mr, nbm, 8, k));
+    double v[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < 5; k++) {
+        slots_each(Nr, kRowSplit * nbn, 8, k, [&](double t) { v[k] = fmax(v[k], t); });
+        slots_each(Mr, nbm, 8, k, [&](double t) { v[k] = fmax(v[k], t); });
+    }
+    __shared__ double top[5];
+    block_max5(v[0], v[1], v[2], v[3], v[4], top);
+    __syncthreads();
     if (threadIdx.x != 0) return;
+    for (int k = 0; k < 5; k++) v[k] = top[k];
     const double den = v[2] * v[3] + v[4];
     S->eta_prev = S->eta;
     S->omega_prev = S->omega;
@@ -3004,7 +3244,7 @@ __global__ __launch_bounds__(256) void k_aug_revert_m(const InstDev* __restrict_
 // W x comes from the factor's kept K0 = W + delta I (Sigma_x = 0).
 // Slots: red[4 b + k] for the n-side blocks, red[4 nbn + 4 b + k] for m-side.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ int ipm_m0(const InstDev& I) { return 4 * cg_nb(I.P.n); }
+__device__ __forceinline__ int ipm_m0(const InstDev& I) { return 4 * kRowSplit * cg_nb(I.P.n); }
 
 // n-side: max |c|; m-side: max |u|; then the record (one workgroup per
 // instance reduces in the second kernel)
@@ -3055,22 +3295,40 @@ __global__ __launch_bounds__(256) void k_ipm_dsw(const InstDev* __restrict__ ins
 // r1 = (K0 - delta I) x + c + J^T z
 __global__ __launch_bounds__(256) void k_ipm_res_n(const InstDev* __restrict__ insts, IpmCall P,
                                                    const WorkItem* __restrict__ items, double delta) {
-    const WorkItem it = items[blockIdx.x];
+    const WorkItem it = items[blockIdx.x / kRowSplit];
     const InstDev& I = insts[it.inst];
-    const int j = it.id + threadIdx.x;
+    const int l = threadIdx.x & 15;
     double ra = 0.0;
-    if (j < I.P.n) {
-        double s = 0.0;
-        for (int64_t p = I.P.sp_ptr[j]; p < I.P.sp_ptr[j + 1]; p++) s += I.k0csr[p] * P.x[I.P.sp_col[p]];
-        s -= delta * P.x[j];
-        double t = 0.0;
-        for (int q = I.P.jt_ptr[j]; q < I.P.jt_ptr[j + 1]; q++) t += P.jv[I.P.jt_e[q]] * P.z[I.P.jt_row[q]];
-        const double r = s + P.c[j] + t;
-        P.r1[j] = r;
-        ra = fabs(r);
+#pragma unroll
+    for (int u = 0; u < kRowsPerGroup; u++) {
+        const int j = group_row(it, u);
+        double s = 0.0, t = 0.0;
+        if (j < I.P.n) {
+            lane_terms(
+                I.P.sp_ptr[j], I.P.sp_ptr[j + 1], l,
+                [&](int64_t p, double& a, double& x) {
+                    a = I.k0csr[p];
+                    x = P.x[I.P.sp_col[p]];
+                },
+                [&](double, double ax) { s += ax; });
+            lane_terms(
+                I.P.jt_ptr[j], I.P.jt_ptr[j + 1], l,
+                [&](int64_t q, double& a, double& x) {
+                    a = P.jv[I.P.jt_e[q]];
+                    x = P.z[I.P.jt_row[q]];
+                },
+                [&](double, double ax) { t += ax; });
+        }
+        s = sum16(s);
+        t = sum16(t);
+        if (l == 0 && j < I.P.n) {
+            const double r = s - delta * P.x[j] + P.c[j] + t;
+            P.r1[j] = r;
+            ra = fmax(ra, fabs(r));
+        }
     }
     ra = block_max(ra);
-    if (threadIdx.x == 0) P.red[4 * (it.id >> 8)] = ra;
+    if (threadIdx.x == 0) P.red[4 * row_slot(it)] = ra;
 }
 
 // r4 = J x + s - u, partial s^T z
@@ -3101,7 +3359,7 @@ __global__ __launch_bounds__(256) void k_ipm_res_m(const InstDev* __restrict__ i
 __global__ __launch_bounds__(256) void k_ipm_decide(const InstDev* __restrict__ insts, IpmCall P, double delta) {
     const InstDev& I = insts[0];
     const int nbn = cg_nb(I.P.n), nbm = cg_nb(I.P.m);
-    const double r1 = slots_max(P.red, nbn, 4, 0);
+    const double r1 = slots_max(P.red, kRowSplit * nbn, 4, 0);
     const double r4 = slots_max(P.red + ipm_m0(I), nbm, 4, 0);
     const double sz = slots_sum(P.red + ipm_m0(I), nbm, 4, 1);
     if (threadIdx.x != 0) return;
@@ -3687,9 +3945,9 @@ hipError_t set_kernel_attributes() {
 
 static inline unsigned blocks_for(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
-void launch_aug_rhs(const InstDev* insts, const AugCall& A, const WorkItem* ncols, int nitems, int mode,
+void launch_aug_rhs(const InstDev* insts, const AugCall& A, const WorkItem* ncols, int nitems, int nlong, int mode,
                     hipStream_t st) {
-    if (nitems > 0) k_aug_rhs<<<nitems, kBlock, 0, st>>>(insts, A, ncols, mode);
+    if (nitems > 0) k_aug_rhs<<<nitems + (nlong + 15) / 16, kBlock, 0, st>>>(insts, A, ncols, nitems, mode);
 }
 void launch_aug_recover(const InstDev* insts, const AugCall& A, const WorkItem* ncols, int nn, const WorkItem* mrows,
                         int nm, int mode, hipStream_t st) {
@@ -3701,7 +3959,7 @@ void launch_aug_reset(const InstDev* insts, int ninst, double tol, int maxit, hi
 }
 void launch_aug_check(const InstDev* insts, const AugCall& A, const WorkItem* ncols, int nn, const WorkItem* mrows,
                       int nm, int ninst, hipStream_t st) {
-    if (nn > 0) k_aug_res_n<<<nn, kBlock, 0, st>>>(insts, A, ncols);
+    if (nn > 0) k_aug_res_n<<<nn * kRowSplit, kBlock, 0, st>>>(insts, A, ncols);
     if (nm > 0) k_aug_res_m<<<nm, kBlock, 0, st>>>(insts, A, mrows);
     if (ninst > 0) k_aug_decide<<<ninst, kBlock, 0, st>>>(insts);
 }
@@ -3721,7 +3979,7 @@ void launch_ipm_dsw(const InstDev* insts, const IpmCall& P, const WorkItem* mrow
 }
 void launch_ipm_residuals(const InstDev* insts, const IpmCall& P, const WorkItem* ncols, int nn, const WorkItem* mrows,
                           int nm, double delta, hipStream_t st) {
-    if (nn > 0) k_ipm_res_n<<<nn, kBlock, 0, st>>>(insts, P, ncols, delta);
+    if (nn > 0) k_ipm_res_n<<<nn * kRowSplit, kBlock, 0, st>>>(insts, P, ncols, delta);
     if (nm > 0) k_ipm_res_m<<<nm, kBlock, 0, st>>>(insts, P, mrows);
     k_ipm_decide<<<1, kBlock, 0, st>>>(insts, P, delta);
 }
@@ -3858,16 +4116,18 @@ void launch_refine_revert(const InstDev* insts, const Calls& C, const WorkItem* 
 void launch_matvec(const InstDev* insts, const double* x, double* y, const WorkItem* rows, int nitems, hipStream_t st) {
     if (nitems > 0) k_matvec<<<nitems, kBlock, 0, st>>>(insts, x, y, rows);
 }
-void launch_cg_fg(const InstDev* insts, const Calls& C, const WorkItem* ncols, int nitems, double tol, int maxit,
-                  double eta_tol, hipStream_t st) {
-    if (nitems > 0) k_cg_fg<<<nitems, kBlock, 0, st>>>(insts, C, ncols, tol, maxit, eta_tol);
+void launch_cg_fg(const InstDev* insts, const Calls& C, const WorkItem* ncols, int nitems, int nlong, double tol,
+                  int maxit, double eta_tol, hipStream_t st) {
+    if (nitems > 0) k_cg_fg<<<nitems + (nlong + 15) / 16, kBlock, 0, st>>>(insts, C, ncols, nitems, tol, maxit, eta_tol);
+    if (nitems > 0) k_cg_rows<<<nitems * kRowSplit, kBlock, 0, st>>>(insts, C, ncols);
 }
 void launch_cg_c(const InstDev* insts, const Calls& C, const WorkItem* mrows, int nitems, int ninst, hipStream_t st) {
     if (nitems > 0) k_cg_c<<<nitems, kBlock, 0, st>>>(insts, C, mrows);
     if (ninst > 0) k_cg_norms<<<ninst, kBlock, 0, st>>>(insts);
 }
-void launch_cg_dir(const InstDev* insts, const WorkItem* ncols, int nitems, int k, int* ndone, hipStream_t st) {
-    if (nitems > 0) k_cg_dir<<<nitems, kBlock, 0, st>>>(insts, ncols, k, ndone);
+void launch_cg_dir(const InstDev* insts, const WorkItem* ncols, int nitems, int nlong, int k, int* ndone,
+                   hipStream_t st) {
+    if (nitems > 0) k_cg_dir<<<nitems + (nlong + 15) / 16, kBlock, 0, st>>>(insts, ncols, nitems, k, ndone);
 }
 void launch_cg_eta_test(const InstDev* insts, const Calls& C, int ninst, int k, int* ndone, hipStream_t st) {
     if (ninst > 0) k_cg_eta_test<<<ninst, kBlock, 0, st>>>(insts, C, k, ndone);
@@ -3879,12 +4139,13 @@ void launch_cg_upd(const InstDev* insts, const Calls& C, const WorkItem* mrows, 
                    hipStream_t st) {
     if (nitems > 0) k_cg_upd<<<nitems, kBlock, 0, st>>>(insts, C, mrows, k, ndone);
 }
-void launch_cg_dxrhs(const InstDev* insts, const Calls& C, const WorkItem* ncols, int nitems, hipStream_t st) {
-    if (nitems > 0) k_cg_dxrhs<<<nitems, kBlock, 0, st>>>(insts, C, ncols);
+void launch_cg_dxrhs(const InstDev* insts, const Calls& C, const WorkItem* ncols, int nitems, int nlong,
+                     hipStream_t st) {
+    if (nitems > 0) k_cg_dxrhs<<<nitems + (nlong + 15) / 16, kBlock, 0, st>>>(insts, C, ncols, nitems);
 }
 void launch_cg_residual(const InstDev* insts, const Calls& C, const WorkItem* ncols, int nn, const WorkItem* mrows,
                         int nm, int ninst, hipStream_t st) {
-    if (nn > 0) k_cg_res_n<<<nn, kBlock, 0, st>>>(insts, C, ncols);
+    if (nn > 0) k_cg_res_n<<<nn * kRowSplit, kBlock, 0, st>>>(insts, C, ncols);
     if (nm > 0) k_cg_res_m<<<nm, kBlock, 0, st>>>(insts, C, mrows);
     if (ninst > 0) k_cg_eta<<<ninst, kBlock, 0, st>>>(insts);
 }

@@ -32,7 +32,9 @@ constexpr int kBlock = 256;
 constexpr int kSplitMaxFronts = 140;  // levels with fewer fronts launch their update matrices by tiles
 constexpr int kSplitMinRows = 64;     // ... when the level's widest update part has at least this many rows
 constexpr int kResidualSplit = 8;    // residual blocks per 256-row item (two rows per 16-lane group)
-static_assert(16 % kResidualSplit == 0, "a 256-row item splits into whole rows per 16-lane group");
+constexpr int kRowSplit = 8;         // the same for the CG, augmented and interior-point row kernels, whose
+                                     // reductions keep one record per part of an item
+static_assert(16 % kResidualSplit == 0 && 16 % kRowSplit == 0, "a 256-row item splits into whole rows per 16-lane group");
 
 // Dependency lists of a persistent (queue-scheduled) launch over the fronts
 // in topological order: parent item (-1 for roots), number of children, and
@@ -137,15 +139,19 @@ void launch_refine_revert(const InstDev* insts, const Calls& C, const WorkItem* 
 void launch_matvec(const InstDev* insts, const double* x, double* y, const WorkItem* rows, int nitems, hipStream_t st);
 
 // Schur-complement CG (one CgState per instance); k is the iteration index
-void launch_cg_fg(const InstDev* insts, const Calls& C, const WorkItem* ncols, int nitems, double tol, int maxit,
-                  double eta_tol, hipStream_t st);
+// (nlong: columns of J listed in PatDev::jtp_long, taken by workgroups of their
+// own behind the row blocks; single instances)
+void launch_cg_fg(const InstDev* insts, const Calls& C, const WorkItem* ncols, int nitems, int nlong, double tol,
+                  int maxit, double eta_tol, hipStream_t st);
 void launch_cg_c(const InstDev* insts, const Calls& C, const WorkItem* mrows, int nitems, int ninst, hipStream_t st);
-void launch_cg_dir(const InstDev* insts, const WorkItem* ncols, int nitems, int k, int* ndone, hipStream_t st);
+void launch_cg_dir(const InstDev* insts, const WorkItem* ncols, int nitems, int nlong, int k, int* ndone,
+                   hipStream_t st);
 void launch_cg_eta_test(const InstDev* insts, const Calls& C, int ninst, int k, int* ndone, hipStream_t st);
 void launch_cg_q(const InstDev* insts, const Calls& C, const WorkItem* mrows, int nitems, int k, hipStream_t st);
 void launch_cg_upd(const InstDev* insts, const Calls& C, const WorkItem* mrows, int nitems, int k, int* ndone,
                    hipStream_t st);
-void launch_cg_dxrhs(const InstDev* insts, const Calls& C, const WorkItem* ncols, int nitems, hipStream_t st);
+void launch_cg_dxrhs(const InstDev* insts, const Calls& C, const WorkItem* ncols, int nitems, int nlong,
+                     hipStream_t st);
 // saddle-system residual of (dx, dy) and its normwise backward error (CgState::eta)
 void launch_cg_residual(const InstDev* insts, const Calls& C, const WorkItem* ncols, int nn, const WorkItem* mrows,
                         int nm, int ninst, hipStream_t st);
@@ -162,7 +168,7 @@ struct AugCall {
 };
 // mode 0: b = -(r1 + J^T (Sigma_s r4 - r2)); mode 1: the same with -r = e,
 // the current residual (correction right-hand side)
-void launch_aug_rhs(const InstDev* insts, const AugCall& A, const WorkItem* ncols, int nitems, int mode,
+void launch_aug_rhs(const InstDev* insts, const AugCall& A, const WorkItem* ncols, int nitems, int nlong, int mode,
                     hipStream_t st);
 // mode 0: ds = -r4 - J dx, dz = -r2 - Sigma_s ds; mode 1: the correction from
 // t = K^{-1} b (in aug_t): the previous iterate is kept, then dx += t,
