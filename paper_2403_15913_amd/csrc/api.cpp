@@ -258,7 +258,8 @@ kkt_status Engine::place(const std::vector<const Symbolic*>& s, const std::vecto
                 n_large++;
             } else {
                 lds_factor = std::max(lds_factor, (size_t)factor_launch_lds_bytes(S.sn_nrow[k], S.sn_ncol[k]));
-                lds_solve = std::max(lds_solve, (size_t)solve_lds_bytes(S.sn_nrow[k], S.sn_ncol[k]));
+                const int r = S.sn_nrow[k], c = S.sn_ncol[k];
+                lds_solve = std::max({lds_solve, (size_t)fwd_lds_bytes(r, c), (size_t)bwd_lds_bytes(r, c)});
             }
             const size_t nbu = (size_t)(S.sn_nrow[k] - S.sn_ncol[k] + 15) / 16;
             nup += nbu * (nbu + 1) / 2;
@@ -270,13 +271,14 @@ kkt_status Engine::place(const std::vector<const Symbolic*>& s, const std::vecto
         nkb += (S.nnzk + kBlock - 1) / kBlock;
         njb += (S.nnz_j + kBlock - 1) / kBlock;
     }
-    if (lds_factor > (size_t)kMaxDynLds || lds_solve > (size_t)kMaxDynLds)
+    if (lds_factor > (size_t)kMaxDynLds || lds_solve > (size_t)kMaxSweepLds)
         return fail(KKT_ERR_PATTERN, "a front exceeds the per-workgroup LDS budget");
     const size_t N = (size_t)n_ofs[ninst], M = (size_t)m_ofs[ninst];
     Carver cv(mem, cap);
     // the stage-structured solver uses the engine for assembly and refinement
     // only: no supernode panels, update matrices or vectors
-    L = cv.take<double>(assembly_only ? 0 : lo[ninst]);
+    // two doubles of padding: the sweeps read rows in pairs
+    L = cv.take<double>(assembly_only ? 0 : lo[ninst] + 2);
     U = cv.take<double>(assembly_only ? 0 : uo[ninst]);
     V = cv.take<double>(assembly_only ? 0 : vo[ninst]);
     kval = cv.take<double>(ko[ninst]);
@@ -381,6 +383,8 @@ kkt_status Engine::place(const std::vector<const Symbolic*>& s, const std::vecto
     lvl_ptr.assign(1, 0);
     lvl_large.clear();
     sw_part.clear();
+    sw_maxr = 0;
+    sw_maxlds = 0;
     sw_lvl.assign(1, 0);
     for (int l = 0; l < nlev; l++) {
         for (int q = 0; q < ninst; q++) {
@@ -388,43 +392,31 @@ kkt_status Engine::place(const std::vector<const Symbolic*>& s, const std::vecto
             if (l >= S.nlevels) continue;
             for (int t = S.lvl_ptr[l]; t < S.lvl_ptr[l + 1]; t++) sn.push_back(WorkItem{q, S.lvl_list[t]});
         }
-        // Each sweep launch takes the LDS of its own largest front, so a level
-        // of small fronts runs two workgroups per compute unit. Fronts of one
-        // level are independent and their order in the launch is free: where
-        // the small fronts alone fill two workgroups on every compute unit,
-        // they get a launch of their own after the larger fronts' (launches
-        // on one stream run one after the other, so a split pays only for
-        // wide levels).
         const int b0 = lvl_ptr.back();
         // large fronts last in the level (their own launches)
         const int bl = (int)(std::stable_partition(sn.begin() + b0, sn.end(),
                                                    [&](const WorkItem& w) { return !is_large(*s[w.inst], w.id); }) -
                              sn.begin());
         lvl_large.push_back(bl);
-        auto slds = [&](const WorkItem& w) {
-            const Symbolic& S = *s[w.inst];
-            return (size_t)solve_lds_bytes(S.sn_nrow[w.id], S.sn_ncol[w.id]);
+        // the level's sweep launches take the LDS of its largest front;
+        // largest fronts first (also in the factor launch), so the small
+        // ones fill the last round
+        auto by_size = [&](const WorkItem& a, const WorkItem& b) {
+            const Symbolic &A = *s[a.inst], &B = *s[b.inst];
+            return solve_lds_bytes(A.sn_nrow[a.id], A.sn_ncol[a.id]) > solve_lds_bytes(B.sn_nrow[b.id], B.sn_ncol[b.id]);
         };
-        int nsmall = 0;
-        for (int t = b0; t < bl; t++) nsmall += slds(sn[t]) <= kSweepHalfLds;
-        int b1 = b0;
-        if (nsmall >= kSweepSplitMin && nsmall < bl - b0)
-            b1 = (int)(std::stable_partition(sn.begin() + b0, sn.begin() + bl,
-                                             [&](const WorkItem& w) { return slds(w) > kSweepHalfLds; }) -
-                       sn.begin());
-        const int b2 = bl;
-        // largest fronts first in each launch (and in the level's factor
-        // launch), so the small ones fill the last round
-        auto by_size = [&](const WorkItem& a, const WorkItem& b) { return slds(a) > slds(b); };
-        std::stable_sort(sn.begin() + b0, sn.begin() + b1, by_size);
-        std::stable_sort(sn.begin() + b1, sn.begin() + b2, by_size);
-        for (int c = 0; c < 2; c++) {
-            const int lo_i = c ? b1 : b0, hi_i = c ? b2 : b1;
-            if (hi_i == lo_i) continue;
-            size_t mx = 0;
-            for (int t = lo_i; t < hi_i; t++) mx = std::max(mx, slds(sn[t]));
-            sw_part.push_back(SweepPart{lo_i, hi_i - lo_i, mx});
+        std::stable_sort(sn.begin() + b0, sn.begin() + bl, by_size);
+        SweepPart part{b0, bl - b0, 0, 0, 0};
+        for (int t = b0; t < bl; t++) {
+            const Symbolic& S = *s[sn[t].inst];
+            const int r = S.sn_nrow[sn[t].id], c = S.sn_ncol[sn[t].id];
+            part.maxr = std::max(part.maxr, r);
+            part.lds_fwd = std::max(part.lds_fwd, (size_t)fwd_lds_bytes(r, c));
+            part.lds_bwd = std::max(part.lds_bwd, (size_t)bwd_lds_bytes(r, c));
         }
+        if (part.count > 0) sw_part.push_back(part);
+        sw_maxr = std::max(sw_maxr, part.maxr);
+        sw_maxlds = std::max(sw_maxlds, part.lds_bwd);
         sw_lvl.push_back((int)sw_part.size());
         lvl_ptr.push_back((int)sn.size());
     }
@@ -697,7 +689,13 @@ void Engine::sweeps(hipStream_t st, int skip_done) {
     for (int l = 0; l < nl; l++) {
         for (int k = sw_lvl[l]; k < sw_lvl[l + 1]; k++) {
             const SweepPart& P = sw_part[k];
-            TL(KKT_PHASE_FWD, launch_fwd(di(), fdesc + P.begin, P.count, P.lds, skip_done, st));
+            // one wave per front where a level's fronts have at most 128 rows
+            // and either no front is taller or the level fills the chip: a
+            // second form of the kernel for a level of a few fronts costs more
+            // (its code is fetched anew: 11 us for the 66-row root, 5.3 us by
+            // two waves) than the spare wave
+            const bool narrow = P.maxr <= 128 && (sw_maxr <= 128 || P.count >= 512);
+            TL(KKT_PHASE_FWD, launch_fwd(di(), fdesc + P.begin, P.count, P.maxr, narrow, P.lds_fwd, skip_done, st));
         }
         if (lvl_large[l] < lvl_ptr[l + 1])
             TL(KKT_PHASE_FWD, launch_big_fwd(di(), fdesc + lvl_large[l], lvl_ptr[l + 1] - lvl_large[l], skip_done, st));
@@ -707,7 +705,9 @@ void Engine::sweeps(hipStream_t st, int skip_done) {
             TL(KKT_PHASE_BWD, launch_big_bwd(fdesc + lvl_large[l], lvl_ptr[l + 1] - lvl_large[l], skip_done, st));
         for (int k = sw_lvl[l]; k < sw_lvl[l + 1]; k++) {
             const SweepPart& P = sw_part[k];
-            TL(KKT_PHASE_BWD, launch_bwd(fdesc + P.begin, P.count, P.lds, skip_done, st));
+            // (chosen as in the forward sweep: one form for the levels of few fronts)
+            const bool light = P.lds_bwd <= kSweepHalfLds && (sw_maxlds <= kSweepHalfLds || P.count >= 512);
+            TL(KKT_PHASE_BWD, launch_bwd(fdesc + P.begin, P.count, light, P.lds_bwd, skip_done, st));
         }
     }
 }

@@ -130,8 +130,10 @@ struct Engine {
     std::vector<int> lvl_ptr;
     // sweep launches: each level split into LDS size classes (small fronts
     // first), parts sw_lvl[l] .. sw_lvl[l + 1] of sw_part
-    struct SweepPart { int begin, count; size_t lds; };
+    struct SweepPart { int begin, count, maxr; size_t lds_fwd, lds_bwd; };
     std::vector<SweepPart> sw_part;
+    int sw_maxr = 0;       // tallest front of the sweep launches,
+    size_t sw_maxlds = 0;  //   largest LDS of a backward step
     std::vector<int> sw_lvl;
     int n_nitems = 0, n_mitems = 0, n_kitems = 0, n_jitems = 0, n_hitems = 0;
     size_t lds_factor = 0, lds_solve = 0;

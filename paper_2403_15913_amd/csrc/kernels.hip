@@ -26,9 +26,6 @@
 
 namespace kkt {
 
-#ifndef KKT_BWD_SMALL_PU
-#define KKT_BWD_SMALL_PU 16
-#endif
 #ifndef KKT_SMALL_WAVES_PER_EU
 #define KKT_SMALL_WAVES_PER_EU 3
 #endif
@@ -1570,122 +1567,82 @@ __global__ __launch_bounds__(kFactorQueueThreads) void k_factor_queue(const Inst
 }
 
 // ---------------------------------------------------------------------------
-// triangular solve with the c x c diagonal triangle of a staged panel, by
-// one wave (c <= 128): lane l carries rows l and l + 64 in x0 and x1, dv
-// holds the pivot reciprocals. Blocks of 16 columns: the block's own
-// triangle is read into registers first, so its 16 dependent steps are
-// register FMAs with row broadcasts; the rows outside the block then take
-// the block's contribution with all their LDS loads issued together.
-// Each row's terms are subtracted in the same order as plain substitution.
-// ---------------------------------------------------------------------------
-// L11^T x = t (backward), blocks from the last one down
-__device__ inline void tri_bwd_wave(const double* __restrict__ P, int ld, int c, const double* __restrict__ dv,
-                                    double& x0, double& x1, int lane) {
-    for (int j0 = (c - 1) & ~15; j0 >= 0; j0 -= 16) {
-        const int nb = min(16, c - j0);
-        const bool hi = j0 >= 64;
-        const int rb = lane - (j0 & 63);
-        const bool inblk = rb >= 0 && rb < nb;
-        const int rbc = min(max(rb, 0), nb - 1);
-        // Lc[k] = L[j0 + k][j0 + rb] for k > rb (row k of the block, this lane's column)
-        double Lc[16];
-        const double* colr = P + (j0 + rbc) * ld + j0;
-#pragma unroll
-        for (int k = 0; k < 16; k++) Lc[k] = colr[min(k, nb - 1)];
-#pragma unroll
-        for (int k = 0; k < 16; k++) Lc[k] = (inblk && k > rb && k < nb) ? Lc[k] : 0.0;
-        const double d = dv[j0 + rbc];
-        double tb = hi ? x1 : x0;
-        // the chain runs inside the block's 16-lane row: step k takes lane
-        // k's value by a row broadcast (lanes of the row past the block
-        // hold zeros and have zero coefficients; other rows' results are
-        // discarded)
-        static_for<16>([&](auto K) {
-            constexpr int k = 15 - decltype(K)::value;
-            tb = fma(-Lc[k], row_bcast<k>(tb * d), tb);
-        });
-        const double xv = tb * d;
-        if (inblk) {
-            if (hi) x1 = xv;
-            else x0 = xv;
-        }
-        // the block's values for the rows above it, from every lane
-        double x[16];
-#pragma unroll
-        for (int k = 0; k < 16; k++) x[k] = j0 > 0 ? readlane_d(xv, (j0 & 63) + k) : 0.0;
-        if (j0 > 0) {  // rows 0 .. j0-1 lie above the block
-            const int i0 = min(lane, j0 - 1), i1 = min(lane + 64, j0 - 1);
-            double a0[16], a1[16];
-#pragma unroll
-            for (int k = 0; k < 16; k++) {
-                const int kr = j0 + min(k, nb - 1);
-                a0[k] = P[i0 * ld + kr];
-                a1[k] = P[i1 * ld + kr];
-            }
-            double s0 = x0, s1 = x1;
-#pragma unroll
-            for (int k = 15; k >= 0; k--) {
-                s0 = fma(-a0[k], x[k], s0);
-                s1 = fma(-a1[k], x[k], s1);
-            }
-            if (lane < j0) x0 = s0;
-            if (lane + 64 < j0) x1 = s1;
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
 // triangular sweeps (y holds the permuted right-hand side, then the solution)
 // ---------------------------------------------------------------------------
-// The panel is staged in LDS (odd leading dimension); the c x c triangle is
-// solved by one wave in 16-column blocks (each block's 16-step chain by
-// DPP row broadcasts), the rectangular part by all threads. Reciprocals of
-// the pivots come from the factorisation.
 constexpr int kSolveThreads = 256;
 static_assert(kSolveThreads == 256, "the sweep work splits assume 256 threads");
 
-__device__ __forceinline__ void fwd_front(const InstDev& I, const FrontDesc& F, double* __restrict__ sh) {
-    const PatDev& T = I.P;
+// skip modes of the sweeps: SKIP_NONE runs every front; SKIP_REFINE skips
+// the fronts of instances whose refinement has stopped, SKIP_CG those whose
+// CG has stopped (the queued rounds after a stop decision do nothing)
+__device__ __forceinline__ bool front_idle(const FrontDesc& F, int skip) {
+    return skip == SKIP_REFINE ? *F.done != 0 : (skip == SKIP_CG ? *F.cgdone != 0 : false);
+}
+
+extern "C" __device__ int kkt_writelane(int v, int lane, int old) __asm("llvm.amdgcn.writelane.i32");
+__device__ __forceinline__ double writelane_d(double v, int lane, double old) {
+    const long long b = __double_as_longlong(v), o = __double_as_longlong(old);
+    const int lo = kkt_writelane((int)b, lane, (int)o), hi = kkt_writelane((int)(b >> 32), lane, (int)(o >> 32));
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// two neighbouring rows of a panel column (8-byte aligned; one 16-byte load).
+// The address unit takes about 16 cycles per load instruction of a wave
+// whatever its width (measured, one workgroup: a panel of 66 x 199 in 5,000
+// cycles by 8-byte loads, 2,900 by 16-byte loads of row pairs).
+typedef double rows2 __attribute__((ext_vector_type(2), aligned(8)));
+
+__device__ __forceinline__ rows2 rows_at(const double* col, unsigned row) {
+    return *(const rows2*)((const char*)col + 8u * row);
+}
+
+// Substitution by the wave that owns the pivot rows (lane l: rows 2 l and
+// 2 l + 1, values acc0 and acc1): every lane takes its terms with the pivot
+// lane's value as a scalar, so one multiply, two lane reads and two FMAs per
+// column solve the column and update all 128 rows (about 50 cycles; a chain
+// inside 16 lanes by DPP broadcasts costs as much and leaves the other rows'
+// updates to be done). The solved values are collected in y0 and y1; sums of
+// rows at and above a solved pivot are no longer meaningful. Four columns from K0
+// on, of a block of nb (TAIL: fewer than four are left).
+template <int K0, bool TAIL>
+__device__ __forceinline__ void fwd_steps(double& acc0, double& acc1, double& y0, double& y1, const rows2 (&a)[16],
+                                          const double d0, const double d1, const int l0, const int nb) {
+    static_for<4>([&](auto K) {
+        constexpr int k = K0 + K;
+        const int l = l0 + (k >> 1);
+        double v = readlane_d((k & 1) ? acc1 * d1 : acc0 * d0, l);
+        if (TAIL) v = k < nb ? v : 0.0;
+        if constexpr ((k & 1) != 0) y1 = writelane_d(v, l, y1);
+        else y0 = writelane_d(v, l, y0);
+        acc0 = fma(-a[k].x, v, acc0);
+        acc1 = fma(-a[k].y, v, acc1);
+    });
+}
+
+// Forward step of one front by NTH threads: thread t holds rows 2 t and
+// 2 t + 1, their panel entries in registers, three blocks of 16 columns in
+// flight (loaded as the panel lies in HBM: no LDS staging, and only vectors in
+// LDS, so the registers alone limit the fronts per compute unit). Levels of
+// few fronts are bound by one wave's chain and the load latency (a 66 x 198
+// front: loads and children's sums 4,700 cycles, columns 52 cycles each; with
+// the panel staged in LDS and 16-lane chains 19,000 in all, 10.4 -> 6.0 us a
+// launch), the leaf levels by HBM (512 fronts of 79 x 227: 26.9 -> 22.5 us).
+template <int NTH, int NBLK>
+__device__ __forceinline__ void fwd_body(const InstDev* __restrict__ insts, const FrontDesc& F,
+                                         double* __restrict__ sh) {
+    constexpr int VU = kSolveThreads / NTH, NR = NBLK < 3 ? NBLK : 3;
     const int c = F.c, r = F.r;
-    const int u = r - c;
     const int ld = r | 1;
-    const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63;
-    double* P = sh;
-    double* w = sh + even_up(ld * c);
-    double* va = w + c;
-    double* dv = va + u;
-    // The panel is staged one 16-column block at a time: block b is one
-    // contiguous range of 8 ld double2 in HBM and in LDS. Block 0 comes
-    // with the prologue; block kb+1 is loaded into registers while phase
-    // kb computes and stored before the phase's barrier. Every load of the
-    // prologue is issued before the first wait: panel block 0, the
-    // right-hand side and pivot reciprocals of the front's columns
-    // (c <= 128 < threads), and the first entries of the first two
-    // children's update vectors with their relative indices.
-    constexpr int BU = 8;  // double2 per thread and block in registers (ld < 256)
-    const double2* __restrict__ s2 = (const double2*)(const double*)F.L;
-    double2* d2 = (double2*)P;
-    const int n2 = even_up(ld * c) >> 1;
-    const int bw2 = 8 * ld;
-    double2 pb[BU];
-    auto blk_load = [&](const int bk) {
-        const int q0 = bk * bw2, q1 = min(q0 + bw2, n2);
-#pragma unroll
-        for (int k = 0; k < BU; k++) pb[k] = s2[min(q0 + tid + k * nt, q1 - 1)];
-    };
-    auto blk_store = [&](const int bk) {
-        const int q0 = bk * bw2, q1 = min(q0 + bw2, n2);
-#pragma unroll
-        for (int k = 0; k < BU; k++) pin(pb[k]);
-#pragma unroll
-        for (int k = 0; k < BU; k++)
-            if (q0 + tid + k * nt < q1) d2[q0 + tid + k * nt] = pb[k];
-        for (int q = q0 + tid + BU * nt; q < q1; q += nt) d2[q] = s2[q];
-    };
-    const int nblk = (c + 15) >> 4;
-    blk_load(0);
-    const int tc = min(tid, c - 1);
-    double wy = F.y[tc], wd = F.dinv[tc];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int cp = rup16(c), re = even_up(r);
+    double* const ys = sh;       // solved values, zero past c
+    double* const s0 = ys + cp;  // the two children's update vectors by row
+    double* const s1 = s0 + re;
+    double* const ex = s1 + re;  // rows past the threads
+    const int row = 2 * tid, rc = min(row, (r - 1) & ~1);
+    // loads before the first wait: the first entries of the first two
+    // children's update vectors, the right-hand side and pivot reciprocals,
+    // and 32 columns of the thread's rows
     const int ch0 = F.ch0, nch = F.nch, ch1 = ch0 + nch;
     struct VChild {
         const double* Vc;
@@ -1701,6 +1658,8 @@ __device__ __forceinline__ void fwd_front(const InstDev& I, const FrontDesc& F, 
             C.Vc = k ? F.cV[1] : F.cV[0];
             C.rl = k ? F.crl[1] : F.crl[0];
         } else {
+            const InstDev& I = insts[F.inst];
+            const PatDev& T = I.P;
             const int ch = __builtin_amdgcn_readfirstlane(T.ch_list[q]);
             const int cc = __builtin_amdgcn_readfirstlane(T.sn_ncol[ch]);
             C.uc = __builtin_amdgcn_readfirstlane(T.sn_nrow[ch]) - cc;
@@ -1710,128 +1669,248 @@ __device__ __forceinline__ void fwd_front(const InstDev& I, const FrontDesc& F, 
         return C;
     };
     VChild V0 = {}, V1 = {};
-    double v0 = 0.0, v1 = 0.0;
-    int r0 = 0, r1 = 0;
+    double v0[VU], v1[VU];
+    int r0[VU], r1[VU];
     if (nch > 0) {
         V0 = vchild(ch0);
-        const int a = min(tid, V0.uc - 1);
-        v0 = V0.Vc[a];
-        r0 = V0.rl[a];
+#pragma unroll
+        for (int h = 0; h < VU; h++) {
+            const int a = min(tid + h * NTH, V0.uc - 1);
+            v0[h] = V0.Vc[a];
+            r0[h] = V0.rl[a];
+        }
     }
     if (nch > 1) {
         V1 = vchild(ch0 + 1);
-        const int a = min(tid, V1.uc - 1);
-        v1 = V1.Vc[a];
-        r1 = V1.rl[a];
-    }
-    pin(wy);
-    pin(wd);
-    pin(v0);
-    pin(v1);
-    pin(r0);
-    pin(r1);
-    blk_store(0);
-    if (tid < c) {
-        w[tid] = wy;
-        dv[tid] = wd;
-    }
-    for (int t = tid; t < u; t += nt) va[t] = 0.0;
-    __syncthreads();
-    if (nblk > 1) blk_load(1);
-    // children's update vectors, child by child (entries of one child are
-    // distinct; two children can add into the same entry)
-    auto add_child = [&](const VChild& C, const bool pre, const double vp, const int rp) {
-        for (int a = tid; a < C.uc; a += nt) {
-            const bool first = pre && a == tid;
-            const int ra = first ? rp : C.rl[a];
-            const double v = first ? vp : C.Vc[a];
-            if (ra < c) w[ra] += v;
-            else va[ra - c] += v;
+#pragma unroll
+        for (int h = 0; h < VU; h++) {
+            const int a = min(tid + h * NTH, V1.uc - 1);
+            v1[h] = V1.Vc[a];
+            r1[h] = V1.rl[a];
         }
-        __syncthreads();
+    }
+    double w0 = 0.0, w1 = 0.0, d0 = 0.0, d1 = 0.0;
+    if (wave == 0) {
+        const int i0 = min(row, c - 1), i1 = min(row + 1, c - 1);
+        w0 = F.y[i0];
+        w1 = F.y[i1];
+        d0 = F.dinv[i0];
+        d1 = F.dinv[i1];
+    }
+    const bool live = 128 * wave < r;
+    const double* const Pl = F.L;
+    rows2 a[NR][16];
+    // (no load depends on a branch, so every wait counts exactly; columns
+    // past the last are read from the last)
+    auto load = [&](auto B) {
+#pragma unroll
+        for (int k = 0; k < 16; k++)
+            a[B % NR][k] = rows_at(Pl + (B + 1 < NBLK ? 16 * B + k : min(16 * B + k, c - 1)) * ld, rc);
     };
-    if (nch > 0) add_child(V0, true, v0, r0);
-    if (nch > 1) add_child(V1, true, v1, r1);
-    for (int q = ch0 + 2; q < ch1; q++) add_child(vchild(q), false, 0.0, 0);
-    // L11 y = w and the update rows' GEMV, pipelined by 16-column blocks.
-    // Phase kb: wave 0 takes block kb-1's contribution into block kb's
-    // rows, then solves block kb (its triangle in registers, row
-    // broadcasts); meanwhile the other waves take block kb-1's contribution
-    // into every later row (triangle rows past block kb and the update
-    // rows). Every row subtracts its terms in ascending column order.
-    const int wave = tid >> 6;
-    for (int kb = 0; kb <= nblk; kb++) {
-        const int p0 = (kb - 1) << 4, nprev = min(16, c - p0);
-        if (wave == 0 && kb < nblk) {
-            const int j0 = kb << 4, nbk = min(16, c - j0);
-            const bool inb = lane < nbk;
-            const int row = j0 + min(lane, nbk - 1);
-            double wb = w[row];
-            if (kb > 0) {
-                double a[16], yv[16];
+    static_for<(NR < 2 ? NR : 2)>([&](auto B) { load(B); });
+    double acc0 = row < c ? w0 : 0.0, acc1 = row + 1 < c ? w1 : 0.0;
+    if (nch > 0) {
+        for (int i = tid; i < re; i += NTH) s0[i] = s1[i] = 0.0;
+        __syncthreads();
 #pragma unroll
-                for (int j = 0; j < 16; j++) {
-                    a[j] = P[(p0 + j) * ld + row];
-                    yv[j] = w[p0 + j];
-                }
+        for (int h = 0; h < VU; h++)
+            if (tid + h * NTH < V0.uc) s0[r0[h]] = v0[h];
+        for (int q = tid + VU * NTH; q < V0.uc; q += NTH) s0[V0.rl[q]] = V0.Vc[q];
 #pragma unroll
-                for (int j = 0; j < 16; j++) wb = fma(-a[j], yv[j], wb);
+        for (int h = 0; h < VU; h++)
+            if (tid + h * NTH < V1.uc) s1[r1[h]] = v1[h];
+        for (int q = tid + VU * NTH; q < V1.uc; q += NTH) s1[V1.rl[q]] = V1.Vc[q];
+        __syncthreads();
+        acc0 = (acc0 + s0[rc]) + s1[rc];
+        acc1 = (acc1 + s0[rc + 1]) + s1[rc + 1];
+        for (int i = tid + 2 * NTH; i < r; i += NTH) ex[i - 2 * NTH] = s0[i] + s1[i];
+        for (int q = ch0 + 2; q < ch1; q += 2) {  // in the children's order, two at a time
+            __syncthreads();
+            for (int i = tid; i < re; i += NTH) s0[i] = s1[i] = 0.0;
+            __syncthreads();
+            const VChild A = vchild(q);
+            for (int e = tid; e < A.uc; e += NTH) s0[A.rl[e]] = A.Vc[e];
+            if (q + 1 < ch1) {
+                const VChild B = vchild(q + 1);
+                for (int e = tid; e < B.uc; e += NTH) s1[B.rl[e]] = B.Vc[e];
             }
-            double Lr[16];
-#pragma unroll
-            for (int k = 0; k < 16; k++) Lr[k] = P[min(j0 + k, c - 1) * ld + row];
-#pragma unroll
-            for (int k = 0; k < 16; k++) Lr[k] = (inb && k < lane) ? Lr[k] : 0.0;
-            const double d = dv[row];
-            // lanes 0-15 hold the block's rows; step k takes lane k's value
-            // by a row broadcast (coefficients past the block are zero)
-            static_for<16>([&](auto K) {
-                constexpr int k = K;
-                wb = fma(-Lr[k], row_bcast<k>(wb * d), wb);
+            __syncthreads();
+            acc0 = (acc0 + s0[rc]) + s1[rc];
+            acc1 = (acc1 + s0[rc + 1]) + s1[rc + 1];
+            for (int i = tid + 2 * NTH; i < r; i += NTH)
+                ex[i - 2 * NTH] = (ex[i - 2 * NTH] + s0[i]) + s1[i];
+        }
+    } else {
+        for (int i = tid + 2 * NTH; i < r; i += NTH) ex[i - 2 * NTH] = 0.0;
+    }
+    if constexpr (NR > 2) load(std::integral_constant<int, 2>{});
+    // L11 y = w and the update rows, 16 columns at a time: the first wave
+    // solves the columns (its own rows, at most 128 of them pivots, take
+    // their terms in the same steps), the other waves take the solved values
+    // one block behind. Every row subtracts its terms in ascending column
+    // order.
+    double y0 = 0.0, y1 = 0.0;
+    static_for<NBLK>([&](auto B) {
+        constexpr int j0 = 16 * B, l0 = 8 * B;
+        const int nb = c - j0;
+        if (wave == 0) {
+            static_for<4>([&](auto Q) {
+                if (B + 1 < NBLK || nb >= 4 * Q + 4)
+                    fwd_steps<4 * Q, false>(acc0, acc1, y0, y1, a[B % NR], d0, d1, l0, nb);
+                else if (nb > 4 * Q)
+                    fwd_steps<4 * Q, true>(acc0, acc1, y0, y1, a[B % NR], d0, d1, l0, nb);
             });
-            if (inb) w[j0 + lane] = wb * d;
-        } else if (kb > 0) {
-            // rows after block kb: triangle rows, then the update rows
-            const int r1 = min(c, (kb + 1) << 4), ntr = c - r1;
-            const int t0 = kb < nblk ? tid - 64 : tid, ts = kb < nblk ? nt - 64 : nt;
-            double yv[16];
-#pragma unroll
-            for (int j = 0; j < 16; j++) yv[j] = j < nprev ? w[p0 + j] : 0.0;
-            for (int q = t0; q < ntr + u; q += ts) {
-                const int prow = q < ntr ? r1 + q : c + (q - ntr);
-                double a[16];
-#pragma unroll
-                for (int j = 0; j < 16; j++) a[j] = P[(p0 + min(j, nprev - 1)) * ld + prow];
-                double acc = q < ntr ? w[prow] : va[q - ntr];
-#pragma unroll
-                for (int j = 0; j < 16; j++) acc = fma(-a[j], yv[j], acc);
-                if (q < ntr) w[prow] = acc;
-                else va[q - ntr] = acc;
+            if (lane >= l0 && lane < l0 + 8) {
+                ys[row] = y0;
+                ys[row + 1] = y1;
             }
         }
-        if (kb + 1 < nblk) blk_store(kb + 1);
         __syncthreads();
-        if (kb + 2 < nblk) blk_load(kb + 2);
+        if (wave > 0 && live) {
+            double y[16];
+#pragma unroll
+            for (int k = 0; k < 16; k++) y[k] = ys[j0 + k];
+#pragma unroll
+            for (int k = 0; k < 16; k++) {
+                acc0 = fma(-a[B % NR][k].x, y[k], acc0);
+                acc1 = fma(-a[B % NR][k].y, y[k], acc1);
+            }
+        }
+        if constexpr (B + NR < NBLK) load(std::integral_constant<int, B + NR>{});
+    });
+    double* const Vs = F.V;
+    if (row < c) F.y[row] = y0;
+    else if (row < r) Vs[row - c] = acc0;
+    if (row + 1 < c) F.y[row + 1] = y1;
+    else if (row + 1 < r) Vs[row + 1 - c] = acc1;
+    for (int i = tid + 2 * NTH; i < r; i += NTH) {
+        double s = ex[i - 2 * NTH];
+        for (int j = 0; j < c; j += 8) {
+            double b[8];
+#pragma unroll
+            for (int k = 0; k < 8; k++) b[k] = Pl[min(j + k, c - 1) * ld + i];
+#pragma unroll
+            for (int k = 0; k < 8; k++) s = fma(-b[k], ys[j + k], s);
+        }
+        Vs[i - c] = s;
     }
-    double* __restrict__ Vs = F.V;
-    for (int i = tid; i < u; i += nt) Vs[i] = va[i];
-    for (int t = tid; t < c; t += nt) F.y[t] = w[t];
 }
 
-// PU: 16-byte panel loads per thread in flight while staging (fewer for
-// small panels keeps the registers low enough for more fronts per compute
-// unit; the arithmetic does not depend on it)
-template <int PU = 32>
+// one body per number of column blocks (c <= 128)
+template <int NTH>
+__device__ __forceinline__ void fwd_front(const InstDev* __restrict__ insts, const FrontDesc& F, const int skip_done,
+                                          double* __restrict__ sh) {
+    if (front_idle(F, skip_done)) return;
+    switch ((F.c + 15) >> 4) {
+        case 1: return fwd_body<NTH, 1>(insts, F, sh);
+        case 2: return fwd_body<NTH, 2>(insts, F, sh);
+        case 3: return fwd_body<NTH, 3>(insts, F, sh);
+        case 4: return fwd_body<NTH, 4>(insts, F, sh);
+        case 5: return fwd_body<NTH, 5>(insts, F, sh);
+        case 6: return fwd_body<NTH, 6>(insts, F, sh);
+        case 7: return fwd_body<NTH, 7>(insts, F, sh);
+        default: return fwd_body<NTH, 8>(insts, F, sh);
+    }
+}
+
+// Columns k0 + 3 down to k0 of a 16-column block by one wave (lane l0 + k of x
+// holds column k; TAIL: the block has nb < k0 + 4). o collects the solution,
+// xl the terms of the columns 64 to the left (HI).
+template <int K0, bool TAIL, bool HI>
+__device__ __forceinline__ void bwd_steps(double& x, double& xl, double& o, const double (&a)[16],
+                                          const double (&al)[16], const double d, const int l0, const int nb) {
+    static_for<4>([&](auto K) {
+        constexpr int k = K0 + 3 - decltype(K)::value;
+        double v = readlane_d(x * d, l0 + k);
+        if (TAIL) v = k < nb ? v : 0.0;
+        o = writelane_d(v, l0 + k, o);
+        x = fma(-a[k], v, x);
+        if constexpr (HI) xl = fma(-al[k], v, xl);
+    });
+}
+
+// L11^T x = t by one wave, from the last column down (c <= 128): lane l
+// carries columns l and l + 64 in x0 and x1 and their pivot reciprocals in
+// d0 and d1; P holds the panel (odd leading dimension ld). Steps as in
+// fwd_steps. The first 64 columns' coefficients are read ahead of the
+// solution (tri_bwd_load, while the other waves still sum), so the steps wait
+// for no load.
+__device__ __forceinline__ void tri_bwd_load(double (&a)[4][16], const double* __restrict__ P, const int ld,
+                                             const int c, const int lane) {
+    const double* const p = P + min(lane, c - 1) * ld;
+    static_for<4>([&](auto B) {
+        if (16 * B < c) {
+#pragma unroll
+            for (int k = 0; k < 16; k++) a[B][k] = p[min(16 * B + k, c - 1)];
+        }
+    });
+}
+__device__ __forceinline__ void tri_bwd_wave(const double (&a)[4][16], const double* __restrict__ P, const int ld,
+                                             const int c, const double d0, const double d1, double& x0, double& x1,
+                                             const int lane) {
+    double o0 = 0.0, o1 = 0.0;
+    if (c > 64) {
+        const double* const p0 = P + lane * ld;
+        const double* const p1 = P + min(lane + 64, c - 1) * ld;
+        for (int j = (c - 1) & ~15; j >= 64; j -= 16) {
+            const int nb = c - j;
+            double u[16], v[16];
+#pragma unroll
+            for (int k = 0; k < 16; k++) {
+                u[k] = p1[min(j + k, c - 1)];
+                v[k] = p0[min(j + k, c - 1)];
+            }
+            static_for<4>([&](auto Q) {
+                if (nb > 12 - 4 * Q) bwd_steps<12 - 4 * Q, true, true>(x1, x0, o1, u, v, d1, j - 64, nb);
+            });
+        }
+    }
+    static_for<4>([&](auto Q) {
+        constexpr int B = 3 - decltype(Q)::value;
+        const int nb = c - 16 * B;
+        if (nb >= 16) {
+            static_for<4>([&](auto R) {
+                bwd_steps<12 - 4 * R, false, false>(x0, x0, o0, a[B], a[B], d0, 16 * B, nb);
+            });
+        } else if (nb > 0) {
+            static_for<4>([&](auto R) {
+                if (nb > 12 - 4 * R) bwd_steps<12 - 4 * R, true, false>(x0, x0, o0, a[B], a[B], d0, 16 * B, nb);
+            });
+        }
+    });
+    x0 = o0;
+    x1 = o1;
+}
+
+// Backward step of one front: the panel is staged in LDS (odd leading
+// dimension) by contiguous 16-byte loads, the dot products run over all
+// threads, the triangle by one wave. A 66 x 198 front takes 5,800 cycles to
+// stage, 3,000 for the products and 3,800 for the triangle (one row's chain
+// after another by DPP broadcasts: 12,500); 11.0 -> 7.3 us a launch of few
+// fronts. Taking the rectangle from HBM to registers instead costs more where
+// few fronts run (8-byte strands load at a third of the rate; 13.7 us) and
+// wins only on levels of more fronts than compute units (17 against 23 us).
+// PU: panel loads per thread in flight while staging (16 where every panel is
+// at most kSweepHalfLds); the arithmetic does not depend on it.
+template <int PU>
 __device__ __forceinline__ void bwd_front(const FrontDesc& F, double* __restrict__ sh) {
     const int c = F.c, r = F.r;
     const int u = r - c;
     double* const yb = F.y - F.col0;  // the instance's work vector
     const int ld = r | 1;
-    const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63;
+    constexpr int nt = kSolveThreads;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // G consecutive lanes per column (G c <= 256 for c <= 128)
+    const int lg = c <= 16 ? 4 : c <= 32 ? 3 : c <= 64 ? 2 : 1, G = 1 << lg;
+    const int nz = (u + 4 * G - 1) & -(4 * G);
     double* P = sh;
-    double* t = sh + even_up(ld * c);
-    double* zu = t + c;
-    double* dv = zu + u;
+    double* z = sh + even_up(ld * c);
+    double* t = z + nz;
+    // row i of the update part at z[place(i)]: a lane's four rows of a step
+    // (G apart) side by side
+    auto place = [&](const int i) {
+        return ((i >> (lg + 2)) << (lg + 2)) + ((i & (G - 1)) << 2) + ((i >> lg) & 3);
+    };
     const int* __restrict__ rw = F.rw;
     // The update rows' indices are loaded first, so the gather of their
     // values waits only for them while the panel loads stay in flight.
@@ -1842,58 +1921,76 @@ __device__ __forceinline__ void bwd_front(const FrontDesc& F, double* __restrict
     double2 pv[PU];
 #pragma unroll
     for (int k = 0; k < PU; k++) pv[k] = s2[min(tid + k * nt, n2 - 1)];
-    double wd = F.dinv[min(tid, c - 1)];
+    double d0 = 0.0, d1 = 0.0, y0 = 0.0, y1 = 0.0;
+    if (wave == 0) {
+        d0 = F.dinv[min(lane, c - 1)];
+        d1 = F.dinv[min(lane + 64, c - 1)];
+        y0 = F.y[min(lane, c - 1)];
+        y1 = F.y[min(lane + 64, c - 1)];
+    }
     pin(ri);
     double zy = u > 0 ? yb[ri] : 0.0;
 #pragma unroll
     for (int k = 0; k < PU; k++) pin(pv[k]);
-    pin(wd);
-    pin(zy);
 #pragma unroll
     for (int k = 0; k < PU; k++)
         if (tid + k * nt < n2) d2[tid + k * nt] = pv[k];
     for (int q = tid + PU * nt; q < n2; q += nt) d2[q] = s2[q];
-    if (tid < u) zu[tid] = zy;
-    for (int i = tid + nt; i < u; i += nt) zu[i] = yb[rw[i]];
-    if (tid < c) dv[tid] = wd;
+    pin(zy);
+    if (tid < nz) z[place(tid)] = tid < u ? zy : 0.0;
+    for (int i = tid + nt; i < nz; i += nt) z[place(i)] = i < u ? yb[rw[i]] : 0.0;
     __syncthreads();
-    // t = y1 - L21^T z: G consecutive lanes per column (G c <= 256 for
-    // c <= 128), each with four running sums over rows g, g + G, ...; a
-    // group's sums are combined in a fixed order
+    // t = y1 - L21^T z: lane g of a column's G takes rows g, g + G, g + 2 G,
+    // g + 3 G of every 4 G into four running sums while all four are there,
+    // the rest into the first; a group's sums are combined in a fixed order.
+    // Four steps' LDS reads go out together.
     {
-        const int lg = c <= 16 ? 4 : c <= 32 ? 3 : c <= 64 ? 2 : 1, G = 1 << lg;
         const int k = tid >> lg, g = tid & (G - 1);
+        const int T = u - 3 * G - g > 0 ? (u - 3 * G - g + 4 * G - 1) >> (lg + 2) : 0;
         double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
         if (k < c) {
-            const double* col = P + k * ld + c;
-            int i = g;
-            for (; i + 3 * G < u; i += 4 * G) {
-                a0 = fma(col[i], zu[i], a0);
-                a1 = fma(col[i + G], zu[i + G], a1);
-                a2 = fma(col[i + 2 * G], zu[i + 2 * G], a2);
-                a3 = fma(col[i + 3 * G], zu[i + 3 * G], a3);
+            const double* const col = P + k * ld + c + g;
+            const double* const zg = z + 4 * g;
+            int s = 0;
+            for (; s + 4 <= T; s += 4) {
+                double p[4][4], q[4][4];
+#pragma unroll
+                for (int e = 0; e < 4; e++)
+#pragma unroll
+                    for (int h = 0; h < 4; h++) {
+                        p[e][h] = col[4 * G * (s + e) + G * h];
+                        q[e][h] = zg[4 * G * (s + e) + h];
+                    }
+#pragma unroll
+                for (int e = 0; e < 4; e++) {
+                    a0 = fma(p[e][0], q[e][0], a0);
+                    a1 = fma(p[e][1], q[e][1], a1);
+                    a2 = fma(p[e][2], q[e][2], a2);
+                    a3 = fma(p[e][3], q[e][3], a3);
+                }
             }
-            for (; i < u; i += G) a0 = fma(col[i], zu[i], a0);
+            for (; s < T; s++) {
+                a0 = fma(col[4 * G * s], zg[4 * G * s], a0);
+                a1 = fma(col[4 * G * s + G], zg[4 * G * s + 1], a1);
+                a2 = fma(col[4 * G * s + 2 * G], zg[4 * G * s + 2], a2);
+                a3 = fma(col[4 * G * s + 3 * G], zg[4 * G * s + 3], a3);
+            }
+            for (int h = 0; g + 4 * G * T + G * h < u; h++) a0 = fma(col[4 * G * T + G * h], zg[4 * G * T + h], a0);
         }
         double part = (a0 + a1) + (a2 + a3);
         for (int off = G >> 1; off > 0; off >>= 1) part += __shfl_xor(part, off);
-        if (k < c && g == 0) t[k] = F.y[k] - part;
+        if (k < c && g == 0) t[k] = part;
     }
+    double a[4][16];
+    if (wave == 0) tri_bwd_load(a, P, ld, c, lane);
     __syncthreads();
-    if (tid < 64) {
-        double x0 = lane < c ? t[lane] : 0.0;
-        double x1 = lane + 64 < c ? t[lane + 64] : 0.0;
-        tri_bwd_wave(P, ld, c, dv, x0, x1, lane);
+    if (wave == 0) {
+        double x0 = lane < c ? y0 - t[lane] : 0.0;
+        double x1 = lane + 64 < c ? y1 - t[lane + 64] : 0.0;
+        tri_bwd_wave(a, P, ld, c, d0, d1, x0, x1, lane);
         if (lane < c) F.y[lane] = x0;
         if (lane + 64 < c) F.y[lane + 64] = x1;
     }
-}
-
-// skip modes of the sweeps: SKIP_NONE runs every front; SKIP_REFINE skips
-// the fronts of instances whose refinement has stopped, SKIP_CG those whose
-// CG has stopped (the queued rounds after a stop decision do nothing)
-__device__ __forceinline__ bool front_idle(const FrontDesc& F, int skip) {
-    return skip == SKIP_REFINE ? *F.done != 0 : (skip == SKIP_CG ? *F.cgdone != 0 : false);
 }
 
 // Forward sweep of large fronts, one workgroup per front: the c x c triangle
@@ -1981,43 +2078,34 @@ __global__ __launch_bounds__(kBigThreads) void k_big_bwd(const FrontDesc* __rest
     __syncthreads();
     if (tid < 64) {
         double x0 = lane < c ? t[lane] : 0.0, x1 = 0.0;
-        tri_bwd_wave(Ls, ldl, c, dv, x0, x1, lane);
+        const double d = dv[min(lane, c - 1)];
+        double a[4][16];
+        tri_bwd_load(a, Ls, ldl, c, lane);
+        tri_bwd_wave(a, Ls, ldl, c, d, d, x0, x1, lane);
         if (lane < c) F.y[lane] = x0;
     }
 }
 
-__global__ __launch_bounds__(kSolveThreads) void k_fwd(const InstDev* __restrict__ insts,
+template <int NTH>
+__global__ __launch_bounds__(NTH, 2) void k_fwd(const InstDev* __restrict__ insts,
                                                       const FrontDesc* __restrict__ fds, int skip_done) {
     extern __shared__ __align__(16) double sh[];
-    const FrontDesc& F = fds[blockIdx.x];
-    if (front_idle(F, skip_done)) return;
-    fwd_front(insts[F.inst], F, sh);
+    fwd_front<NTH>(insts, fds[blockIdx.x], skip_done, sh);
 }
 
+template <int PU>
 __global__ __launch_bounds__(kSolveThreads) void k_bwd(const FrontDesc* __restrict__ fds, int skip_done) {
     extern __shared__ __align__(16) double sh[];
     const FrontDesc& F = fds[blockIdx.x];
     if (front_idle(F, skip_done)) return;
-    bwd_front(F, sh);
-}
-
-// the same for launches of small panels (at most kSweepHalfLds of LDS):
-// sixteen staged loads per thread (110 registers instead of 184), so the
-// registers allow four workgroups per compute unit where the LDS does
-// (measured on the 256-instance batch: backward sweeps 1.13 -> 1.05 ms; eight
-// loads per thread: 1.14 ms)
-__global__ __launch_bounds__(kSolveThreads) void k_bwd_small(const FrontDesc* __restrict__ fds, int skip_done) {
-    extern __shared__ __align__(16) double sh[];
-    const FrontDesc& F = fds[blockIdx.x];
-    if (front_idle(F, skip_done)) return;
-    bwd_front<KKT_BWD_SMALL_PU>(F, sh);
+    bwd_front<PU>(F, sh);
 }
 
 // Both sweeps in one launch: tickets 0..N-1 are the forward sweep in
 // topological order, tickets N..2N-1 the backward sweep in reverse order. A
 // front's backward step waits for its parent's (a root waits for its own
 // forward step, the last of its tree).
-__global__ __launch_bounds__(kSolveThreads) void k_sweeps_queue(const InstDev* __restrict__ insts,
+__global__ __launch_bounds__(kSolveThreads, 2) void k_sweeps_queue(const InstDev* __restrict__ insts,
                                                                const FrontDesc* __restrict__ fds, DepLists D,
                                                                int skip_done) {
     extern __shared__ __align__(16) double sh[];
@@ -2037,11 +2125,8 @@ __global__ __launch_bounds__(kSolveThreads) void k_sweeps_queue(const InstDev* _
         __syncthreads();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         const FrontDesc& F = fds[k];
-        const int idle = __builtin_amdgcn_readfirstlane((int)front_idle(F, skip_done));
-        if (!idle) {
-            if (fwd) fwd_front(insts[F.inst], F, sh);
-            else bwd_front(F, sh);
-        }
+        if (fwd) fwd_front<kSolveThreads>(insts, F, skip_done, sh);
+        else if (!front_idle(F, skip_done)) bwd_front<32>(F, sh);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         __syncthreads();
         if (sched_wave()) {
@@ -3922,11 +4007,7 @@ hipError_t set_kernel_attributes() {
     if (e != hipSuccess) return e;
     e = hipFuncSetAttribute((const void*)k_factor_small, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute((const void*)k_fwd, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e != hipSuccess) return e;
     e = hipFuncSetAttribute((const void*)k_factor_queue, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute((const void*)k_sweeps_queue, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
     e = hipFuncSetAttribute((const void*)k_cr_factor<1>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
@@ -3938,9 +4019,9 @@ hipError_t set_kernel_attributes() {
     if (e != hipSuccess) return e;
     e = hipFuncSetAttribute((const void*)k_cr_factor<5>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute((const void*)k_bwd_small, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e != hipSuccess) return e;
-    return hipFuncSetAttribute((const void*)k_bwd, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    for (const void* k : {(const void*)k_fwd<64>, (const void*)k_fwd<128>, (const void*)k_fwd<256>, (const void*)k_sweeps_queue, (const void*)k_bwd<16>, (const void*)k_bwd<32>})
+        if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxSweepLds);
+    return e;
 }
 
 static inline unsigned blocks_for(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
@@ -4087,13 +4168,17 @@ void launch_sweeps_queue(const InstDev* insts, const FrontDesc* fds, const DepLi
                          int skip_done, hipStream_t st) {
     if (D.nitems > 0) k_sweeps_queue<<<grid, kSolveThreads, lds, st>>>(insts, fds, D, skip_done);
 }
-void launch_fwd(const InstDev* insts, const FrontDesc* fds, int nitems, size_t lds, int skip_done, hipStream_t st) {
-    if (nitems > 0) k_fwd<<<nitems, kSolveThreads, lds, st>>>(insts, fds, skip_done);
-}
-void launch_bwd(const FrontDesc* fds, int nitems, size_t lds, int skip_done, hipStream_t st) {
+void launch_fwd(const InstDev* insts, const FrontDesc* fds, int nitems, int maxr, bool narrow, size_t lds, int skip_done, hipStream_t st) {
     if (nitems <= 0) return;
-    if (lds <= kSweepHalfLds) k_bwd_small<<<nitems, kSolveThreads, lds, st>>>(fds, skip_done);
-    else k_bwd<<<nitems, kSolveThreads, lds, st>>>(fds, skip_done);
+    // a wave holds 128 rows
+    if (narrow) k_fwd<64><<<nitems, 64, lds, st>>>(insts, fds, skip_done);
+    else if (maxr <= 256) k_fwd<128><<<nitems, 128, lds, st>>>(insts, fds, skip_done);
+    else k_fwd<256><<<nitems, 256, lds, st>>>(insts, fds, skip_done);
+}
+void launch_bwd(const FrontDesc* fds, int nitems, bool light, size_t lds, int skip_done, hipStream_t st) {
+    if (nitems <= 0) return;
+    if (light) k_bwd<16><<<nitems, kSolveThreads, lds, st>>>(fds, skip_done);
+    else k_bwd<32><<<nitems, kSolveThreads, lds, st>>>(fds, skip_done);
 }
 void launch_perm_in(const InstDev* insts, const Calls& C, const WorkItem* rows, int nitems, int mode, hipStream_t st) {
     if (nitems > 0) k_perm_in<<<nitems, kBlock, 0, st>>>(insts, C, rows, mode);

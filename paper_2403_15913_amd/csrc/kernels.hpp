@@ -53,12 +53,12 @@ struct DepLists {
 // Dynamic LDS a front may use (the kernels also hold a little static LDS;
 // gfx950 gives a workgroup 160 KiB in total).
 constexpr int kMaxDynLds = 158 * 1024;
-// sweep fronts at or below this LDS size run two workgroups per compute unit
-// (160 KiB of LDS per CU; the sweep kernels' registers allow two)
+// backward sweep fronts at or below this LDS size run two workgroups per
+// compute unit (160 KiB of LDS per CU)
 constexpr size_t kSweepHalfLds = 79 * 1024;
-// a level's small fronts get a sweep launch of their own from this many on
-// (two workgroups on each of the 256 compute units)
-constexpr int kSweepSplitMin = 512;
+// what a sweep launch may ask for: the update values are padded to whole steps
+// (at most 63 doubles past what the fronts' budget counts)
+constexpr int kMaxSweepLds = kMaxDynLds + 1024;
 
 hipError_t set_kernel_attributes();
 
@@ -121,8 +121,11 @@ void launch_factor_queue(const InstDev* insts, const FrontDesc* fds, const DepLi
                          hipStream_t st);
 void launch_sweeps_queue(const InstDev* insts, const FrontDesc* fds, const DepLists& D, int grid, size_t lds,
                          int skip_done, hipStream_t st);
-void launch_fwd(const InstDev* insts, const FrontDesc* fds, int nitems, size_t lds, int skip_done, hipStream_t st);
-void launch_bwd(const FrontDesc* fds, int nitems, size_t lds, int skip_done, hipStream_t st);
+// (narrow: one wave per front, for fronts of at most 128 rows)
+void launch_fwd(const InstDev* insts, const FrontDesc* fds, int nitems, int maxr, bool narrow, size_t lds,
+                int skip_done, hipStream_t st);
+// (light: half the panel loads in flight, for panels of at most kSweepHalfLds)
+void launch_bwd(const FrontDesc* fds, int nitems, bool light, size_t lds, int skip_done, hipStream_t st);
 
 // permutation modes
 enum { PIN_B = 0, PIN_R = 1 };

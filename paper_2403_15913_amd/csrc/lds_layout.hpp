@@ -46,6 +46,18 @@ inline int64_t factor_launch_lds_bytes(int r, int c) {
 // sweeps: (r|1) x c panel (padded to an even count) + r vector entries + c pivot reciprocals
 inline int64_t solve_lds_bytes(int r, int c) { return ((((int64_t)(r | 1) * c + 1) & ~(int64_t)1) + r + c) * 8; }
 
+// what the sweep launches reserve: forward, the solved values (padded to 16
+// columns), two vectors of r and the rows past 128;
+// backward, the panel (padded to an even count), the update values (padded
+// to whole steps of the dot products) and c sums
+inline int64_t fwd_lds_bytes(int r, int c) {
+    return (((c + 15) & ~15) + 2 * (int64_t)((r + 1) & ~1) + std::max(0, r - 128)) * 8;
+}
+inline int64_t bwd_lds_bytes(int r, int c) {
+    const int g4 = c <= 16 ? 64 : c <= 32 ? 32 : c <= 64 ? 16 : 8;
+    return ((((int64_t)(r | 1) * c + 1) & ~(int64_t)1) + ((r - c + g4 - 1) & -g4) + c) * 8;
+}
+
 inline int64_t front_lds_bytes(int r, int c) { return std::max(factor_lds_bytes(r, c), solve_lds_bytes(r, c)); }
 
 // A front too tall for the LDS budget even at one column is a large front:
