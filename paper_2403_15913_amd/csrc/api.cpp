@@ -698,11 +698,11 @@ void Engine::sweeps(hipStream_t st, int skip_done) {
             TL(KKT_PHASE_FWD, launch_fwd(di(), fdesc + P.begin, P.count, P.maxr, narrow, P.lds_fwd, skip_done, st));
         }
         if (lvl_large[l] < lvl_ptr[l + 1])
-            TL(KKT_PHASE_FWD, launch_big_fwd(di(), fdesc + lvl_large[l], lvl_ptr[l + 1] - lvl_large[l], skip_done, st));
+            TL(KKT_PHASE_FWD, launch_big_fwd(di(), fdesc + lvl_large[l], lvl_ptr[l + 1] - lvl_large[l], lvl_lmaxr[l], skip_done, st));
     }
     for (int l = nl - 1; l >= 0; l--) {
         if (lvl_large[l] < lvl_ptr[l + 1])
-            TL(KKT_PHASE_BWD, launch_big_bwd(fdesc + lvl_large[l], lvl_ptr[l + 1] - lvl_large[l], skip_done, st));
+            TL(KKT_PHASE_BWD, launch_big_bwd(fdesc + lvl_large[l], lvl_ptr[l + 1] - lvl_large[l], lvl_lmaxc[l], skip_done, st));
         for (int k = sw_lvl[l]; k < sw_lvl[l + 1]; k++) {
             const SweepPart& P = sw_part[k];
             // (chosen as in the forward sweep: one form for the levels of few fronts)

@@ -1344,40 +1344,41 @@ __device__ inline unsigned big_diag_chain(const double* P, int ld, int r, int j0
 // child's update columns mapping into the block, and its update rows mapping
 // into the row range, are contiguous ranges, its relative rows being
 // ascending). Every entry belongs to one workgroup and takes the same
-// operations in the same order as with whole columns per workgroup.
+// operations in the same order as with whole columns per workgroup. Bound by
+// load latency: every round trip has its loads issued together (45 -> 27 us on
+// a front of 64 x 2,900 with two children).
 constexpr int kBigInitRows = 256;
 __global__ __launch_bounds__(kBigThreads) void k_big_init(const InstDev* __restrict__ insts,
                                                         const FrontDesc* __restrict__ fds) {
+    __shared__ int cnt[2][4];
     const FrontDesc& F = fds[blockIdx.x];
     const int c = F.c, r = F.r, ld = r | 1;
     const int b0 = blockIdx.y << 4, r0 = (int)blockIdx.z * kBigInitRows;
     if (b0 >= c || r0 >= r) return;
-    const int b1 = min(c, b0 + 16), r1 = min(r, r0 + kBigInitRows), nr = r1 - r0;
+    const int b1 = min(c, b0 + 16), r1 = min(r, r0 + kBigInitRows);
     const InstDev& I = insts[F.inst];
     const PatDev& T = I.P;
     double* const P = F.L;
-    const int tid = threadIdx.x, nt = blockDim.x;
-    for (int q = tid; q < (b1 - b0) * nr; q += nt) {
-        const int col = b0 + q / nr, row = r0 + (q - (q / nr) * nr);
-        P[(int64_t)col * ld + row] = 0.0;
-    }
+    const int tid = threadIdx.x;
+    constexpr int nt = kBigThreads;
+    static_assert(kBigInitRows == kBigThreads, "one row per thread");
+    const int row = r0 + tid;
+    double* const Pr = P + (int64_t)b0 * ld + min(row, r - 1);
+    if (row < r1)
+        for (int j = 0; j < b1 - b0; j++) Pr[(int64_t)j * ld] = 0.0;
     __syncthreads();
-    for (int q = tid; q < F.nk; q += nt) {
-        const int loc = F.kl[q];
-        const int col = loc >> 16, row = loc & 0xffff;
-        if (col >= b0 && col < b1 && row >= r0 && row < r1) P[(int64_t)col * ld + row] = F.kv[q];
-    }
-    __syncthreads();
-    // first index of the ascending rl[0 .. n) at or above v
-    auto lower = [](const int* rl, int n, int v) {
-        int lo = 0, hi = n;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (rl[mid] < v) lo = mid + 1;
-            else hi = mid;
+    constexpr int KU = 8;  // places in flight per thread
+    for (int q0 = tid; q0 < F.nk; q0 += KU * nt) {
+        int loc[KU];
+#pragma unroll
+        for (int e = 0; e < KU; e++) loc[e] = F.kl[min(q0 + e * nt, F.nk - 1)];
+#pragma unroll
+        for (int e = 0; e < KU; e++) {
+            const int col = loc[e] >> 16, i = loc[e] & 0xffff;
+            if (q0 + e * nt < F.nk && col >= b0 && col < b1 && i >= r0 && i < r1)
+                P[(int64_t)col * ld + i] = F.kv[q0 + e * nt];
         }
-        return lo;
-    };
+    }
     for (int k = 0; k < F.nch; k++) {
         const int ch = T.ch_list[F.ch0 + k];
         const int cc = T.sn_ncol[ch];
@@ -1385,13 +1386,47 @@ __global__ __launch_bounds__(kBigThreads) void k_big_init(const InstDev* __restr
         const double* const Uc = I.U + T.sn_uofs[ch];
         const int* const rl = T.rel + T.sn_rowofs[ch] + cc;
         // child update columns e0 .. e1-1 map into columns b0 .. b1-1, its
-        // update rows a0 .. a1-1 into rows r0 .. r1-1
-        const int e0 = lower(rl, nb, b0), e1 = lower(rl, nb, b1);
-        const int a0 = lower(rl, uc, r0), a1 = lower(rl, uc, r1), na = a1 - a0;
-        const int64_t ctot = (int64_t)(e1 - e0) * na;
-        for (int64_t q = tid; q < ctot; q += nt) {
-            const int b = e0 + (int)(q / na), a = a0 + (int)(q - (int64_t)(b - e0) * na);
-            if (a >= b) P[(int64_t)rl[b] * ld + rl[a]] += Uc[(int64_t)b * uc + a];
+        // update rows a0 .. a1-1 into rows r0 .. r1-1: the ascending relative
+        // rows below each bound, counted by all threads (four binary searches
+        // one after the other are some 40 dependent loads)
+        if (tid < 4) cnt[k & 1][tid] = 0;
+        __syncthreads();
+        int n0 = 0, n1 = 0, n2 = 0, n3 = 0;
+        for (int q0 = tid; q0 < uc; q0 += KU * nt) {
+            int v[KU];
+#pragma unroll
+            for (int e = 0; e < KU; e++) v[e] = q0 + e * nt < uc ? rl[min(q0 + e * nt, uc - 1)] : r;
+#pragma unroll
+            for (int e = 0; e < KU; e++) {
+                n0 += v[e] < b0 && q0 + e * nt < nb;
+                n1 += v[e] < b1 && q0 + e * nt < nb;
+                n2 += v[e] < r0;
+                n3 += v[e] < r1;
+            }
+        }
+        atomicAdd(&cnt[k & 1][0], n0);
+        atomicAdd(&cnt[k & 1][1], n1);
+        atomicAdd(&cnt[k & 1][2], n2);
+        atomicAdd(&cnt[k & 1][3], n3);
+        __syncthreads();
+        const int e0 = cnt[k & 1][0], ne = cnt[k & 1][1] - e0, a0 = cnt[k & 1][2], a1 = cnt[k & 1][3];
+        // at most one of the child's rows per thread, sixteen columns
+        const int a = a0 + tid;
+        if (ne > 0 && a < a1) {
+            const int ra = rl[a];
+            int rb[16];
+            double uv[16], pv[16];
+#pragma unroll
+            for (int j = 0; j < 16; j++) {
+                const int b = e0 + min(j, ne - 1);
+                rb[j] = rl[b];
+                uv[j] = Uc[(int64_t)b * uc + a];
+            }
+#pragma unroll
+            for (int j = 0; j < 16; j++) pv[j] = P[(int64_t)rb[j] * ld + ra];
+#pragma unroll
+            for (int j = 0; j < 16; j++)
+                if (j < ne && a >= e0 + j) P[(int64_t)rb[j] * ld + ra] = pv[j] + uv[j];
         }
         __syncthreads();
     }
@@ -1993,32 +2028,47 @@ __device__ __forceinline__ void bwd_front(const FrontDesc& F, double* __restrict
     }
 }
 
-// Forward sweep of large fronts, one workgroup per front: the c x c triangle
-// is staged in LDS, the children's update vectors are added child by child
-// (the update part in the front's own HBM slot), the triangle is solved by
-// one wave (y_j = w_j / l_jj, then w_i -= l_ij y_j for i > j, in column
-// order) and the update rows take -L21 y by one thread per row (column order).
+// Forward sweep of large fronts. k_big_fwd, one workgroup per front: the
+// children's update vectors are added child by child (the update part in the
+// front's own HBM slot), the c x c triangle is solved by one wave, its
+// coefficients in registers (y_j = w_j / l_jj, then w_i -= l_ij y_j for i > j,
+// in column order). k_big_fwd_rows: the update rows take -L21 y by one thread
+// per row (column order), over as many workgroups as they fill. By one
+// workgroup in all, its loads one after another, the pass took 50 us on a
+// front of 64 x 2,900; 12 us now.
+template <int K0, bool TAIL>
+__device__ __forceinline__ void row_steps(double& w, double& y, const double (&a)[16], const double d, const int l0,
+                                          const int nb) {
+    static_for<4>([&](auto K) {
+        constexpr int k = K0 + K;
+        double v = readlane_d(w * d, l0 + k);
+        if (TAIL) v = k < nb ? v : 0.0;
+        y = writelane_d(v, l0 + k, y);
+        w = fma(-a[k], v, w);
+    });
+}
 __global__ __launch_bounds__(kBigThreads) void k_big_fwd(const InstDev* __restrict__ insts,
                                                        const FrontDesc* __restrict__ fds, int skip_done) {
-    __shared__ double Ls[kBigMaxCols * (kBigMaxCols + 1)];
-    __shared__ double w[kBigMaxCols], dv[kBigMaxCols];
+    __shared__ double w[kBigMaxCols];
     const FrontDesc& F = fds[blockIdx.x];
     if (front_idle(F, skip_done)) return;
     const InstDev& I = insts[F.inst];
     const PatDev& T = I.P;
-    const int c = F.c, r = F.r, u = r - c, ld = r | 1, ldl = c | 1;
+    const int c = F.c, r = F.r, u = r - c, ld = r | 1;
     const double* const P = F.L;
     double* const V = F.V;
-    const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63;
-    for (int q = tid; q < c * c; q += nt) {
-        const int j = q / c, i = q - j * c;
-        Ls[j * ldl + i] = P[(int64_t)j * ld + i];
+    constexpr int nt = kBigThreads, VU = 8;
+    const int tid = threadIdx.x, lane = tid & 63;
+    double a[4][16], d = 0.0;
+    if (tid < 64) {
+        static_for<4>([&](auto B) {
+#pragma unroll
+            for (int k = 0; k < 16; k++) a[B][k] = P[(int64_t)min(16 * B + k, c - 1) * ld + min(lane, c - 1)];
+        });
+        d = F.dinv[min(lane, c - 1)];
     }
-    if (tid < c) {
-        w[tid] = F.y[tid];
-        dv[tid] = F.dinv[tid];
-    }
-    for (int a = tid; a < u; a += nt) V[a] = 0.0;
+    if (tid < c) w[tid] = F.y[tid];
+    for (int i = tid; i < u; i += nt) V[i] = 0.0;
     __syncthreads();
     for (int k = 0; k < F.nch; k++) {
         const int ch = T.ch_list[F.ch0 + k];
@@ -2026,59 +2076,121 @@ __global__ __launch_bounds__(kBigThreads) void k_big_fwd(const InstDev* __restri
         const int uc = T.sn_nrow[ch] - cc;
         const double* const Vc = I.V + T.sn_vofs[ch];
         const int* const rl = T.rel + T.sn_rowofs[ch] + cc;
-        for (int a = tid; a < uc; a += nt) {
-            const int ra = rl[a];
-            const double v = Vc[a];
-            if (ra < c) w[ra] += v;
-            else V[ra - c] += v;
+        // (a child's entries are distinct: VU of them per thread in flight)
+        for (int q0 = tid; q0 < uc; q0 += VU * nt) {
+            int ra[VU];
+            double v[VU], t[VU];
+#pragma unroll
+            for (int e = 0; e < VU; e++) {
+                const int q = min(q0 + e * nt, uc - 1);
+                ra[e] = rl[q];
+                v[e] = Vc[q];
+            }
+#pragma unroll
+            for (int e = 0; e < VU; e++) t[e] = u > 0 ? V[max(ra[e] - c, 0)] : 0.0;
+#pragma unroll
+            for (int e = 0; e < VU; e++) {
+                if (q0 + e * nt >= uc) continue;
+                if (ra[e] < c) w[ra[e]] += v[e];
+                else V[ra[e] - c] = t[e] + v[e];
+            }
         }
         __syncthreads();
     }
     if (tid < 64) {
-        double wi = lane < c ? w[lane] : 0.0;
-        for (int j = 0; j < c; j++) {
-            const double yj = readlane_d(wi, j) * dv[j];
-            if (lane > j && lane < c) wi = fma(-Ls[j * ldl + lane], yj, wi);
-        }
-        if (lane < c) w[lane] = wi * dv[lane];
+        double x = lane < c ? w[lane] : 0.0, y = 0.0;
+        static_for<4>([&](auto B) {
+            const int nb = c - 16 * B;
+            static_for<4>([&](auto Q) {
+                if (nb >= 4 * Q + 4) row_steps<4 * Q, false>(x, y, a[B], d, 16 * B, nb);
+                else if (nb > 4 * Q) row_steps<4 * Q, true>(x, y, a[B], d, 16 * B, nb);
+            });
+        });
+        if (lane < c) F.y[lane] = y;
     }
+}
+__global__ __launch_bounds__(kBigThreads) void k_big_fwd_rows(const FrontDesc* __restrict__ fds, int skip_done) {
+    const FrontDesc& F = fds[blockIdx.x];
+    const int c = F.c, r = F.r, u = r - c, ld = r | 1;
+    const int row = (int)blockIdx.y * kBigThreads + threadIdx.x;
+    if ((int)blockIdx.y * kBigThreads >= u) return;
+    if (front_idle(F, skip_done)) return;
+    __shared__ double y[kBigMaxCols];
+    if (threadIdx.x < kBigMaxCols) y[threadIdx.x] = (int)threadIdx.x < c ? F.y[threadIdx.x] : 0.0;
+    const int i = min(row, u - 1);
+    const double* const P = (const double*)F.L + c + i;
+    double acc = F.V[i];
+    double a[4][16];
+    static_for<4>([&](auto B) {
+#pragma unroll
+        for (int k = 0; k < 16; k++) a[B][k] = P[(int64_t)min(16 * B + k, c - 1) * ld];
+    });
     __syncthreads();
-    for (int a = tid; a < u; a += nt) {
-        double acc = V[a];
-        for (int j = 0; j < c; j++) acc = fma(-P[(int64_t)j * ld + c + a], w[j], acc);
-        V[a] = acc;
-    }
-    if (tid < c) F.y[tid] = w[tid];
+    static_for<4>([&](auto B) {
+        if (16 * B < c) {
+#pragma unroll
+            for (int k = 0; k < 16; k++)
+                if (16 * B + k < c) acc = fma(-a[B][k], y[16 * B + k], acc);
+        }
+    });
+    if (row < u) F.V[row] = acc;
 }
 
-// Backward sweep of large fronts: t = y1 - L21^T z by one wave per column
-// (lanes over rows, a fixed butterfly), then the triangle by one wave.
-__global__ __launch_bounds__(kBigThreads) void k_big_bwd(const FrontDesc* __restrict__ fds, int skip_done) {
-    __shared__ double Ls[kBigMaxCols * (kBigMaxCols + 1)];
-    __shared__ double t[kBigMaxCols], dv[kBigMaxCols];
+// Backward sweep of large fronts. k_big_bwd_dot: y1 - L21^T z, one wave per
+// column (lanes over rows, a fixed butterfly); k_big_bwd: the triangle by one
+// wave, one workgroup per front. With the dot products in the front's one
+// workgroup, a row index, its value and the panel entry at a time, the pass
+// took 104 us on a front of 64 x 2,900; 9 us now.
+__global__ __launch_bounds__(kBigThreads) void k_big_bwd_dot(const FrontDesc* __restrict__ fds, int skip_done) {
+    constexpr int RU = 8;  // rows per lane in flight
     const FrontDesc& F = fds[blockIdx.x];
+    const int c = F.c, r = F.r, u = r - c, ld = r | 1;
+    const int lane = threadIdx.x & 63;
+    const int j = __builtin_amdgcn_readfirstlane((int)blockIdx.y * (kBigThreads >> 6) + (int)(threadIdx.x >> 6));
+    if (j >= c || u == 0) return;
     if (front_idle(F, skip_done)) return;
-    const int c = F.c, r = F.r, u = r - c, ld = r | 1, ldl = c | 1;
-    const double* const P = F.L;
+    const double* const col = (const double*)F.L + (int64_t)j * ld + c;
     const double* const yb = F.y - F.col0;  // the instance's work vector
     const int* const rw = F.rw;
-    const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wave = tid >> 6, nwave = nt >> 6;
-    for (int q = tid; q < c * c; q += nt) {
-        const int j = q / c, i = q - j * c;
-        Ls[j * ldl + i] = P[(int64_t)j * ld + i];
+    double s = 0.0;
+    for (int a0 = lane; a0 < u; a0 += 64 * RU) {
+        int ri[RU];
+        double p[RU], z[RU];
+#pragma unroll
+        for (int e = 0; e < RU; e++) {
+            const int a = min(a0 + 64 * e, u - 1);
+            ri[e] = rw[a];
+            p[e] = col[a];
+        }
+#pragma unroll
+        for (int e = 0; e < RU; e++) z[e] = yb[ri[e]];
+#pragma unroll
+        for (int e = 0; e < RU; e++)
+            if (a0 + 64 * e < u) s = fma(p[e], z[e], s);
     }
-    if (tid < c) dv[tid] = F.dinv[tid];
-    for (int j = wave; j < c; j += nwave) {
-        const double* const col = P + (int64_t)j * ld + c;
-        double s = 0.0;
-        for (int a = lane; a < u; a += 64) s = fma(col[a], yb[rw[a]], s);
-        for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-        if (lane == 0) t[j] = F.y[j] - s;
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+    if (lane == 0) F.y[j] = F.y[j] - s;
+}
+__global__ __launch_bounds__(kBigThreads) void k_big_bwd(const FrontDesc* __restrict__ fds, int skip_done) {
+    __shared__ double Ls[kBigMaxCols * (kBigMaxCols + 1)];
+    const FrontDesc& F = fds[blockIdx.x];
+    if (front_idle(F, skip_done)) return;
+    const int c = F.c, r = F.r, ld = r | 1, ldl = c | 1;
+    const double* const P = F.L;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    double t[16];
+#pragma unroll
+    for (int k = 0; k < 16; k++) t[k] = P[(int64_t)min(4 * k + wave, c - 1) * ld + min(lane, c - 1)];
+    double x0 = 0.0, x1 = 0.0, d = 0.0;
+    if (wave == 0) {
+        x0 = lane < c ? F.y[min(lane, c - 1)] : 0.0;
+        d = F.dinv[min(lane, c - 1)];
     }
+#pragma unroll
+    for (int k = 0; k < 16; k++)
+        if (4 * k + wave < c && lane < c) Ls[(4 * k + wave) * ldl + lane] = t[k];
     __syncthreads();
-    if (tid < 64) {
-        double x0 = lane < c ? t[lane] : 0.0, x1 = 0.0;
-        const double d = dv[min(lane, c - 1)];
+    if (wave == 0) {
         double a[4][16];
         tri_bwd_load(a, Ls, ldl, c, lane);
         tri_bwd_wave(a, Ls, ldl, c, d, d, x0, x1, lane);
@@ -4151,11 +4263,17 @@ void launch_big_factor(const InstDev* insts, const FrontDesc* fds, int nitems, i
         k_big_tiles<<<dim3(nitems, std::max(1, (ntile + wpg - 1) / wpg)), kBigThreads, 0, st>>>(insts, fds, kb);
     }
 }
-void launch_big_fwd(const InstDev* insts, const FrontDesc* fds, int nitems, int skip_done, hipStream_t st) {
-    if (nitems > 0) k_big_fwd<<<nitems, kBigThreads, 0, st>>>(insts, fds, skip_done);
+void launch_big_fwd(const InstDev* insts, const FrontDesc* fds, int nitems, int max_rows, int skip_done, hipStream_t st) {
+    if (nitems <= 0) return;
+    k_big_fwd<<<nitems, kBigThreads, 0, st>>>(insts, fds, skip_done);
+    const int nb = (max_rows + kBigThreads - 1) / kBigThreads;
+    k_big_fwd_rows<<<dim3(nitems, nb), kBigThreads, 0, st>>>(fds, skip_done);
 }
-void launch_big_bwd(const FrontDesc* fds, int nitems, int skip_done, hipStream_t st) {
-    if (nitems > 0) k_big_bwd<<<nitems, kBigThreads, 0, st>>>(fds, skip_done);
+void launch_big_bwd(const FrontDesc* fds, int nitems, int max_cols, int skip_done, hipStream_t st) {
+    if (nitems <= 0) return;
+    const int wpg = kBigThreads / 64;
+    k_big_bwd_dot<<<dim3(nitems, (max_cols + wpg - 1) / wpg), kBigThreads, 0, st>>>(fds, skip_done);
+    k_big_bwd<<<nitems, kBigThreads, 0, st>>>(fds, skip_done);
 }
 void launch_update(const InstDev* insts, const FrontDesc* fds, const StripItem* items, int nitems, hipStream_t st) {
     if (nitems > 0) k_update<<<nitems, kUpdThreads, 0, st>>>(insts, fds, items);

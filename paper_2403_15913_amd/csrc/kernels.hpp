@@ -113,8 +113,8 @@ void launch_factor_small(const InstDev* insts, const FrontDesc* fds, int nitems,
 // max_cols / max_rows bound the fronts of the launch)
 void launch_big_factor(const InstDev* insts, const FrontDesc* fds, int nitems, int max_cols, int max_rows,
                        hipStream_t st);
-void launch_big_fwd(const InstDev* insts, const FrontDesc* fds, int nitems, int skip_done, hipStream_t st);
-void launch_big_bwd(const FrontDesc* fds, int nitems, int skip_done, hipStream_t st);
+void launch_big_fwd(const InstDev* insts, const FrontDesc* fds, int nitems, int max_rows, int skip_done, hipStream_t st);
+void launch_big_bwd(const FrontDesc* fds, int nitems, int max_cols, int skip_done, hipStream_t st);
 // update matrices by 16-column strips (after the factor launch of the same level)
 void launch_update(const InstDev* insts, const FrontDesc* fds, const StripItem* items, int nitems, hipStream_t st);
 void launch_factor_queue(const InstDev* insts, const FrontDesc* fds, const DepLists& D, int grid, size_t lds,
