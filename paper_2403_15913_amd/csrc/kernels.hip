@@ -3665,14 +3665,6 @@ __device__ __forceinline__ double recip_f64(double d) {
     return r;
 }
 
-// the value of v in lane `lane` (uniform), through the scalar unit
-__device__ __forceinline__ double readlane_f64(double v, int lane) {
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane((int)b, lane);
-    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
 __global__ void k_fill_f64(double* __restrict__ p, double v, int64_t n) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = v;
@@ -3907,6 +3899,58 @@ __global__ __launch_bounds__(256) void k_cr_factor(const InstDev* __restrict__ i
         }
 }
 
+// L y = t by one wave (s columns, column-major with s rows in LDS): lane l
+// carries rows l and l + 64 in t0 and t1 and their pivot reciprocals in d0
+// and d1; steps as in fwd_steps, a block's coefficients read while the block
+// before it is solved
+template <int K0, bool TAIL, bool HI>
+__device__ __forceinline__ void cr_steps(double& t, double& th, double& y, const double (&a)[16],
+                                         const double (&ah)[16], const double d, const int l0, const int nb) {
+    static_for<4>([&](auto K) {
+        constexpr int k = K0 + K;
+        double v = readlane_d(t * d, l0 + k);
+        if (TAIL) v = k < nb ? v : 0.0;
+        y = writelane_d(v, l0 + k, y);
+        t = fma(-a[k], v, t);
+        if constexpr (HI) th = fma(-ah[k], v, th);
+    });
+}
+__device__ __forceinline__ void tri_fwd_wave(const double* __restrict__ L, const int s, const double d0,
+                                             const double d1, double& t0, double& t1, const int lane) {
+    static_assert(kCrMaxStage <= 128, "two rows per lane");
+    double y0 = 0.0, y1 = 0.0;
+    const double *const p0 = L + min(lane, s - 1), *const p1 = L + min(lane + 64, s - 1);
+    double a[2][16], b[2][16];
+    auto load = [&](auto Q, const int j) {
+#pragma unroll
+        for (int k = 0; k < 16; k++) {
+            a[Q][k] = p0[min(j + k, s - 1) * s];
+            b[Q][k] = p1[min(j + k, s - 1) * s];
+        }
+    };
+    load(std::integral_constant<int, 0>{}, 0);
+    static_for<4>([&](auto B) {
+        const int nb = s - 16 * B;
+        if (nb > 0) {
+            load(std::integral_constant<int, (B + 1) & 1>{}, 16 * B + 16);
+            static_for<4>([&](auto R) {
+                if (nb >= 4 * R + 4) cr_steps<4 * R, false, true>(t0, t1, y0, a[B & 1], b[B & 1], d0, 16 * B, nb);
+                else if (nb > 4 * R) cr_steps<4 * R, true, true>(t0, t1, y0, a[B & 1], b[B & 1], d0, 16 * B, nb);
+            });
+        }
+    });
+    for (int j = 64; j < s; j += 16) {
+        const int nb = s - j;
+        if (j > 64) load(std::integral_constant<int, 0>{}, j);
+        static_for<4>([&](auto R) {
+            if (nb >= 4 * R + 4) cr_steps<4 * R, false, false>(t1, t1, y1, b[0], b[0], d1, j - 64, nb);
+            else if (nb > 4 * R) cr_steps<4 * R, true, false>(t1, t1, y1, b[0], b[0], d1, j - 64, nb);
+        });
+    }
+    t0 = y0;
+    t1 = y1;
+}
+
 // Stages L_k (s_k x s_k, column-major) into LDS: every thread issues its
 // loads before the first store.
 __device__ inline void cr_stage_block(double* __restrict__ dst, const double* __restrict__ src, int n) {
@@ -3966,8 +4010,8 @@ __device__ inline void cr_matvec_t_part(const double* __restrict__ P, int prow, 
 
 // Forward solve L y = b, per level: a task eliminating its stage takes t_k -
 // the previous level's contributions, then y_k = L_k^{-1} t_k by
-// substitution in wave 0 (lane i holds rows i and i + 64, the pivot value is
-// broadcast by a lane shuffle, the pivots' reciprocals come from LDS); a
+// substitution in wave 0 (tri_fwd_wave: 12.9 us a launch of few stages of 66,
+// 18.5 with one LDS column read ahead per step); a
 // task of a stage that stays only subtracts the contributions. On
 // level 0 t_k starts from b (mode 0) or the refinement residual (mode 1,
 // stopped instances skipped); later levels from t.
@@ -3999,21 +4043,7 @@ __global__ __launch_bounds__(256) void k_cr_fwd(const InstDev* __restrict__ inst
     double t0 = i0 < sk ? src[i0] - ((red[0][i0] + red[1][i0]) + (red[2][i0] + red[3][i0])) : 0.0;
     double t1 = i1 < sk ? src[i1] - ((red[0][i1] + red[1][i1]) + (red[2][i1] + red[3][i1])) : 0.0;
     if (elim) {
-        // column j + 1 of L is read while step j runs (rows clamped into the
-        // block; their values are not used past s_k)
-        const int c0 = min(i0, sk - 1), c1 = min(i1, sk - 1);
-        double l0 = Ls[c0], l1 = Ls[c1], iv = inv[0];
-        for (int j = 0; j < sk; j++) {
-            const int jn = j + 1 < sk ? j + 1 : j;
-            const double l0n = Ls[jn * sk + c0], l1n = Ls[jn * sk + c1], ivn = inv[jn];
-            const double tj = j < 64 ? readlane_f64(t0, j) : readlane_f64(t1, j - 64);
-            const double yj = tj * iv;
-            t0 = i0 == j ? yj : (i0 > j ? fma(-l0, yj, t0) : t0);
-            t1 = i1 == j ? yj : (i1 > j ? fma(-l1, yj, t1) : t1);
-            l0 = l0n;
-            l1 = l1n;
-            iv = ivn;
-        }
+        tri_fwd_wave(Ls, sk, inv[min(i0, sk - 1)], inv[min(i1, sk - 1)], t0, t1, r);
     }
     if (i0 < sk) AR.t[T.v0 + i0] = t0;
     if (i1 < sk) AR.t[T.v0 + i1] = t1;
@@ -4021,7 +4051,9 @@ __global__ __launch_bounds__(256) void k_cr_fwd(const InstDev* __restrict__ inst
 
 // Backward solve L^T x = y, levels in reverse, eliminated stages only: x_k =
 // L_k^{-T} (y_k - L(l,k)^T x_l - L(r,k)^T x_r), the neighbours being
-// eliminated later (their x already in t). x_k goes to t and to the output:
+// eliminated later (their x already in t), the triangle as in the supernodal
+// sweep (10.3 us a launch of few stages of 66, 16.7 step by step from LDS).
+// x_k goes to t and to the output:
 // mode 0 x = x_k; mode 1 xprev = x, x += x_k.
 __global__ __launch_bounds__(256) void k_cr_bwd(const InstDev* __restrict__ insts, CrArrays AR, int task0, Calls C,
                                                 int mode) {
@@ -4044,20 +4076,9 @@ __global__ __launch_bounds__(256) void k_cr_bwd(const InstDev* __restrict__ inst
     const int i0 = r, i1 = r + 64;
     double t0 = i0 < sk ? AR.t[T.v0 + i0] - ((red[0][i0] + red[1][i0]) + (red[2][i0] + red[3][i0])) : 0.0;
     double t1 = i1 < sk ? AR.t[T.v0 + i1] - ((red[0][i1] + red[1][i1]) + (red[2][i1] + red[3][i1])) : 0.0;
-    // row j of L (entries L(j, i), i < j) is read one step ahead
-    const int c0 = min(i0, sk - 1), c1 = min(i1, sk - 1);
-    double l0 = Ls[c0 * sk + sk - 1], l1 = Ls[c1 * sk + sk - 1], iv = inv[sk - 1];
-    for (int j = sk - 1; j >= 0; j--) {
-        const int jn = j > 0 ? j - 1 : 0;
-        const double l0n = Ls[c0 * sk + jn], l1n = Ls[c1 * sk + jn], ivn = inv[jn];
-        const double tj = j < 64 ? readlane_f64(t0, j) : readlane_f64(t1, j - 64);
-        const double xj = tj * iv;
-        t0 = i0 == j ? xj : (i0 < j ? fma(-l0, xj, t0) : t0);
-        t1 = i1 == j ? xj : (i1 < j ? fma(-l1, xj, t1) : t1);
-        l0 = l0n;
-        l1 = l1n;
-        iv = ivn;
-    }
+    double a[4][16];
+    tri_bwd_load(a, Ls, sk, sk, r);
+    tri_bwd_wave(a, Ls, sk, sk, inv[min(i0, sk - 1)], inv[min(i1, sk - 1)], t0, t1, r);
     double* x = C.x + T.v0;
     if (i0 < sk) {
         AR.t[T.v0 + i0] = t0;
