@@ -532,7 +532,7 @@ kkt_status Engine::place(const std::vector<const Symbolic*>& s, const std::vecto
     size_t up_bytes = 0;
     for (auto& pc : pieces) up_bytes += pc.bytes;
     // read-back area: error latch, status words, refinement or CG records
-    const size_t readback = 128 + (size_t)ninst * (8 + std::max(sizeof(RefineState), sizeof(CgState))) + 64;
+    const size_t readback = 128 + (size_t)ninst * (8 + std::max(sizeof(RefineReport), sizeof(CgState))) + 64;
     hipError_t e = ensure_pinned(std::max(up_bytes, readback));
     if (e != hipSuccess) return hip_fail(e, "pinned host buffer");
     // one packed staging buffer, one copy per piece
@@ -738,17 +738,17 @@ kkt_status Engine::parse_status(int derr, const int* hs, int* st_out, int* bad_o
 
 // first solve from the right-hand side (refinement state reset)
 void Engine::solve_start(const Calls& C, int maxit, double tol, hipStream_t st) {
-    TL(KKT_PHASE_CONTROL, launch_refine_reset(di(), ninst, tol, maxit, st));
-    TL(KKT_PHASE_CONTROL, launch_fill_i32(ndone, 0, 1, st));
+    TL(KKT_PHASE_CONTROL, launch_refine_reset(di(), ninst, tol, maxit, ndone, st));
     TL(KKT_PHASE_PERMUTE, launch_perm_in(di(), C, nitems, n_nitems, PIN_B, st));
     sweeps(st, SKIP_NONE);
     TL(KKT_PHASE_PERMUTE, launch_perm_out(di(), C, nitems, n_nitems, POUT_X, st));
 }
 
 // residual + stop decision of every instance still refining
-void Engine::refine_check(const Calls& C, hipStream_t st) {
+// (report: into the pinned buffer, where the host reads it after the stream)
+void Engine::refine_check(const Calls& C, bool report, hipStream_t st) {
     TL(KKT_PHASE_RESIDUAL, launch_residual(di(), C, nitems, n_nitems, st));
-    TL(KKT_PHASE_CONTROL, launch_refine_decide(di(), ninst, ndone, st));
+    TL(KKT_PHASE_CONTROL, launch_refine_decide(di(), ninst, ndone, report ? (RefineReport*)hpin : nullptr, deps().err, st));
 }
 
 // one correction x += K^{-1} r of every instance still refining
@@ -769,10 +769,10 @@ kkt_status Engine::solve(const Calls& C, int maxit, double tol, kkt_solve_info* 
 // sweeps of an instance that has stopped return at once, so the result is
 // the same bit for bit and nothing is read back.
 void Engine::solve_rounds(const Calls& C, int maxit, hipStream_t st) {
-    refine_check(C, st);
+    refine_check(C, false, st);
     for (int q = 0; q < maxit; q++) {
         refine_correct(C, st);
-        refine_check(C, st);
+        refine_check(C, false, st);
     }
     TL(KKT_PHASE_PERMUTE, launch_refine_revert(di(), C, nitems, n_nitems, st));
 }
@@ -782,58 +782,46 @@ void Engine::solve_rounds(const Calls& C, int maxit, hipStream_t st) {
 // factor status and the per-instance reports.
 kkt_status Engine::solve_finish(const Calls& C, int iter0, int maxit, double tol, kkt_solve_info* infos,
                                 hipStream_t st) {
-    // With several instances, one round of lookahead: the next correction
-    // and check are queued before the host reads the current count of
-    // stopped instances, so the GPU does not idle on the round trip. Every
-    // refinement kernel skips stopped instances, so the extra queued round
-    // changes no result. A single instance reads its decision first (after
-    // its last correction a queued round would only delay the return).
-    volatile int* hp = (volatile int*)hpin;
+    // Every check's decision kernel writes the instances' reports to pinned
+    // memory, so one synchronisation per round carries all that the host
+    // needs (a copy of the stop count, then a launch, three copies and a second
+    // synchronisation at the end were 60 us of a 250 us solve). The next round
+    // is queued after the count is known: a round of lookahead leaves its
+    // launches to run idle in every solve, which costs more than the round
+    // trip (40 launches against 18 us on the 20-level batch).
+    const RefineReport* const hr = (const RefineReport*)hpin;
     hipError_t e = hipSuccess;
-    if (!ctl_event && (e = hipEventCreateWithFlags(&ctl_event, hipEventDisableTiming)) != hipSuccess)
-        return hip_fail(e, "refinement control event");
-    refine_check(C, st);
-    for (int iter = iter0; iter <= maxit + 1 && ninst == 1; iter++) {
-        if ((e = hipMemcpyAsync((void*)hp, ndone, 4, hipMemcpyDeviceToHost, st)) != hipSuccess ||
-            (e = hipStreamSynchronize(st)) != hipSuccess)
-            return hip_fail(e, "refinement control");
-        if (hp[0] >= ninst) break;
+    bool revert = false;
+    for (int iter = iter0;; iter++) {
+        refine_check(C, true, st);
+        if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "solve launch");
+        if ((e = hipStreamSynchronize(st)) != hipSuccess) return hip_fail(e, "refinement control");
+        int stopped = 0;
+        for (int q = 0; q < ninst; q++) stopped += hr[q].rs.done != 0;
+        if (stopped >= ninst || iter > maxit) break;
         refine_correct(C, st);
-        refine_check(C, st);
     }
-    for (int iter = iter0; iter <= maxit + 1 && ninst > 1; iter++) {
-        // ndone after the check of round iter
-        if ((e = hipMemcpyAsync((void*)hp, ndone, 4, hipMemcpyDeviceToHost, st)) != hipSuccess ||
-            (e = hipEventRecord(ctl_event, st)) != hipSuccess)
-            return hip_fail(e, "refinement control");
-        refine_correct(C, st);
-        refine_check(C, st);
-        if ((e = hipEventSynchronize(ctl_event)) != hipSuccess) return hip_fail(e, "refinement control");
-        if (hp[0] >= ninst) break;
+    for (int q = 0; q < ninst; q++) revert = revert || hr[q].rs.revert != 0;
+    if (revert) {
+        TL(KKT_PHASE_PERMUTE, launch_refine_revert(di(), C, nitems, n_nitems, st));
+        if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "solve launch");
+        if ((e = hipStreamSynchronize(st)) != hipSuccess) return hip_fail(e, "solve read-back");
     }
-    TL(KKT_PHASE_PERMUTE, launch_refine_revert(di(), C, nitems, n_nitems, st));
-    e = hipGetLastError();
-    if (e != hipSuccess) return hip_fail(e, "solve launch");
-    // One synchronisation: the error latch, the status words and the
-    // refinement records are copied behind the queued work, then read.
-    char* hb = (char*)hpin;
-    int* hderr = (int*)hb;
-    const int* hs = (const int*)(hb + 64);
-    const RefineState* hr = (const RefineState*)(hb + 64 + (((size_t)ninst * 8 + 63) & ~(size_t)63));
-    if ((e = hipMemcpyAsync(hderr, deps().err, sizeof(int), hipMemcpyDeviceToHost, st)) != hipSuccess ||
-        (e = hipMemcpyAsync((void*)hs, status, (size_t)ninst * 8, hipMemcpyDeviceToHost, st)) != hipSuccess ||
-        (infos && (e = hipMemcpyAsync((void*)hr, rs, (size_t)ninst * sizeof(RefineState), hipMemcpyDeviceToHost,
-                                      st)) != hipSuccess) ||
-        (e = hipStreamSynchronize(st)) != hipSuccess)
-        return hip_fail(e, "solve read-back");
     // a failed factor makes the solve meaningless: report it
-    kkt_status fst = parse_status(*hderr, hs, nullptr, nullptr);
+    int derr = 0;
+    hstat.resize(2 * (size_t)ninst);
+    for (int q = 0; q < ninst; q++) {
+        derr |= hr[q].err;
+        hstat[2 * q] = hr[q].status[0];
+        hstat[2 * q + 1] = hr[q].status[1];
+    }
+    kkt_status fst = parse_status(derr, hstat.data(), nullptr, nullptr);
     if (fst == KKT_ERR_DEVICE || fst == KKT_ERR_OOM) return fst;
     if (fst != KKT_OK) return fail(fst, "factor failed; solve result invalid");
     if (!infos) return KKT_OK;
     kkt_status worst = KKT_OK;
     for (int q = 0; q < ninst; q++) {
-        const RefineState& S = hr[q];
+        const RefineState& S = hr[q].rs;
         const bool rev = S.revert != 0;
         kkt_solve_info& inf = infos[q];
         inf.iters = rev ? S.it - 1 : S.it;
@@ -872,7 +860,7 @@ kkt_status Engine::capture(const Calls& C, int maxit, double tol, int rounds) {
     if (ks == KKT_OK) {
         solve_start(C, maxit, tol, st);
         for (int q = 0; q < rounds; q++) {
-            refine_check(C, st);
+            refine_check(C, false, st);
             refine_correct(C, st);
         }
     }
@@ -1020,10 +1008,12 @@ kkt_status Engine::solve_augmented(const AugCall& A, int maxit, double tol, kkt_
         solve_start(Ct, 0, 0.0, st);
         TL(KKT_PHASE_RESIDUAL, launch_aug_recover(di(), A, nitems, n_nitems, mitems, n_mitems, 1, st));
     }
-    TL(KKT_PHASE_PERMUTE, launch_aug_revert(di(), A, nitems, n_nitems, mitems, n_mitems, st));
-    if ((e = hipGetLastError()) != hipSuccess || (e = hipStreamSynchronize(st)) != hipSuccess)
-        return hip_fail(e, "augmented solve");
     const bool rev = S.revert != 0;
+    if (!S.done || rev) {  // (the check that stopped the rounds has been waited for)
+        TL(KKT_PHASE_PERMUTE, launch_aug_revert(di(), A, nitems, n_nitems, mitems, n_mitems, st));
+        if ((e = hipGetLastError()) != hipSuccess || (e = hipStreamSynchronize(st)) != hipSuccess)
+            return hip_fail(e, "augmented solve");
+    }
     const double om = rev ? S.omega_prev : S.omega;
     if (info) {
         info->iters = rev ? S.it - 1 : S.it;

@@ -138,6 +138,7 @@ struct Engine {
     int n_nitems = 0, n_mitems = 0, n_kitems = 0, n_jitems = 0, n_hitems = 0;
     size_t lds_factor = 0, lds_solve = 0;
     std::vector<int64_t> n_ofs, m_ofs, w_ofs, j_ofs;  // ninst + 1 prefix offsets
+    std::vector<int> hstat;                            // status pairs of the last solve's reports
     void* hpin = nullptr;                              // pinned host staging (uploads, readback)
     size_t hpin_bytes = 0;
     LaunchTimer timer;
@@ -166,7 +167,7 @@ struct Engine {
     // Lifted-KKT solve with refinement; infos (ninst entries) filled when non-NULL.
     kkt_status solve(const Calls& C, int maxit, double tol, kkt_solve_info* infos, hipStream_t st);
     void solve_start(const Calls& C, int maxit, double tol, hipStream_t st);
-    void refine_check(const Calls& C, hipStream_t st);
+    void refine_check(const Calls& C, bool report, hipStream_t st);
     void refine_correct(const Calls& C, hipStream_t st);
     kkt_status solve_finish(const Calls& C, int iter0, int maxit, double tol, kkt_solve_info* infos,
                             hipStream_t st);

@@ -92,6 +92,15 @@ struct RefineState {
     int revert;    // 1: the previous iterate is the better one
 };
 
+// what the host reads of one instance after a refinement check, written by
+// the decision kernel into pinned host memory: the refinement record, the
+// factor status pair and the queue schedule's error latch
+struct RefineReport {
+    RefineState rs;
+    int status[2];
+    int err;
+};
+
 // Conjugate-gradient record of one instance (eq. (schurcomp)), written by the
 // instance's workgroup 0 of the kernel that takes each decision.
 struct CgState {

@@ -2290,8 +2290,10 @@ __global__ __launch_bounds__(256) void k_perm_out(const InstDev* __restrict__ in
 // ---------------------------------------------------------------------------
 // residual r = b - K x and backward-error reductions (original numbering)
 // ---------------------------------------------------------------------------
-__global__ void k_refine_reset(const InstDev* __restrict__ insts, int ninst, double tol, int maxit) {
+__global__ void k_refine_reset(const InstDev* __restrict__ insts, int ninst, double tol, int maxit,
+                               int* __restrict__ ndone) {
     const int q = blockIdx.x * blockDim.x + threadIdx.x;
+    if (q == 0) *ndone = 0;
     if (q >= ninst) return;
     RefineState* S = insts[q].rs;
     S->omega = S->omega_prev = INFINITY;
@@ -2409,10 +2411,26 @@ __global__ __launch_bounds__(256) void k_residual(const InstDev* __restrict__ in
 // (order-independent), then eta / omega and the refinement stop rule
 // (omega <= tol, maxit corrections, or omega not halving; in the last case
 // the previous iterate wins if omega grew).
-__global__ __launch_bounds__(256) void k_refine_decide(const InstDev* __restrict__ insts, int* ndone) {
+// With rep, the instance's report goes to the host (also of an instance that
+// has stopped before: the host reads the reports of the last check only), so
+// no copy follows the check.
+__global__ __launch_bounds__(256) void k_refine_decide(const InstDev* __restrict__ insts, int* ndone,
+                                                       RefineReport* __restrict__ rep, const int* __restrict__ err) {
     const InstDev& I = insts[blockIdx.x];
     RefineState* S = I.rs;
-    if (S->done) return;  // uniform per block
+    auto report = [&]() {
+        if (!rep) return;
+        RefineReport r;
+        r.rs = *S;
+        r.status[0] = I.status[0];
+        r.status[1] = I.status[1];
+        r.err = *err;
+        rep[blockIdx.x] = r;
+    };
+    if (S->done) {  // uniform per block
+        if (threadIdx.x == 0) report();
+        return;
+    }
     const int nslots = ((I.P.n + 255) >> 8) * kResidualSplit;
     double m[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
     // eight slots per thread in flight at once; a maximum is unchanged by
@@ -2460,6 +2478,7 @@ __global__ __launch_bounds__(256) void k_refine_decide(const InstDev* __restrict
     } else {
         S->it += 1;
     }
+    report();
 }
 
 __global__ __launch_bounds__(256) void k_refine_revert(const InstDev* __restrict__ insts, Calls C,
@@ -4325,14 +4344,15 @@ void launch_perm_in(const InstDev* insts, const Calls& C, const WorkItem* rows, 
 void launch_perm_out(const InstDev* insts, const Calls& C, const WorkItem* rows, int nitems, int mode, hipStream_t st) {
     if (nitems > 0) k_perm_out<<<nitems, kBlock, 0, st>>>(insts, C, rows, mode);
 }
-void launch_refine_reset(const InstDev* insts, int ninst, double tol, int maxit, hipStream_t st) {
-    k_refine_reset<<<blocks_for(ninst, 64), 64, 0, st>>>(insts, ninst, tol, maxit);
+void launch_refine_reset(const InstDev* insts, int ninst, double tol, int maxit, int* ndone, hipStream_t st) {
+    k_refine_reset<<<blocks_for(ninst, 64), 64, 0, st>>>(insts, ninst, tol, maxit, ndone);
 }
 void launch_residual(const InstDev* insts, const Calls& C, const WorkItem* rows, int nitems, hipStream_t st) {
     if (nitems > 0) k_residual<<<nitems * kResidualSplit, kBlock, 0, st>>>(insts, C, rows);
 }
-void launch_refine_decide(const InstDev* insts, int ninst, int* ndone, hipStream_t st) {
-    if (ninst > 0) k_refine_decide<<<ninst, 256, 0, st>>>(insts, ndone);
+void launch_refine_decide(const InstDev* insts, int ninst, int* ndone, RefineReport* rep, const int* err,
+                          hipStream_t st) {
+    if (ninst > 0) k_refine_decide<<<ninst, 256, 0, st>>>(insts, ndone, rep, err);
 }
 void launch_refine_revert(const InstDev* insts, const Calls& C, const WorkItem* rows, int nitems, hipStream_t st) {
     if (nitems > 0) k_refine_revert<<<nitems, kBlock, 0, st>>>(insts, C, rows);

@@ -135,9 +135,11 @@ enum { SKIP_NONE = 0, SKIP_REFINE = 1, SKIP_CG = 2 };
 void launch_perm_in(const InstDev* insts, const Calls& C, const WorkItem* rows, int nitems, int mode, hipStream_t st);
 void launch_perm_out(const InstDev* insts, const Calls& C, const WorkItem* rows, int nitems, int mode, hipStream_t st);
 
-void launch_refine_reset(const InstDev* insts, int ninst, double tol, int maxit, hipStream_t st);
+void launch_refine_reset(const InstDev* insts, int ninst, double tol, int maxit, int* ndone, hipStream_t st);
 void launch_residual(const InstDev* insts, const Calls& C, const WorkItem* rows, int nitems, hipStream_t st);
-void launch_refine_decide(const InstDev* insts, int ninst, int* ndone, hipStream_t st);
+// (rep: one report per instance in pinned host memory, or null)
+void launch_refine_decide(const InstDev* insts, int ninst, int* ndone, RefineReport* rep, const int* err,
+                          hipStream_t st);
 void launch_refine_revert(const InstDev* insts, const Calls& C, const WorkItem* rows, int nitems, hipStream_t st);
 void launch_matvec(const InstDev* insts, const double* x, double* y, const WorkItem* rows, int nitems, hipStream_t st);
 

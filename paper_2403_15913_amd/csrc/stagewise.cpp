@@ -415,14 +415,13 @@ extern "C" kkt_status kkt_stagewise_solve(kkt_stagewise* w, const double* rhs, d
     std::memset(&C, 0, sizeof(C));
     C.b = rhs;
     C.x = x;
-    TL(KKT_PHASE_CONTROL, launch_refine_reset(E.di(), E.ninst, tol, maxit, st));
-    TL(KKT_PHASE_CONTROL, launch_fill_i32(E.ndone, 0, 1, st));
+    TL(KKT_PHASE_CONTROL, launch_refine_reset(E.di(), E.ninst, tol, maxit, E.ndone, st));
     cr_sweeps(w, C, 0, st);
     volatile int* hp = (volatile int*)E.hpin;
     hipError_t e = hipSuccess;
     for (int iter = 0; iter <= maxit + 1; iter++) {
         TL(KKT_PHASE_RESIDUAL, launch_residual(E.di(), C, E.nitems, E.n_nitems, st));
-        TL(KKT_PHASE_CONTROL, launch_refine_decide(E.di(), E.ninst, E.ndone, st));
+        TL(KKT_PHASE_CONTROL, launch_refine_decide(E.di(), E.ninst, E.ndone, nullptr, nullptr, st));
         if ((e = hipMemcpyAsync((void*)hp, E.ndone, 4, hipMemcpyDeviceToHost, st)) != hipSuccess ||
             (e = hipStreamSynchronize(st)) != hipSuccess)
             return hip_fail(e, "refinement control");
