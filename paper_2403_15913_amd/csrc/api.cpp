@@ -406,13 +406,14 @@ kkt_status Engine::place(const std::vector<const Symbolic*>& s, const std::vecto
             return solve_lds_bytes(A.sn_nrow[a.id], A.sn_ncol[a.id]) > solve_lds_bytes(B.sn_nrow[b.id], B.sn_ncol[b.id]);
         };
         std::stable_sort(sn.begin() + b0, sn.begin() + bl, by_size);
-        SweepPart part{b0, bl - b0, 0, 0, 0};
+        SweepPart part{b0, bl - b0, 0, 0, 0, 0};
         for (int t = b0; t < bl; t++) {
             const Symbolic& S = *s[sn[t].inst];
             const int r = S.sn_nrow[sn[t].id], c = S.sn_ncol[sn[t].id];
             part.maxr = std::max(part.maxr, r);
             part.lds_fwd = std::max(part.lds_fwd, (size_t)fwd_lds_bytes(r, c));
             part.lds_bwd = std::max(part.lds_bwd, (size_t)bwd_lds_bytes(r, c));
+            part.lds_wide = std::max(part.lds_wide, (size_t)bwd_wide_lds_bytes(r, c));
         }
         if (part.count > 0) sw_part.push_back(part);
         sw_maxr = std::max(sw_maxr, part.maxr);
@@ -705,9 +706,15 @@ void Engine::sweeps(hipStream_t st, int skip_done) {
             TL(KKT_PHASE_BWD, launch_big_bwd(fdesc + lvl_large[l], lvl_ptr[l + 1] - lvl_large[l], lvl_lmaxc[l], skip_done, st));
         for (int k = sw_lvl[l]; k < sw_lvl[l + 1]; k++) {
             const SweepPart& P = sw_part[k];
-            // (chosen as in the forward sweep: one form for the levels of few fronts)
+            // light panels chosen as in the forward sweep (one form for the
+            // levels of few fronts); panels that leave a compute unit room for
+            // one workgroup and a level of more fronts than compute units: two
+            // workgroups share a unit with only the triangle in LDS (512 fronts
+            // of 79 x 227: 24 -> 18 us; on a level of 129 fronts 8.3 -> 10.6)
             const bool light = P.lds_bwd <= kSweepHalfLds && (sw_maxlds <= kSweepHalfLds || P.count >= 512);
-            TL(KKT_PHASE_BWD, launch_bwd(fdesc + P.begin, P.count, light, P.lds_bwd, skip_done, st));
+            const bool wide = P.lds_bwd > kSweepHalfLds && P.lds_wide <= kSweepHalfLds && P.count > kSweepWideMin;
+            TL(KKT_PHASE_BWD, launch_bwd(fdesc + P.begin, P.count, wide ? BWD_WIDE : light ? BWD_LIGHT : BWD_PANEL,
+                                         wide ? P.lds_wide : P.lds_bwd, skip_done, st));
         }
     }
 }

@@ -2028,6 +2028,191 @@ __device__ __forceinline__ void bwd_front(const FrontDesc& F, double* __restrict
     }
 }
 
+// sum of a column's 4 G strands (strand g + G q holds rows g + G q, g + G q +
+// 4 G, ... of the column): the four strands of each g, then g by halves
+template <int G>
+__device__ __forceinline__ double strand_sum(const double* __restrict__ w) {
+    double p[G];
+#pragma unroll
+    for (int g = 0; g < G; g++) p[g] = (w[g] + w[g + G]) + (w[g + 2 * G] + w[g + 3 * G]);
+#pragma unroll
+    for (int h = G >> 1; h > 0; h >>= 1)
+#pragma unroll
+        for (int g = 0; g < h; g++) p[g] += p[g + h];
+    return p[0];
+}
+
+// Backward step of one front of a level of more fronts than compute units: the
+// rectangle goes from HBM to registers straight into the dot products (a lane
+// holds two neighbouring strands of a column: 8 strands a column above 64
+// columns, 16, 32 or 64 at most 64, 32, 16, so two passes cover every front)
+// and only the triangle is staged in LDS, so two workgroups share a compute
+// unit where a whole panel leaves room for one. Every sum takes the order of
+// bwd_front (same bits). Bound by HBM and the address unit (16 cycles a load).
+__device__ __forceinline__ void bwd_front_wide(const FrontDesc& F, double* __restrict__ sh) {
+    constexpr int nt = kSolveThreads, NT = 6, NP = 2;
+    const int c = F.c, r = F.r, u = r - c;
+    double* const yb = F.y - F.col0;  // the instance's work vector
+    const int ld = r | 1, ldt = c | 1;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lg = c <= 16 ? 4 : c <= 32 ? 3 : c <= 64 ? 2 : 1, G = 1 << lg, S = 4 * G;
+    double* const P = sh;
+    double* const z = P + even_up(ldt * c);
+    double* const w = z + even_up(u);
+    const int* const rw = F.rw;
+    const double* const Pl = F.L;
+    // loads, before the first wait: the update rows' indices (the gather of
+    // their values waits for them alone), the first rows of the strands and
+    // 64 columns of the triangle
+    const int ri = u > 0 ? rw[min(tid, u - 1)] : 0;
+    const int cpp = nt >> (lg + 1);  // columns per pass
+    const int e = 2 * (tid & (2 * G - 1)), col = tid >> (lg + 1), g = e & (G - 1);
+    const int wcol = (64 * wave) >> (lg + 1);  // the wave's first
+    rows2 v0[NP][NT], v1[NP][NT];
+    auto load = [&](rows2 (&v)[NP][NT], const int t0) {
+        static_for<NP>([&](auto p) {
+            if (p * cpp + wcol < c) {
+                const double* const b = Pl + (min(p * cpp + col, c - 1) * ld + c);
+#pragma unroll
+                for (int t = 0; t < NT; t++) v[p][t] = *(const rows2*)(b + min(e + S * (t0 + t), u - 1));
+            }
+        });
+    };
+    const int nT = (u + S - 1) >> (lg + 2);  // rows per strand, at most
+    if (u > 0) load(v0, 0);
+    rows2 ta[16];
+    auto tri_load = [&](const int j0) {
+#pragma unroll
+        for (int k = 0; k < 16; k++)
+            if (j0 + 4 * k + wave < c)
+                ta[k] = rows_at(Pl + (j0 + 4 * k + wave) * ld, min(2 * lane, (c - 1) & ~1));
+    };
+    auto tri_store = [&](const int j0) {
+#pragma unroll
+        for (int k = 0; k < 16; k++) {
+            const int j = j0 + 4 * k + wave;
+            if (j < c) {
+                double* const d = P + j * ldt + 2 * lane;
+                if (2 * lane < c) d[0] = ta[k].x;
+                if (2 * lane + 1 < c) d[1] = ta[k].y;
+            }
+        }
+    };
+    tri_load(0);
+    double d0 = 0.0, d1 = 0.0, y0 = 0.0, y1 = 0.0;
+    if (wave == 0) {
+        d0 = F.dinv[min(lane, c - 1)];
+        d1 = F.dinv[min(lane + 64, c - 1)];
+        y0 = F.y[min(lane, c - 1)];
+        y1 = F.y[min(lane + 64, c - 1)];
+    }
+    const double zy = u > 0 ? yb[ri] : 0.0;
+    if (nT > NT) load(v1, NT);
+    tri_store(0);
+    if (c > 64) tri_load(64);
+    if (tid < u) z[tid] = zy;
+    for (int i = tid + nt; i < u; i += nt) z[i] = yb[rw[i]];
+    __syncthreads();
+    // t = y1 - L21^T z. Lane g of a column's G takes rows four G at a time,
+    // one per strand, while four are left (T steps); what remains of its rows
+    // goes to its first strand.
+    auto steps = [&](const int g) { return u - 3 * G - g > 0 ? (u - 3 * G - g + S - 1) >> (lg + 2) : 0; };
+    const int T0 = steps(g), T1 = steps(g + 1);
+    double s0[NP] = {0.0, 0.0}, s1[NP] = {0.0, 0.0};
+    if (u > 0) {
+        auto terms = [&](const rows2 (&v)[NP][NT], const int t0) {
+            double za[NT], zb[NT];
+#pragma unroll
+            for (int t = 0; t < NT; t++) {
+                const int i = min(e + S * (t0 + t), (u - 1) & ~1);
+                za[t] = z[i];
+                zb[t] = z[i + 1];
+            }
+#pragma unroll
+            for (int t = 0; t < NT; t++) {
+                za[t] = t0 + t < T0 ? za[t] : 0.0;
+                zb[t] = t0 + t < T1 ? zb[t] : 0.0;
+            }
+            static_for<NP>([&](auto p) {
+                if (p * cpp + wcol < c) {
+#pragma unroll
+                    for (int t = 0; t < NT; t++) {
+                        s0[p] = fma(t0 + t < T0 ? v[p][t].x : 0.0, za[t], s0[p]);
+                        s1[p] = fma(t0 + t < T1 ? v[p][t].y : 0.0, zb[t], s1[p]);
+                    }
+                }
+            });
+        };
+        double ra[NP][3], rb[NP][3];
+        const int i0 = g + S * T0, i1 = g + 1 + S * T1;
+        if (e < G) {
+            static_for<NP>([&](auto p) {
+                if (p * cpp + wcol < c) {
+                    const double* const b = Pl + (min(p * cpp + col, c - 1) * ld + c);
+#pragma unroll
+                    for (int k = 0; k < 3; k++) {
+                        ra[p][k] = b[min(i0 + G * k, u - 1)];
+                        rb[p][k] = b[min(i1 + G * k, u - 1)];
+                    }
+                }
+            });
+        }
+        for (int t0 = 0; t0 < nT; t0 += 2 * NT) {
+            terms(v0, t0);
+            if (t0 + 2 * NT < nT) load(v0, t0 + 2 * NT);
+            if (t0 + NT < nT) terms(v1, t0 + NT);
+            if (t0 + 3 * NT < nT) load(v1, t0 + 3 * NT);
+        }
+        if (e < G) {
+            double za[3], zb[3];
+#pragma unroll
+            for (int k = 0; k < 3; k++) {
+                za[k] = i0 + G * k < u ? z[i0 + G * k] : 0.0;
+                zb[k] = i1 + G * k < u ? z[i1 + G * k] : 0.0;
+            }
+            static_for<NP>([&](auto p) {
+                if (p * cpp + wcol < c) {
+#pragma unroll
+                    for (int k = 0; k < 3; k++) {
+                        s0[p] = fma(ra[p][k], za[k], s0[p]);
+                        s1[p] = fma(rb[p][k], zb[k], s1[p]);
+                    }
+                }
+            });
+        }
+    }
+    if (c > 64) tri_store(64);
+    const int ws = S + 1;
+#pragma unroll
+    for (int p = 0; p < NP; p++)
+        if (p * cpp + col < c) {
+            w[(p * cpp + col) * ws + e] = s0[p];
+            w[(p * cpp + col) * ws + e + 1] = s1[p];
+        }
+    __syncthreads();
+    if (wave == 0) {
+        double x0 = 0.0, x1 = 0.0;
+        const double* const w0 = w + min(lane, c - 1) * ws;
+        if (G == 2) {
+            x0 = strand_sum<2>(w0);
+            x1 = strand_sum<2>(w + min(lane + 64, c - 1) * ws);
+        } else if (G == 4) {
+            x0 = strand_sum<4>(w0);
+        } else if (G == 8) {
+            x0 = strand_sum<8>(w0);
+        } else {
+            x0 = strand_sum<16>(w0);
+        }
+        x0 = lane < c ? y0 - x0 : 0.0;
+        x1 = lane + 64 < c ? y1 - x1 : 0.0;
+        double a[4][16];
+        tri_bwd_load(a, P, ldt, c, lane);
+        tri_bwd_wave(a, P, ldt, c, d0, d1, x0, x1, lane);
+        if (lane < c) F.y[lane] = x0;
+        if (lane + 64 < c) F.y[lane + 64] = x1;
+    }
+}
+
 // Forward sweep of large fronts. k_big_fwd, one workgroup per front: the
 // children's update vectors are added child by child (the update part in the
 // front's own HBM slot), the c x c triangle is solved by one wave, its
@@ -2211,6 +2396,13 @@ __global__ __launch_bounds__(kSolveThreads) void k_bwd(const FrontDesc* __restri
     const FrontDesc& F = fds[blockIdx.x];
     if (front_idle(F, skip_done)) return;
     bwd_front<PU>(F, sh);
+}
+
+__global__ __launch_bounds__(kSolveThreads, 2) void k_bwd_wide(const FrontDesc* __restrict__ fds, int skip_done) {
+    extern __shared__ __align__(16) double sh[];
+    const FrontDesc& F = fds[blockIdx.x];
+    if (front_idle(F, skip_done)) return;
+    bwd_front_wide(F, sh);
 }
 
 // Both sweeps in one launch: tickets 0..N-1 are the forward sweep in
@@ -4171,7 +4363,7 @@ hipError_t set_kernel_attributes() {
     if (e != hipSuccess) return e;
     e = hipFuncSetAttribute((const void*)k_cr_factor<5>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
-    for (const void* k : {(const void*)k_fwd<64>, (const void*)k_fwd<128>, (const void*)k_fwd<256>, (const void*)k_sweeps_queue, (const void*)k_bwd<16>, (const void*)k_bwd<32>})
+    for (const void* k : {(const void*)k_fwd<64>, (const void*)k_fwd<128>, (const void*)k_fwd<256>, (const void*)k_sweeps_queue, (const void*)k_bwd<16>, (const void*)k_bwd<32>, (const void*)k_bwd_wide})
         if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxSweepLds);
     return e;
 }
@@ -4333,9 +4525,10 @@ void launch_fwd(const InstDev* insts, const FrontDesc* fds, int nitems, int maxr
     else if (maxr <= 256) k_fwd<128><<<nitems, 128, lds, st>>>(insts, fds, skip_done);
     else k_fwd<256><<<nitems, 256, lds, st>>>(insts, fds, skip_done);
 }
-void launch_bwd(const FrontDesc* fds, int nitems, bool light, size_t lds, int skip_done, hipStream_t st) {
+void launch_bwd(const FrontDesc* fds, int nitems, int form, size_t lds, int skip_done, hipStream_t st) {
     if (nitems <= 0) return;
-    if (light) k_bwd<16><<<nitems, kSolveThreads, lds, st>>>(fds, skip_done);
+    if (form == BWD_WIDE) k_bwd_wide<<<nitems, kSolveThreads, lds, st>>>(fds, skip_done);
+    else if (form == BWD_LIGHT) k_bwd<16><<<nitems, kSolveThreads, lds, st>>>(fds, skip_done);
     else k_bwd<32><<<nitems, kSolveThreads, lds, st>>>(fds, skip_done);
 }
 void launch_perm_in(const InstDev* insts, const Calls& C, const WorkItem* rows, int nitems, int mode, hipStream_t st) {

@@ -56,6 +56,8 @@ constexpr int kMaxDynLds = 158 * 1024;
 // backward sweep fronts at or below this LDS size run two workgroups per
 // compute unit (160 KiB of LDS per CU)
 constexpr size_t kSweepHalfLds = 79 * 1024;
+// levels of more fronts than this (one per compute unit) take the wide form
+constexpr int kSweepWideMin = 256;
 // what a sweep launch may ask for: the update values are padded to whole steps
 // (at most 63 doubles past what the fronts' budget counts)
 constexpr int kMaxSweepLds = kMaxDynLds + 1024;
@@ -124,8 +126,10 @@ void launch_sweeps_queue(const InstDev* insts, const FrontDesc* fds, const DepLi
 // (narrow: one wave per front, for fronts of at most 128 rows)
 void launch_fwd(const InstDev* insts, const FrontDesc* fds, int nitems, int maxr, bool narrow, size_t lds,
                 int skip_done, hipStream_t st);
-// (light: half the panel loads in flight, for panels of at most kSweepHalfLds)
-void launch_bwd(const FrontDesc* fds, int nitems, bool light, size_t lds, int skip_done, hipStream_t st);
+// BWD_LIGHT: half the panel loads in flight, for panels of at most
+// kSweepHalfLds; BWD_WIDE: only the triangle in LDS
+enum { BWD_PANEL = 0, BWD_LIGHT = 1, BWD_WIDE = 2 };
+void launch_bwd(const FrontDesc* fds, int nitems, int form, size_t lds, int skip_done, hipStream_t st);
 
 // permutation modes
 enum { PIN_B = 0, PIN_R = 1 };

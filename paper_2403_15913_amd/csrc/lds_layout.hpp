@@ -57,6 +57,12 @@ inline int64_t bwd_lds_bytes(int r, int c) {
     const int g4 = c <= 16 ? 64 : c <= 32 ? 32 : c <= 64 ? 16 : 8;
     return ((((int64_t)(r | 1) * c + 1) & ~(int64_t)1) + ((r - c + g4 - 1) & -g4) + c) * 8;
 }
+// (levels of many fronts: the triangle with an odd leading dimension, u values
+// and the columns' partial sums, 65, 33, 17 or 9 places a column)
+inline int64_t bwd_wide_lds_bytes(int r, int c) {
+    const int places = c <= 16 ? 65 : c <= 32 ? 33 : c <= 64 ? 17 : 9;
+    return ((((int64_t)(c | 1) * c + 1) & ~(int64_t)1) + ((r - c + 1) & ~1) + places * c) * 8;
+}
 
 inline int64_t front_lds_bytes(int r, int c) { return std::max(factor_lds_bytes(r, c), solve_lds_bytes(r, c)); }
 
