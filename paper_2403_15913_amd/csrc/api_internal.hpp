@@ -128,8 +128,7 @@ struct Engine {
     Staging stage;                                  // used by served waves only
     std::vector<InstDev> hinst;
     std::vector<int> lvl_ptr;
-    // sweep launches: each level split into LDS size classes (small fronts
-    // first), parts sw_lvl[l] .. sw_lvl[l + 1] of sw_part
+    // sweep launches of level l: parts sw_lvl[l] .. sw_lvl[l + 1] of sw_part
     struct SweepPart { int begin, count, maxr; size_t lds_fwd, lds_bwd, lds_wide; };
     std::vector<SweepPart> sw_part;
     int sw_maxr = 0;       // tallest front of the sweep launches,

@@ -43,7 +43,8 @@ inline int64_t factor_launch_lds_bytes(int r, int c) {
     return front_blocked(r, c, 4) ? std::max(factor_lds_bytes(r, c), blocked_lds_bytes(r, c)) : factor_lds_bytes(r, c);
 }
 
-// sweeps: (r|1) x c panel (padded to an even count) + r vector entries + c pivot reciprocals
+// what the fronts' budget counts for the sweeps: (r|1) x c panel (padded to an
+// even count), r + c vector entries
 inline int64_t solve_lds_bytes(int r, int c) { return ((((int64_t)(r | 1) * c + 1) & ~(int64_t)1) + r + c) * 8; }
 
 // what the sweep launches reserve: forward, the solved values (padded to 16
