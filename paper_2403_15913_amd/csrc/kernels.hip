@@ -1345,8 +1345,8 @@ __device__ inline unsigned big_diag_chain(const double* P, int ld, int r, int j0
 // into the row range, are contiguous ranges, its relative rows being
 // ascending). Every entry belongs to one workgroup and takes the same
 // operations in the same order as with whole columns per workgroup. Bound by
-// load latency: every round trip has its loads issued together (45 -> 27 us on
-// a front of 64 x 2,900 with two children).
+// load latency: every round trip has its loads issued together (49 -> 27 us on
+// a front of 64 x 1,460 with two children).
 constexpr int kBigInitRows = 256;
 __global__ __launch_bounds__(kBigThreads) void k_big_init(const InstDev* __restrict__ insts,
                                                         const FrontDesc* __restrict__ fds) {
@@ -2219,8 +2219,8 @@ __device__ __forceinline__ void bwd_front_wide(const FrontDesc& F, double* __res
 // coefficients in registers (y_j = w_j / l_jj, then w_i -= l_ij y_j for i > j,
 // in column order). k_big_fwd_rows: the update rows take -L21 y by one thread
 // per row (column order), over as many workgroups as they fill. By one
-// workgroup in all, its loads one after another, the pass took 50 us on a
-// front of 64 x 2,900; 12 us now.
+// workgroup in all, its loads one after another, the pass took 46 us on a
+// front of 64 x 1,460; 12 us now.
 template <int K0, bool TAIL>
 __device__ __forceinline__ void row_steps(double& w, double& y, const double (&a)[16], const double d, const int l0,
                                           const int nb) {
@@ -2325,7 +2325,7 @@ __global__ __launch_bounds__(kBigThreads) void k_big_fwd_rows(const FrontDesc* _
 // column (lanes over rows, a fixed butterfly); k_big_bwd: the triangle by one
 // wave, one workgroup per front. With the dot products in the front's one
 // workgroup, a row index, its value and the panel entry at a time, the pass
-// took 104 us on a front of 64 x 2,900; 9 us now.
+// took 113 us on a front of 64 x 1,460; 9 us now.
 __global__ __launch_bounds__(kBigThreads) void k_big_bwd_dot(const FrontDesc* __restrict__ fds, int skip_done) {
     constexpr int RU = 8;  // rows per lane in flight
     const FrontDesc& F = fds[blockIdx.x];
