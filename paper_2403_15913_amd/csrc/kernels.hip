@@ -1922,18 +1922,21 @@ __device__ __forceinline__ void tri_bwd_wave(const double (&a)[4][16], const dou
 // threads, the triangle by one wave. A 66 x 198 front takes 5,800 cycles to
 // stage, 3,000 for the products and 3,800 for the triangle (one row's chain
 // after another by DPP broadcasts: 12,500); 11.0 -> 7.3 us a launch of few
-// fronts. Taking the rectangle from HBM to registers instead costs more where
-// few fronts run (8-byte strands load at a third of the rate; 13.7 us) and
+// fronts with four waves, 6.6 with eight, two lanes then sharing a column's
+// four sums. Taking the rectangle from HBM to registers instead costs more where
+// few fronts run (its strands load at a third of the rate; about 10 us) and
 // wins only on levels of more fronts than compute units (17 against 23 us).
-// PU: panel loads per thread in flight while staging (16 where every panel is
-// at most kSweepHalfLds); the arithmetic does not depend on it.
-template <int PU>
+// PU: panel loads per thread in flight while staging; NTH: 512 threads, or
+// 256 where every panel is at most kSweepHalfLds (several fronts share a
+// compute unit) and in the queue. The sums do not depend on either.
+template <int PU, int NTH>
 __device__ __forceinline__ void bwd_front(const FrontDesc& F, double* __restrict__ sh) {
+    constexpr int HS = NTH / kSolveThreads, NS = 4 / HS;  // lanes per g, strands per lane
     const int c = F.c, r = F.r;
     const int u = r - c;
     double* const yb = F.y - F.col0;  // the instance's work vector
     const int ld = r | 1;
-    constexpr int nt = kSolveThreads;
+    constexpr int nt = NTH;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // G consecutive lanes per column (G c <= 256 for c <= 128)
     const int lg = c <= 16 ? 4 : c <= 32 ? 3 : c <= 64 ? 2 : 1, G = 1 << lg;
@@ -1980,41 +1983,46 @@ __device__ __forceinline__ void bwd_front(const FrontDesc& F, double* __restrict
     // the rest into the first; a group's sums are combined in a fixed order.
     // Four steps' LDS reads go out together.
     {
-        const int k = tid >> lg, g = tid & (G - 1);
+        constexpr int sp = HS == 2 ? 1 : 0;
+        const int k = tid >> (lg + sp), g = tid & (G - 1), half = sp ? (tid >> lg) & 1 : 0;
         const int T = u - 3 * G - g > 0 ? (u - 3 * G - g + 4 * G - 1) >> (lg + 2) : 0;
-        double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
+        double a[NS];
+#pragma unroll
+        for (int h = 0; h < NS; h++) a[h] = 0.0;
         if (k < c) {
-            const double* const col = P + k * ld + c + g;
-            const double* const zg = z + 4 * g;
+            const double* const col = P + k * ld + c + g + G * NS * half;
+            const double* const zg = z + 4 * g + NS * half;
             int s = 0;
             for (; s + 4 <= T; s += 4) {
-                double p[4][4], q[4][4];
+                double p[4][NS], q[4][NS];
 #pragma unroll
                 for (int e = 0; e < 4; e++)
 #pragma unroll
-                    for (int h = 0; h < 4; h++) {
+                    for (int h = 0; h < NS; h++) {
                         p[e][h] = col[4 * G * (s + e) + G * h];
                         q[e][h] = zg[4 * G * (s + e) + h];
                     }
 #pragma unroll
-                for (int e = 0; e < 4; e++) {
-                    a0 = fma(p[e][0], q[e][0], a0);
-                    a1 = fma(p[e][1], q[e][1], a1);
-                    a2 = fma(p[e][2], q[e][2], a2);
-                    a3 = fma(p[e][3], q[e][3], a3);
-                }
+                for (int e = 0; e < 4; e++)
+#pragma unroll
+                    for (int h = 0; h < NS; h++) a[h] = fma(p[e][h], q[e][h], a[h]);
             }
-            for (; s < T; s++) {
-                a0 = fma(col[4 * G * s], zg[4 * G * s], a0);
-                a1 = fma(col[4 * G * s + G], zg[4 * G * s + 1], a1);
-                a2 = fma(col[4 * G * s + 2 * G], zg[4 * G * s + 2], a2);
-                a3 = fma(col[4 * G * s + 3 * G], zg[4 * G * s + 3], a3);
-            }
-            for (int h = 0; g + 4 * G * T + G * h < u; h++) a0 = fma(col[4 * G * T + G * h], zg[4 * G * T + h], a0);
+            for (; s < T; s++)
+#pragma unroll
+                for (int h = 0; h < NS; h++) a[h] = fma(col[4 * G * s + G * h], zg[4 * G * s + h], a[h]);
+            if (half == 0)
+                for (int h = 0; g + 4 * G * T + G * h < u; h++)
+                    a[0] = fma(col[4 * G * T + G * h], zg[4 * G * T + h], a[0]);
         }
-        double part = (a0 + a1) + (a2 + a3);
+        double part;
+        if constexpr (HS == 1) {
+            part = (a[0] + a[1]) + (a[2] + a[3]);
+        } else {
+            part = a[0] + a[1];
+            part += __shfl_xor(part, G);
+        }
         for (int off = G >> 1; off > 0; off >>= 1) part += __shfl_xor(part, off);
-        if (k < c && g == 0) t[k] = part;
+        if (k < c && g == 0 && half == 0) t[k] = part;
     }
     double a[4][16];
     if (wave == 0) tri_bwd_load(a, P, ld, c, lane);
@@ -2390,12 +2398,12 @@ __global__ __launch_bounds__(NTH, 2) void k_fwd(const InstDev* __restrict__ inst
     fwd_front<NTH>(insts, fds[blockIdx.x], skip_done, sh);
 }
 
-template <int PU>
-__global__ __launch_bounds__(kSolveThreads) void k_bwd(const FrontDesc* __restrict__ fds, int skip_done) {
+template <int PU, int NTH>
+__global__ __launch_bounds__(NTH) void k_bwd(const FrontDesc* __restrict__ fds, int skip_done) {
     extern __shared__ __align__(16) double sh[];
     const FrontDesc& F = fds[blockIdx.x];
     if (front_idle(F, skip_done)) return;
-    bwd_front<PU>(F, sh);
+    bwd_front<PU, NTH>(F, sh);
 }
 
 __global__ __launch_bounds__(kSolveThreads, 2) void k_bwd_wide(const FrontDesc* __restrict__ fds, int skip_done) {
@@ -2430,7 +2438,7 @@ __global__ __launch_bounds__(kSolveThreads, 2) void k_sweeps_queue(const InstDev
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         const FrontDesc& F = fds[k];
         if (fwd) fwd_front<kSolveThreads>(insts, F, skip_done, sh);
-        else if (!front_idle(F, skip_done)) bwd_front<32>(F, sh);
+        else if (!front_idle(F, skip_done)) bwd_front<32, kSolveThreads>(F, sh);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         __syncthreads();
         if (sched_wave()) {
@@ -4363,7 +4371,7 @@ hipError_t set_kernel_attributes() {
     if (e != hipSuccess) return e;
     e = hipFuncSetAttribute((const void*)k_cr_factor<5>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
-    for (const void* k : {(const void*)k_fwd<64>, (const void*)k_fwd<128>, (const void*)k_fwd<256>, (const void*)k_sweeps_queue, (const void*)k_bwd<16>, (const void*)k_bwd<32>, (const void*)k_bwd_wide})
+    for (const void* k : {(const void*)k_fwd<64>, (const void*)k_fwd<128>, (const void*)k_fwd<256>, (const void*)k_sweeps_queue, (const void*)k_bwd<16, 256>, (const void*)k_bwd<16, 512>, (const void*)k_bwd_wide})
         if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxSweepLds);
     return e;
 }
@@ -4528,8 +4536,8 @@ void launch_fwd(const InstDev* insts, const FrontDesc* fds, int nitems, int maxr
 void launch_bwd(const FrontDesc* fds, int nitems, int form, size_t lds, int skip_done, hipStream_t st) {
     if (nitems <= 0) return;
     if (form == BWD_WIDE) k_bwd_wide<<<nitems, kSolveThreads, lds, st>>>(fds, skip_done);
-    else if (form == BWD_LIGHT) k_bwd<16><<<nitems, kSolveThreads, lds, st>>>(fds, skip_done);
-    else k_bwd<32><<<nitems, kSolveThreads, lds, st>>>(fds, skip_done);
+    else if (form == BWD_LIGHT) k_bwd<16, 256><<<nitems, 256, lds, st>>>(fds, skip_done);
+    else k_bwd<16, 512><<<nitems, 512, lds, st>>>(fds, skip_done);
 }
 void launch_perm_in(const InstDev* insts, const Calls& C, const WorkItem* rows, int nitems, int mode, hipStream_t st) {
     if (nitems > 0) k_perm_in<<<nitems, kBlock, 0, st>>>(insts, C, rows, mode);

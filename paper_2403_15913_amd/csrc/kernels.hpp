@@ -126,7 +126,7 @@ void launch_sweeps_queue(const InstDev* insts, const FrontDesc* fds, const DepLi
 // (narrow: one wave per front, for fronts of at most 128 rows)
 void launch_fwd(const InstDev* insts, const FrontDesc* fds, int nitems, int maxr, bool narrow, size_t lds,
                 int skip_done, hipStream_t st);
-// BWD_LIGHT: half the panel loads in flight, for panels of at most
+// BWD_PANEL: eight waves a front; BWD_LIGHT: four, for panels of at most
 // kSweepHalfLds; BWD_WIDE: only the triangle in LDS
 enum { BWD_PANEL = 0, BWD_LIGHT = 1, BWD_WIDE = 2 };
 void launch_bwd(const FrontDesc* fds, int nitems, int form, size_t lds, int skip_done, hipStream_t st);
