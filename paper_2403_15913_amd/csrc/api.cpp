@@ -247,8 +247,8 @@ kkt_status Engine::place(const std::vector<const Symbolic*>& s, const std::vecto
         ko[q + 1] = ko[q] + S.nnzk;
         co[q + 1] = co[q] + S.sp_ptr[S.n];
         po[q + 1] = po[q] + 5 * (int64_t)((S.n + kBlock - 1) / kBlock) * kResidualSplit;
-        // reduction slots of the CG and the augmented solve: up to 8 per part
-        // of a 256-row block of n and per block of m
+        // reduction slots of the CG and the augmented solve (single factors
+        // only): up to 8 per part of a 256-row block of n and per block of m
         ro[q + 1] = ro[q] + 8 * (int64_t)(kRowSplit * ((S.n + kBlock - 1) / kBlock) + (S.m + kBlock - 1) / kBlock) +
                     (S.n + 15) / 16 + 4;  // (and one per 16 long columns)
         for (int k = 0; k < S.ns; k++) {
@@ -294,7 +294,7 @@ kkt_status Engine::place(const std::vector<const Symbolic*>& s, const std::vecto
     pvec = cv.take<double>(M);
     pvec2 = cv.take<double>(M);
     qvec = cv.take<double>(M);
-    red = cv.take<double>(ro[ninst]);
+    red = single_storage ? cv.take<double>(ro[ninst]) : nullptr;
     jcopy = cv.take<double>(j_ofs[ninst]);
     jtv = single_storage ? cv.take<double>(j_ofs[ninst]) : nullptr;
     k0csr = single_storage ? cv.take<double>(co[ninst]) : nullptr;
@@ -371,7 +371,7 @@ kkt_status Engine::place(const std::vector<const Symbolic*>& s, const std::vecto
         I.aug_e = aug_e;
         I.aug_prev = aug_prev;
         I.aug = aug ? aug + q : nullptr;
-        I.red = red + ro[q];
+        I.red = red ? red + ro[q] : nullptr;
         I.status = status + 2 * q;
         I.rs = rs + q;
         I.cg = cg + q;
