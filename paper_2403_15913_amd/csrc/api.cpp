@@ -1017,11 +1017,11 @@ kkt_status Engine::solve_augmented(const AugCall& A, int maxit, double tol, kkt_
         TL(KKT_PHASE_RESIDUAL, launch_aug_recover(di(), A, nitems, n_nitems, mitems, n_mitems, 1, st));
     }
     const bool rev = S.revert != 0;
-    if (!S.done || rev) {  // (the check that stopped the rounds has been waited for)
-        TL(KKT_PHASE_PERMUTE, launch_aug_revert(di(), A, nitems, n_nitems, mitems, n_mitems, st));
-        if ((e = hipGetLastError()) != hipSuccess || (e = hipStreamSynchronize(st)) != hipSuccess)
-            return hip_fail(e, "augmented solve");
-    }
+    const bool behind = !S.done || rev;  // (the check that stopped the rounds has been waited for)
+    if (behind) TL(KKT_PHASE_PERMUTE, launch_aug_revert(di(), A, nitems, n_nitems, mitems, n_mitems, st));
+    // (a refused launch leaves its outputs as they were, whatever the last check says)
+    if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "augmented solve launch");
+    if (behind && (e = hipStreamSynchronize(st)) != hipSuccess) return hip_fail(e, "augmented solve");
     const double om = rev ? S.omega_prev : S.omega;
     if (info) {
         info->iters = rev ? S.it - 1 : S.it;
