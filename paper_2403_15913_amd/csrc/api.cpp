@@ -336,6 +336,7 @@ kkt_status Engine::place(const std::vector<const Symbolic*>& s, const std::vecto
     if (total > cap) return fail(KKT_ERR_BUDGET, "instances do not fit the arena");
 
     hinst.assign(ninst, InstDev{});
+    hstat.assign(2 * (size_t)ninst, 0);  // (here, so that no solve call allocates)
     for (int q = 0; q < ninst; q++) {
         InstDev& I = hinst[q];
         std::memset(&I, 0, sizeof(I));
@@ -817,7 +818,6 @@ kkt_status Engine::solve_finish(const Calls& C, int iter0, int maxit, double tol
     }
     // a failed factor makes the solve meaningless: report it
     int derr = 0;
-    hstat.resize(2 * (size_t)ninst);
     for (int q = 0; q < ninst; q++) {
         derr |= hr[q].err;
         hstat[2 * q] = hr[q].status[0];
