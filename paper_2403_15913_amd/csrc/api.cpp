@@ -383,10 +383,9 @@ kkt_status Engine::place(const std::vector<const Symbolic*>& s, const std::vecto
     sn.reserve(nsn);
     lvl_ptr.assign(1, 0);
     lvl_large.clear();
-    sw_part.clear();
     sw_maxr = 0;
     sw_maxlds = 0;
-    sw_lvl.assign(1, 0);
+    sw_lvl.clear();
     for (int l = 0; l < nlev; l++) {
         for (int q = 0; q < ninst; q++) {
             const Symbolic& S = *s[q];
@@ -407,19 +406,18 @@ kkt_status Engine::place(const std::vector<const Symbolic*>& s, const std::vecto
             return solve_lds_bytes(A.sn_nrow[a.id], A.sn_ncol[a.id]) > solve_lds_bytes(B.sn_nrow[b.id], B.sn_ncol[b.id]);
         };
         std::stable_sort(sn.begin() + b0, sn.begin() + bl, by_size);
-        SweepPart part{b0, bl - b0, 0, 0, 0, 0};
+        SweepLevel P{b0, bl - b0, 0, 0, 0, 0};
         for (int t = b0; t < bl; t++) {
             const Symbolic& S = *s[sn[t].inst];
             const int r = S.sn_nrow[sn[t].id], c = S.sn_ncol[sn[t].id];
-            part.maxr = std::max(part.maxr, r);
-            part.lds_fwd = std::max(part.lds_fwd, (size_t)fwd_lds_bytes(r, c));
-            part.lds_bwd = std::max(part.lds_bwd, (size_t)bwd_lds_bytes(r, c));
-            part.lds_wide = std::max(part.lds_wide, (size_t)bwd_wide_lds_bytes(r, c));
+            P.maxr = std::max(P.maxr, r);
+            P.lds_fwd = std::max(P.lds_fwd, (size_t)fwd_lds_bytes(r, c));
+            P.lds_bwd = std::max(P.lds_bwd, (size_t)bwd_lds_bytes(r, c));
+            P.lds_wide = std::max(P.lds_wide, (size_t)bwd_wide_lds_bytes(r, c));
         }
-        if (part.count > 0) sw_part.push_back(part);
-        sw_maxr = std::max(sw_maxr, part.maxr);
-        sw_maxlds = std::max(sw_maxlds, part.lds_bwd);
-        sw_lvl.push_back((int)sw_part.size());
+        sw_lvl.push_back(P);
+        sw_maxr = std::max(sw_maxr, P.maxr);
+        sw_maxlds = std::max(sw_maxlds, P.lds_bwd);
         lvl_ptr.push_back((int)sn.size());
     }
     // update-matrix tiles (lower part) of the same fronts, level by level
@@ -586,7 +584,7 @@ kkt_status Engine::init_owned(const std::vector<const Symbolic*>& s) {
     size_t need = 0;
     if ((st = place(s, p, nullptr, 0, false, nullptr, &need)) != KKT_OK) return st;
     if ((e = own.alloc(need)) != hipSuccess) return hip_fail(e, "device allocation");
-    // control events of the refinement and CG loops (created here, so that
+    // control events of the CG loop (created here, so that
     // no solve call allocates)
     if ((e = hipEventCreateWithFlags(&ctl_event, hipEventDisableTiming)) != hipSuccess ||
         (e = hipEventCreateWithFlags(&ctl_event2, hipEventDisableTiming)) != hipSuccess)
@@ -690,8 +688,8 @@ void Engine::sweeps(hipStream_t st, int skip_done) {
     }
     const int nl = (int)lvl_ptr.size() - 1;
     for (int l = 0; l < nl; l++) {
-        for (int k = sw_lvl[l]; k < sw_lvl[l + 1]; k++) {
-            const SweepPart& P = sw_part[k];
+        const SweepLevel& P = sw_lvl[l];
+        if (P.count > 0) {
             // one wave per front where a level's fronts have at most 128 rows
             // and either no front is taller or the level fills the chip: a
             // second form of the kernel for a level of a few fronts costs more
@@ -706,8 +704,8 @@ void Engine::sweeps(hipStream_t st, int skip_done) {
     for (int l = nl - 1; l >= 0; l--) {
         if (lvl_large[l] < lvl_ptr[l + 1])
             TL(KKT_PHASE_BWD, launch_big_bwd(fdesc + lvl_large[l], lvl_ptr[l + 1] - lvl_large[l], lvl_lmaxc[l], skip_done, st));
-        for (int k = sw_lvl[l]; k < sw_lvl[l + 1]; k++) {
-            const SweepPart& P = sw_part[k];
+        const SweepLevel& P = sw_lvl[l];
+        if (P.count > 0) {
             // light panels chosen as in the forward sweep (one form for the
             // levels of few fronts); panels that leave a compute unit room for
             // one workgroup and a level of more fronts than compute units: two

@@ -121,19 +121,18 @@ struct Engine {
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec = nullptr;
     hipStream_t cap_stream = nullptr;
-    hipEvent_t ctl_event = nullptr, ctl_event2 = nullptr;  // refinement / CG control readback
+    hipEvent_t ctl_event = nullptr, ctl_event2 = nullptr;  // CG control readback
     Calls g_calls{};
     int g_rounds = 0, g_maxit = 0;
     double g_tol = 0.0;
     Staging stage;                                  // used by served waves only
     std::vector<InstDev> hinst;
     std::vector<int> lvl_ptr;
-    // sweep launches of level l: parts sw_lvl[l] .. sw_lvl[l + 1] of sw_part
-    struct SweepPart { int begin, count, maxr; size_t lds_fwd, lds_bwd, lds_wide; };
-    std::vector<SweepPart> sw_part;
+    // sweep launch of every level: its fronts in LDS (none where all are large)
+    struct SweepLevel { int begin, count, maxr; size_t lds_fwd, lds_bwd, lds_wide; };
+    std::vector<SweepLevel> sw_lvl;
     int sw_maxr = 0;       // tallest front of the sweep launches,
     size_t sw_maxlds = 0;  //   largest LDS of a backward step
-    std::vector<int> sw_lvl;
     int n_nitems = 0, n_mitems = 0, n_kitems = 0, n_jitems = 0, n_hitems = 0;
     size_t lds_factor = 0, lds_solve = 0;
     std::vector<int64_t> n_ofs, m_ofs, w_ofs, j_ofs;  // ninst + 1 prefix offsets

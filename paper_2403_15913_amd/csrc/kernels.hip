@@ -373,26 +373,6 @@ __device__ inline void copy_vec(double* __restrict__ dst, const double* __restri
 
 __device__ inline int even_up(int x) { return (x + 1) & ~1; }
 
-// Loop over q in [0, tot) in batches: every thread first issues up to UNR
-// independent loads (load(q)), then consumes them (use(q, value)), so up to
-// UNR global loads per thread are in flight at once.
-template <int UNR, class LoadF, class UseF>
-__device__ inline void batched(int tot, int tid, int nt, LoadF load, UseF use) {
-    for (int base = tid; base < tot; base += nt * UNR) {
-        double v[UNR];
-        // clamped indices: every load is valid, so none is predicated
-#pragma unroll
-        for (int k = 0; k < UNR; k++) v[k] = load(min(base + k * nt, tot - 1));
-#pragma unroll
-        for (int k = 0; k < UNR; k++) pin(v[k]);
-#pragma unroll
-        for (int k = 0; k < UNR; k++) {
-            const int q = base + k * nt;
-            if (q < tot) use(q, v[k]);
-        }
-    }
-}
-
 // lower-triangular tile enumeration: t -> (ti, tj) with tj0 <= tj <= ti < nb
 __device__ inline void tri_tile(int t, int tj0, int nb, int& ti, int& tj) {
     tj = tj0;
