@@ -1635,17 +1635,23 @@ __device__ __forceinline__ void fwd_steps(double& acc0, double& acc1, double& y0
 }
 
 // Forward step of one front by NTH threads: thread t holds rows 2 t and
-// 2 t + 1, their panel entries in registers, three blocks of 16 columns in
-// flight (loaded as the panel lies in HBM: no LDS staging, and only vectors in
+// 2 t + 1, their panel entries in registers, up to three blocks of 16
+// columns in flight (loaded as the panel lies in HBM: no LDS staging, and only vectors in
 // LDS, so the registers alone limit the fronts per compute unit). Levels of
 // few fronts are bound by one wave's chain and the load latency (a 66 x 198
 // front: loads and children's sums 4,700 cycles, columns 52 cycles each; with
 // the panel staged in LDS and 16-lane chains 19,000 in all, 10.4 -> 6.0 us a
 // launch), the leaf levels by HBM (512 fronts of 79 x 227: 26.9 -> 22.5 us).
-template <int NTH, int NBLK>
+// MAXR: blocks in flight at most, two for fronts of more than 96 columns and in
+// the queue, where a third does not fit the registers. A spilled value makes
+// every hardware queue allocate scratch memory at the first launch of the
+// kernel (the first solve of a 450-variable system on a new queue 240 us
+// against 110), and costs more than the third block gives (500 stages of 54
+// variables, fronts of up to 112 columns: 186 -> 161 us a solve).
+template <int NTH, int NBLK, int MAXR>
 __device__ __forceinline__ void fwd_body(const InstDev* __restrict__ insts, const FrontDesc& F,
                                          double* __restrict__ sh) {
-    constexpr int VU = kSolveThreads / NTH, NR = NBLK < 3 ? NBLK : 3;
+    constexpr int VU = kSolveThreads / NTH, NR = NBLK < MAXR ? NBLK : NBLK < 7 ? MAXR : 2;
     const int c = F.c, r = F.r;
     const int ld = r | 1;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1781,14 +1787,17 @@ __device__ __forceinline__ void fwd_body(const InstDev* __restrict__ insts, cons
             }
         }
         __syncthreads();
-        if (wave > 0 && live) {
-            double y[16];
+        if (wave > 0 && live) {  // (eight of the values at a time: registers)
 #pragma unroll
-            for (int k = 0; k < 16; k++) y[k] = ys[j0 + k];
+            for (int h = 0; h < 16; h += 8) {
+                double y[8];
 #pragma unroll
-            for (int k = 0; k < 16; k++) {
-                acc0 = fma(-a[B % NR][k].x, y[k], acc0);
-                acc1 = fma(-a[B % NR][k].y, y[k], acc1);
+                for (int k = 0; k < 8; k++) y[k] = ys[j0 + h + k];
+#pragma unroll
+                for (int k = 0; k < 8; k++) {
+                    acc0 = fma(-a[B % NR][h + k].x, y[k], acc0);
+                    acc1 = fma(-a[B % NR][h + k].y, y[k], acc1);
+                }
             }
         }
         if constexpr (B + NR < NBLK) load(std::integral_constant<int, B + NR>{});
@@ -1812,19 +1821,19 @@ __device__ __forceinline__ void fwd_body(const InstDev* __restrict__ insts, cons
 }
 
 // one body per number of column blocks (c <= 128)
-template <int NTH>
+template <int NTH, int MAXR>
 __device__ __forceinline__ void fwd_front(const InstDev* __restrict__ insts, const FrontDesc& F, const int skip_done,
                                           double* __restrict__ sh) {
     if (front_idle(F, skip_done)) return;
     switch ((F.c + 15) >> 4) {
-        case 1: return fwd_body<NTH, 1>(insts, F, sh);
-        case 2: return fwd_body<NTH, 2>(insts, F, sh);
-        case 3: return fwd_body<NTH, 3>(insts, F, sh);
-        case 4: return fwd_body<NTH, 4>(insts, F, sh);
-        case 5: return fwd_body<NTH, 5>(insts, F, sh);
-        case 6: return fwd_body<NTH, 6>(insts, F, sh);
-        case 7: return fwd_body<NTH, 7>(insts, F, sh);
-        default: return fwd_body<NTH, 8>(insts, F, sh);
+        case 1: return fwd_body<NTH, 1, MAXR>(insts, F, sh);
+        case 2: return fwd_body<NTH, 2, MAXR>(insts, F, sh);
+        case 3: return fwd_body<NTH, 3, MAXR>(insts, F, sh);
+        case 4: return fwd_body<NTH, 4, MAXR>(insts, F, sh);
+        case 5: return fwd_body<NTH, 5, MAXR>(insts, F, sh);
+        case 6: return fwd_body<NTH, 6, MAXR>(insts, F, sh);
+        case 7: return fwd_body<NTH, 7, MAXR>(insts, F, sh);
+        default: return fwd_body<NTH, 8, MAXR>(insts, F, sh);
     }
 }
 
@@ -1908,8 +1917,10 @@ __device__ __forceinline__ void tri_bwd_wave(const double (&a)[4][16], const dou
 // wins only on levels of more fronts than compute units (17 against 23 us).
 // PU: panel loads per thread in flight while staging; NTH: 512 threads, or
 // 256 where every panel is at most kSweepHalfLds (several fronts share a
-// compute unit) and in the queue. The sums do not depend on either.
-template <int PU, int NTH>
+// compute unit) and in the queue. REST: what is left of the panel PU at a time
+// too (the queue, whose 256 threads take whole panels; on the level launches,
+// with little left, it costs 1 to 2 %). The sums do not depend on any of them.
+template <int PU, int NTH, bool REST>
 __device__ __forceinline__ void bwd_front(const FrontDesc& F, double* __restrict__ sh) {
     constexpr int HS = NTH / kSolveThreads, NS = 4 / HS;  // lanes per g, strands per lane
     const int c = F.c, r = F.r;
@@ -1953,7 +1964,19 @@ __device__ __forceinline__ void bwd_front(const FrontDesc& F, double* __restrict
 #pragma unroll
     for (int k = 0; k < PU; k++)
         if (tid + k * nt < n2) d2[tid + k * nt] = pv[k];
-    for (int q = tid + PU * nt; q < n2; q += nt) d2[q] = s2[q];
+    if constexpr (REST) {
+        for (int q = tid + PU * nt; q < n2; q += PU * nt) {
+#pragma unroll
+            for (int k = 0; k < PU; k++) pv[k] = s2[min(q + k * nt, n2 - 1)];
+#pragma unroll
+            for (int k = 0; k < PU; k++) pin(pv[k]);
+#pragma unroll
+            for (int k = 0; k < PU; k++)
+                if (q + k * nt < n2) d2[q + k * nt] = pv[k];
+        }
+    } else {
+        for (int q = tid + PU * nt; q < n2; q += nt) d2[q] = s2[q];
+    }
     pin(zy);
     if (tid < nz) z[place(tid)] = tid < u ? zy : 0.0;
     for (int i = tid + nt; i < nz; i += nt) z[place(i)] = i < u ? yb[rw[i]] : 0.0;
@@ -2375,7 +2398,7 @@ template <int NTH>
 __global__ __launch_bounds__(NTH, 2) void k_fwd(const InstDev* __restrict__ insts,
                                                       const FrontDesc* __restrict__ fds, int skip_done) {
     extern __shared__ __align__(16) double sh[];
-    fwd_front<NTH>(insts, fds[blockIdx.x], skip_done, sh);
+    fwd_front<NTH, 3>(insts, fds[blockIdx.x], skip_done, sh);
 }
 
 template <int PU, int NTH>
@@ -2383,7 +2406,7 @@ __global__ __launch_bounds__(NTH) void k_bwd(const FrontDesc* __restrict__ fds, 
     extern __shared__ __align__(16) double sh[];
     const FrontDesc& F = fds[blockIdx.x];
     if (front_idle(F, skip_done)) return;
-    bwd_front<PU, NTH>(F, sh);
+    bwd_front<PU, NTH, false>(F, sh);
 }
 
 __global__ __launch_bounds__(kSolveThreads, 2) void k_bwd_wide(const FrontDesc* __restrict__ fds, int skip_done) {
@@ -2417,8 +2440,8 @@ __global__ __launch_bounds__(kSolveThreads, 2) void k_sweeps_queue(const InstDev
         __syncthreads();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         const FrontDesc& F = fds[k];
-        if (fwd) fwd_front<kSolveThreads>(insts, F, skip_done, sh);
-        else if (!front_idle(F, skip_done)) bwd_front<32, kSolveThreads>(F, sh);
+        if (fwd) fwd_front<kSolveThreads, 2>(insts, F, skip_done, sh);
+        else if (!front_idle(F, skip_done)) bwd_front<16, kSolveThreads, true>(F, sh);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         __syncthreads();
         if (sched_wave()) {
