@@ -495,9 +495,10 @@ kkt_status kkt_factor_set_update_split(kkt_factor* f, int32_t max_fronts, int32_
  * the dense kernels of the supernodal Cholesky), level schedule only: a tree
  * level whose widest front has at most max_cols columns is factored by
  * 256-thread workgroups that reserve only that level's LDS (two fit on a
- * compute unit when the level's fronts need at most 80 KiB); other levels by
- * 768-thread workgroups. Both give every entry the same operations in the
- * same order, so results are bitwise identical; only the time differs.
+ * compute unit when the level's fronts need at most 80 KiB, three at 53 KiB);
+ * other levels by 768-thread workgroups. Both give every entry the same
+ * operations in the same order, so results are bitwise identical; only the
+ * time differs.
  * Default 0 (every level by 768 threads); the autotuner picks it by
  * measurement. INVALID_ARG if negative. Host only; applies to launches
  * issued after the call.

@@ -710,7 +710,7 @@ void Engine::sweeps(hipStream_t st, int skip_done) {
             // levels of few fronts); panels that leave a compute unit room for
             // one workgroup and a level of more fronts than compute units: two
             // workgroups share a unit with only the triangle in LDS (512 fronts
-            // of 79 x 227: 24 -> 18 us; on a level of 129 fronts 8.3 -> 10.6)
+            // of 79 x 227: 24 -> 18.5 us; on a level of 129 fronts 8.3 -> 10.6)
             const bool light = P.lds_bwd <= kSweepHalfLds && (sw_maxlds <= kSweepHalfLds || P.count >= 512);
             const bool wide = P.lds_bwd > kSweepHalfLds && P.lds_wide <= kSweepHalfLds && P.count > kSweepWideMin;
             TL(KKT_PHASE_BWD, launch_bwd(fdesc + P.begin, P.count, wide ? BWD_WIDE : light ? BWD_LIGHT : BWD_PANEL,

@@ -1594,6 +1594,7 @@ __device__ __forceinline__ bool front_idle(const FrontDesc& F, int skip) {
     return skip == SKIP_REFINE ? *F.done != 0 : (skip == SKIP_CG ? *F.cgdone != 0 : false);
 }
 
+// v_writelane_b32 by the name of its intrinsic, which this compiler gives no builtin
 extern "C" __device__ int kkt_writelane(int v, int lane, int old) __asm("llvm.amdgcn.writelane.i32");
 __device__ __forceinline__ double writelane_d(double v, int lane, double old) {
     const long long b = __double_as_longlong(v), o = __double_as_longlong(old);
@@ -1635,9 +1636,9 @@ __device__ __forceinline__ void fwd_steps(double& acc0, double& acc1, double& y0
 }
 
 // Forward step of one front by NTH threads: thread t holds rows 2 t and
-// 2 t + 1, their panel entries in registers, up to three blocks of 16
-// columns in flight (loaded as the panel lies in HBM: no LDS staging, and only vectors in
-// LDS, so the registers alone limit the fronts per compute unit). Levels of
+// 2 t + 1, their panel entries in registers, up to three blocks of 16 columns
+// in flight (loaded as the panel lies in HBM: no LDS staging, and only vectors
+// in LDS, so the registers alone limit the fronts per compute unit). Levels of
 // few fronts are bound by one wave's chain and the load latency (a 66 x 198
 // front: loads and children's sums 4,700 cycles, columns 52 cycles each; with
 // the panel staged in LDS and 16-lane chains 19,000 in all, 10.4 -> 6.0 us a
@@ -1914,7 +1915,7 @@ __device__ __forceinline__ void tri_bwd_wave(const double (&a)[4][16], const dou
 // fronts with four waves, 6.6 with eight, two lanes then sharing a column's
 // four sums. Taking the rectangle from HBM to registers instead costs more where
 // few fronts run (its strands load at a third of the rate; about 10 us) and
-// wins only on levels of more fronts than compute units (17 against 23 us).
+// wins only on levels of more fronts than compute units (bwd_front_wide).
 // PU: panel loads per thread in flight while staging; NTH: 512 threads, or
 // 256 where every panel is at most kSweepHalfLds (several fronts share a
 // compute unit) and in the queue. REST: what is left of the panel PU at a time
@@ -2058,8 +2059,9 @@ __device__ __forceinline__ double strand_sum(const double* __restrict__ w) {
 // holds two neighbouring strands of a column: 8 strands a column above 64
 // columns, 16, 32 or 64 at most 64, 32, 16, so two passes cover every front)
 // and only the triangle is staged in LDS, so two workgroups share a compute
-// unit where a whole panel leaves room for one. Every sum takes the order of
-// bwd_front (same bits). Bound by HBM and the address unit (16 cycles a load).
+// unit where a whole panel leaves room for one (512 fronts of 79 x 227: 24 ->
+// 18.5 us). Every sum takes the order of bwd_front (same bits). Bound by HBM
+// and the address unit (16 cycles a load).
 __device__ __forceinline__ void bwd_front_wide(const FrontDesc& F, double* __restrict__ sh) {
     constexpr int nt = kSolveThreads, NT = 6, NP = 2;
     const int c = F.c, r = F.r, u = r - c;
@@ -2725,7 +2727,8 @@ __global__ __launch_bounds__(256) void k_matvec(const InstDev* __restrict__ inst
 // Every kernel returns at once when the instance's CG has stopped, so the
 // iterations can be queued without reading decisions back.
 //
-// Reduction slots of one instance (4 per 256-row block):
+// Reduction slots of one single factor (4 per part of a 256-row block of n, of
+// which there are kRowSplit, and 4 per block of m):
 //   N-region red[4 (kRowSplit b + part) + k], n-side blocks: 0 max row sum of
 //                                          |A| (k_cg_rows, every part), 1 max
 //                                          |f| (k_cg_fg, part 0); 2 max |r|,
@@ -3385,7 +3388,8 @@ __global__ __launch_bounds__(256) void k_cg_norms(const InstDev* __restrict__ in
 // follow as ds = -r4 - J dx, dz = -r2 - Sigma_s ds. The refinement on the
 // full system (section "Hybrid linear solver") takes the residual e of the
 // augmented system and solves for the correction the same way.
-// Slots: N-region 8 per block (k_aug_res_n), M-region 8 per block after it.
+// Slots: N-region 8 per part of a 256-row block, kRowSplit parts a block
+// (k_aug_res_n), M-region 8 per block after it.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ int aug_mslot0(const InstDev& I) { return 8 * kRowSplit * cg_nb(I.P.n); }
 
@@ -3661,7 +3665,8 @@ __global__ __launch_bounds__(256) void k_aug_revert_m(const InstDev* __restrict_
 //   the Newton step (dx, ds, dz) from the augmented system, the largest
 //   alpha_p, alpha_d <= 1 keeping s and z above (1 - tau) of their values.
 // W x comes from the factor's kept K0 = W + delta I (Sigma_x = 0).
-// Slots: red[4 b + k] for the n-side blocks, red[4 nbn + 4 b + k] for m-side.
+// Slots: red[4 (kRowSplit b + part) + k] for the n-side (nbn blocks; k_ipm_norm_n
+// uses the first nbn records), red[4 kRowSplit nbn + 4 b + k] for the m-side.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ int ipm_m0(const InstDev& I) { return 4 * kRowSplit * cg_nb(I.P.n); }
 

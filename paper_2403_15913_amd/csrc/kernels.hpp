@@ -208,7 +208,8 @@ struct IpmCall {
     dptr<double> dx;         // n
     dptr<double> ds;         // m
     dptr<double> dz;         // m
-    dptr<double> red;        // reduction slots (4 per 256-row block of n, then of m)
+    dptr<double> red;        // reduction slots (4 for each of the kRowSplit parts of a 256-row
+                             // block of n, then 4 per block of m)
     dptr<IpmState> st;
 };
 void launch_ipm_start(const InstDev* insts, const IpmCall& P, const WorkItem* ncols, int nn, const WorkItem* mrows,
