@@ -162,14 +162,16 @@ hipError_t DevPattern::build(const Symbolic& S) {
         }
     }
     for (size_t p = 0; p < S.j_col.size(); p++) colp[p] = S.iperm[S.j_col[p]];
+    // (the list of long columns behind the column pointers: an upload of its
+    // own would be one more allocation per registered pattern)
+    tp.insert(tp.end(), tl.begin(), tl.end());
     if ((e = upload(b_jtpptr, tp)) != hipSuccess || (e = upload(b_jtprow, trow)) != hipSuccess ||
-        (e = upload(b_jtpe, te)) != hipSuccess || (e = upload(b_jtplong, tl)) != hipSuccess ||
-        (e = upload(b_jcolp, colp)) != hipSuccess)
+        (e = upload(b_jtpe, te)) != hipSuccess || (e = upload(b_jcolp, colp)) != hipSuccess)
         return e;
     desc.jtp_ptr = (const int*)b_jtpptr.p;
     desc.jtp_row = (const int*)b_jtprow.p;
     desc.jtp_e = (const int*)b_jtpe.p;
-    desc.jtp_long = (const int*)b_jtplong.p;
+    desc.jtp_long = (const int*)b_jtpptr.p + S.n + 1;
     desc.nlong = (int)tl.size();
     desc.j_colp = (const int*)b_jcolp.p;
     return hipSuccess;
