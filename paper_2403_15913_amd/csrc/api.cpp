@@ -696,7 +696,9 @@ void Engine::sweeps(hipStream_t st, int skip_done) {
             // and either no front is taller or the level fills the chip: a
             // second form of the kernel for a level of a few fronts costs more
             // (its code is fetched anew: 11 us for the 66-row root, 5.3 us by
-            // two waves) than the spare wave
+            // two waves) than the spare wave; on levels of 64 to 1,024 leaves
+            // under a 150-row hub the two are within 2 % (64 leaves of 66 x 126:
+            // 190 us a sweep pair by the narrow form, 202 by the hub's)
             const bool narrow = P.maxr <= 128 && (sw_maxr <= 128 || P.count >= 512);
             TL(KKT_PHASE_FWD, launch_fwd(di(), fdesc + P.begin, P.count, P.maxr, narrow, P.lds_fwd, skip_done, st));
         }
