@@ -85,8 +85,7 @@ typedef struct kkt_options {
     int32_t relax_small;   /* supernodes up to this width always amalgamate (0: 16, <0: none) */
     double relax_frac;     /* amalgamation may add up to this fraction of explicit zeros (<0: 0.5) */
     int32_t front_lds_max; /* LDS bytes one front panel may use (0 or more than 158 KiB: 158 KiB; less
-                              than 4 KiB: 4 KiB; the sweeps' launches pad the vector beside it and
-                              may reserve up to 504 bytes more). A front too tall to fit at one column is a large
+                              than 4 KiB: 4 KiB). A front too tall to fit at one column is a large
                               front: at most 64 columns, assembled, factored and solved in place in HBM
                               by several workgroups per front (its update matrix by one wave per
                               tile); level schedule only, INVALID_ARG if negative */

@@ -259,7 +259,7 @@ kkt_status Engine::place(const std::vector<const Symbolic*>& s, const std::vecto
                 if (S.sn_ncol[k] > kLargeFrontCols) return fail(KKT_ERR_PATTERN, "large front wider than 64 columns");
                 n_large++;
             } else {
-                lds_factor = std::max(lds_factor, (size_t)factor_launch_lds_bytes(S.sn_nrow[k], S.sn_ncol[k], S.lds_budget));
+                lds_factor = std::max(lds_factor, (size_t)factor_launch_lds_bytes(S.sn_nrow[k], S.sn_ncol[k]));
                 const int r = S.sn_nrow[k], c = S.sn_ncol[k];
                 lds_solve = std::max({lds_solve, (size_t)fwd_lds_bytes(r, c), (size_t)bwd_lds_bytes(r, c)});
             }
@@ -443,8 +443,7 @@ kkt_status Engine::place(const std::vector<const Symbolic*>& s, const std::vecto
                 lvl_lmaxr[l] = std::max(lvl_lmaxr[l], S.sn_nrow[sn[t].id]);
             } else {
                 lvl_maxu[l] = std::max(lvl_maxu[l], u);
-                lvl_flds[l] = std::max(lvl_flds[l], (size_t)factor_launch_lds_bytes(S.sn_nrow[sn[t].id], S.sn_ncol[sn[t].id],
-                                                                                    S.lds_budget));
+                lvl_flds[l] = std::max(lvl_flds[l], (size_t)factor_launch_lds_bytes(S.sn_nrow[sn[t].id], S.sn_ncol[sn[t].id]));
                 lvl_maxc[l] = std::max(lvl_maxc[l], S.sn_ncol[sn[t].id]);
             }
             const int nbu = (u + 15) / 16;
@@ -504,7 +503,7 @@ kkt_status Engine::place(const std::vector<const Symbolic*>& s, const std::vecto
             F.cinv[j] = PD.pinv + S.pinv_ofs[F.ch0 + j];
         }
         F.inst = q;
-        F.pw = blocked_panel_waves(F.r, F.c, S.lds_budget);
+        F.id = k;
     }
     for (int q = 0; q < ninst; q++) {
         const Symbolic& S = *s[q];

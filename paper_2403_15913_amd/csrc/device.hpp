@@ -187,7 +187,7 @@ struct FrontDesc {
     dptr<const int> cinv[2];     //   inverse maps (this front's update row -> theirs, or -1),
     int cuc[2], cnb[2];     //   update sizes, and rows mapping into this front's columns
     int r, c, col0, nk;     // rows, columns, first column, entries of K
-    int nch, ch0, inst, pw; // children, first child in ch_list, instance, blocked_panel_waves
+    int nch, ch0, inst, id; // children, first child in ch_list, instance, supernode
 };
 
 struct WorkItem {

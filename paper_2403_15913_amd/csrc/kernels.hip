@@ -439,8 +439,8 @@ __device__ __forceinline__ Frag frag_load(const double* __restrict__ p, const in
 }
 
 // Dense part of a front whose panel is column-major in LDS (leading dimension
-// ld = r | 1): fronts taller than the panel waves can cover, and fronts whose
-// blocked panel is over a small LDS budget. The pivot chain by wave 0 beside the updates, then the rows below the diagonal block by all
+// ld = r | 1): fronts taller than the panel waves can cover. The pivot chain
+// by wave 0 beside the updates, then the rows below the diagonal block by all
 // threads (the blocked path's arithmetic). With eight waves or more, those
 // that share wave 0's SIMD (waves 4, 8) stay out of the updates beside the
 // chain, so the pivot chain has its SIMD to itself.
@@ -621,10 +621,10 @@ __device__ __forceinline__ void factor_front(const InstDev& I, const FrontDesc& 
     const int nbc = cp >> 4, nbu = (u + 15) >> 4, nbr = nbc + nbu, rt = nbr << 4;
     // At most four waves factor a panel block (one per 64 rows below its
     // diagonal block), and at least one is left for the updates. Taller
-    // fronts, and those whose blocked panel is over the LDS budget of their
-    // analysis, use a plain column-major panel (leading dimension ld).
+    // fronts, and the few whose blocked panel does not fit, use a plain
+    // column-major panel (leading dimension ld).
     const int maxp = min(4, nwave - 1);
-    const bool blocked = F.pw <= maxp;
+    const bool blocked = front_blocked(r, c, maxp);
     const int shift = blocked ? cp - c : 0;  // panel row of an update row: row + shift
     // place of (row, column) of the front in the LDS panel
     auto place = [&](const int row, const int col) {

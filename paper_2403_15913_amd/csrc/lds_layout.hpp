@@ -30,22 +30,17 @@ KKT_HD constexpr int64_t blocked_lds_bytes(int r, int c) {
     const int64_t nbc = (c + 15) >> 4, rt = 16 * (nbc + ((r - c + 15) >> 4));
     return 8 * kFrontRowStride * (nbc * rt - 8 * nbc * (nbc - 1));
 }
-// Panel waves that a front's blocked panel takes: one covers 64 rows below the
-// diagonal block. A front takes it where the kernel has that many (four, with
-// four waves a workgroup three) and it fits the LDS budget of the analysis: a
-// budget below the default may be one that only the column-major panel fits
-// (the blocked panel's rows are padded twice; at 158 KiB every front that the
-// panel waves cover fits).
-constexpr int kNoBlockedPanel = 1 << 20;
-inline int blocked_panel_waves(int r, int c, int64_t budget) {
+constexpr int64_t kBlockedLdsMax = 158 * 1024;
+// Fronts that take the blocked panel with maxp panel waves: one wave covers 64
+// rows below the diagonal block. The few whose blocked panel is over the
+// budget although the column-major one fits stay column-major.
+KKT_HD constexpr bool front_blocked(int r, int c, int maxp) {
     const int rt = 16 * (((c + 15) >> 4) + ((r - c + 15) >> 4));
-    return blocked_lds_bytes(r, c) <= budget ? (rt - 16 + 63) >> 6 : kNoBlockedPanel;
+    return rt <= 16 + 64 * maxp && blocked_lds_bytes(r, c) <= kBlockedLdsMax;
 }
-// what a front of the factor launches reserves (twelve, eight or four waves:
-// four or three panel waves)
-inline int64_t factor_launch_lds_bytes(int r, int c, int64_t budget) {
-    return blocked_panel_waves(r, c, budget) <= 4 ? std::max(factor_lds_bytes(r, c), blocked_lds_bytes(r, c))
-                                                  : factor_lds_bytes(r, c);
+// what a front of the factor launches reserves (eight or four waves)
+inline int64_t factor_launch_lds_bytes(int r, int c) {
+    return front_blocked(r, c, 4) ? std::max(factor_lds_bytes(r, c), blocked_lds_bytes(r, c)) : factor_lds_bytes(r, c);
 }
 
 // what the fronts' budget counts for the sweeps: (r|1) x c panel (padded to an
