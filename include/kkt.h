@@ -84,8 +84,11 @@ typedef struct kkt_options {
     int32_t max_super;     /* widest supernode in columns (0: 96) */
     int32_t relax_small;   /* supernodes up to this width always amalgamate (0: 16, <0: none) */
     double relax_frac;     /* amalgamation may add up to this fraction of explicit zeros (<0: 0.5) */
-    int32_t front_lds_max; /* LDS bytes one front panel may use (0 or more than 158 KiB: 158 KiB; less
-                              than 4 KiB: 4 KiB). A front too tall to fit at one column is a large
+    int32_t front_lds_max; /* LDS bytes one front panel may use, as the analysis counts it: rows | 1 by the
+                              columns padded to 16, or the sweeps' panel and vectors (0 or more than
+                              158 KiB: 158 KiB; less than 4 KiB: 4 KiB). The launches pad a front to whole
+                              blocks and may reserve up to 5,288 bytes more to factor it and 376 more to
+                              solve with it. A front too tall to fit at one column is a large
                               front: at most 64 columns, assembled, factored and solved in place in HBM
                               by several workgroups per front (its update matrix by one wave per
                               tile); level schedule only, INVALID_ARG if negative */

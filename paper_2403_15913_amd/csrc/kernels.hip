@@ -621,8 +621,7 @@ __device__ __forceinline__ void factor_front(const InstDev& I, const FrontDesc& 
     const int nbc = cp >> 4, nbu = (u + 15) >> 4, nbr = nbc + nbu, rt = nbr << 4;
     // At most four waves factor a panel block (one per 64 rows below its
     // diagonal block), and at least one is left for the updates. Taller
-    // fronts, and the few whose blocked panel does not fit, use a plain
-    // column-major panel (leading dimension ld).
+    // fronts use a plain column-major panel (leading dimension ld).
     const int maxp = min(4, nwave - 1);
     const bool blocked = front_blocked(r, c, maxp);
     const int shift = blocked ? cp - c : 0;  // panel row of an update row: row + shift

@@ -30,15 +30,15 @@ KKT_HD constexpr int64_t blocked_lds_bytes(int r, int c) {
     const int64_t nbc = (c + 15) >> 4, rt = 16 * (nbc + ((r - c + 15) >> 4));
     return 8 * kFrontRowStride * (nbc * rt - 8 * nbc * (nbc - 1));
 }
-constexpr int64_t kBlockedLdsMax = 158 * 1024;
 // Fronts that take the blocked panel with maxp panel waves: one wave covers 64
-// rows below the diagonal block. The few whose blocked panel is over the
-// budget although the column-major one fits stay column-major.
+// rows below the diagonal block. Taller fronts stay column-major. (Every front
+// so covered that fits 158 KiB by front_lds_bytes fits them blocked too.)
 KKT_HD constexpr bool front_blocked(int r, int c, int maxp) {
-    const int rt = 16 * (((c + 15) >> 4) + ((r - c + 15) >> 4));
-    return rt <= 16 + 64 * maxp && blocked_lds_bytes(r, c) <= kBlockedLdsMax;
+    return 16 * (((c + 15) >> 4) + ((r - c + 15) >> 4)) <= 16 + 64 * maxp;
 }
-// what a front of the factor launches reserves (eight or four waves)
+// what a front of the factor launches reserves (twelve, eight or four waves: four
+// or three panel waves); the padding to whole 16-row and 16-column blocks takes
+// it up to 5,288 bytes past the front's budget
 inline int64_t factor_launch_lds_bytes(int r, int c) {
     return front_blocked(r, c, 4) ? std::max(factor_lds_bytes(r, c), blocked_lds_bytes(r, c)) : factor_lds_bytes(r, c);
 }
